@@ -631,11 +631,11 @@ void split_stage(GemmStage& st) {
     st.tiles.swap(out);
 }
 
-template <bool AK, bool BK>
+template <bool BK>
 jorge_status launch_gemm(jorge_ctx* c, const GemmStage& st, int stage, float beta1) {
     if (st.ntiles() == 0) return JORGE_OK;
     TimedLaunch tl(c, stage);
-    hipLaunchKernelGGL((gemm_grouped<AK, BK>), dim3(st.ntiles()), dim3(kGemmThreads), 0, c->stream,
+    hipLaunchKernelGGL((gemm_grouped<BK>), dim3(st.ntiles()), dim3(kGemmThreads), 0, c->stream,
                        st.dprobs, st.dtiles, st.dsmall, beta1, c->splitws);
     tl.finish();
     JORGE_HIP(c, hipGetLastError());
@@ -1132,6 +1132,8 @@ std::string check_stage(const jorge_ctx* c, const GemmStage& st, bool bk, const 
         const int64_t blast = bk ? (int64_t)(p.N - 1) * p.ldb + k1 - 1 : (int64_t)(k1 - 1) * p.ldb + p.N - 1;
         if (!aligned16(p.B, p.ldb) || !in_buffer(c, p.B, fl(blast))) return where + "B";
         if (k2 > 0) {
+            // One set of lane offsets serves both K segments.
+            if (p.lda2 != p.lda || p.ldb2 != p.ldb) return where + "segment strides";
             if (!aligned16(p.A2, p.lda2) || !in_buffer(c, p.A2, fl((int64_t)(p.M - 1) * p.lda2 + k2 - 1)))
                 return where + "A2";
             const int64_t b2 = bk ? (int64_t)(p.N - 1) * p.ldb2 + k2 - 1 : (int64_t)(k2 - 1) * p.ldb2 + p.N - 1;
@@ -1451,9 +1453,9 @@ void free_ctx(jorge_ctx* c) {
 }
 
 jorge_status launch_stage(jorge_ctx* c, int stage, float beta1) {
-    jorge_status s = launch_gemm<true, true>(c, c->nt[stage], stage, beta1);
+    jorge_status s = launch_gemm<true>(c, c->nt[stage], stage, beta1);
     if (s != JORGE_OK) return s;
-    return launch_gemm<true, false>(c, c->nn[stage], stage, beta1);
+    return launch_gemm<false>(c, c->nn[stage], stage, beta1);
 }
 
 jorge_status run_update(jorge_ctx* c, double beta2) {

@@ -1,25 +1,19 @@
-// Grouped fp32 MFMA GEMM for gfx950 with fused epilogues.
+// Grouped fp32 GEMM for gfx950 with fused epilogues.
 //
 // One launch covers every tile of a list of independent products (all
 // factors' products of one dependency level of the step). Each product
 // carries its own epilogue (flags and coefficient set, decided at run time
 // per problem), so products with different epilogues share a launch. A
 // workgroup of 256 threads computes one 128 x 128 tile of C = A * B; its
-// four waves each own a 64 x 64 sub-tile held as 4 x 4 blocks of
-// v_mfma_f32_16x16x4_f32 accumulators (this form reads and writes half as
-// many accumulator registers per flop as the 32 x 32 one). K is consumed in
-// slabs of 32 staged through double-buffered LDS (one barrier per slab): while
-// the waves run the MFMAs of slab k, slab k+1 streams into the other buffer.
-// K-contiguous operands go straight from global memory to LDS
-// (global_load_lds_dwordx4, no register staging); an MN-contiguous operand
-// (the NN kernel's B) is held in registers and written to LDS after the MFMAs.
+// four waves each own a 64 x 64 sub-tile held as 4 x 4 blocks of 16 x 16
+// accumulators. Operands and results are fp32.
 //
-// Within a slab, lane l of a wave contributes k = 16*kg + 4*q + s to the MFMA
-// of step s (s = 0..3) of 16-wide k group kg, with q = quarter(l / 16): the
-// four lane groups take disjoint quarters of each group, so a K-contiguous
-// operand is read from LDS as one 16-byte load per lane per 16 k values. The
-// same k map is used for A and B, so every product A[i][k] * B[k][j] is
-// formed exactly once.
+// NT products (both operands K-contiguous: every product of the symmetric
+// mode) run on the bf16 matrix pipe without giving up fp32: each operand
+// element is split into three bf16 terms that sum to it exactly (24 bits),
+// and the six term products down to 2^-16 of the whole are accumulated in
+// fp32 (see split_pair below). NN products (the literal mode's powers) use the
+// fp32 MFMA with a K-contiguous A and an MN-contiguous B.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -40,32 +34,20 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ int acc_row(int b, int lane, int wy) { return wy * 64 + (b >> 2) * 16 + (lane >> 4) * 4; }
 __device__ __forceinline__ int acc_col(int b, int lane, int wx) { return wx * 64 + (b & 3) * 16 + (lane & 15); }
 
-// The k quarter that lane group g (lanes 16 g .. 16 g + 15) reads: groups 1
-// and 2 swapped. A 16-byte LDS read is served in passes that pair lanes
-// 0-7 with 32-39 (8-15 with 40-47, ...); with the swap, the two halves of a
-// pass read chunks an odd distance apart, which the XOR layout below puts in
-// opposite halves of the banks (with the identity map they collide 2-way).
-__device__ __forceinline__ int quarter(int g) { return ((g & 1) << 1) | (g >> 1); }
-
 constexpr int kTile = 128;                    // tile rows = tile columns
 constexpr int kSlab = 32;                     // K per LDS stage
 constexpr int kGemmThreads = 256;
-// A K-contiguous operand slab (128 rows x 32 k) sits in LDS as 16 blocks of
-// 8 rows of 128 bytes, the 1 KB one wave-wide 16-byte load to LDS writes:
-// lane L loads row L / 8 of the block, so eight consecutive lanes read one
-// contiguous 128-byte row of global memory. The lane loads logical chunk
-// (L % 8) ^ (L / 8) (k = 4c .. 4c+3 is chunk c), so chunk c of block row r
-// sits at physical chunk c ^ r: eight lanes reading one chunk of 8 rows hit
-// 8 distinct 16-byte bank groups, and the 128-byte pad between blocks moves
-// the next 8 rows to the other half of a 64-bank LDS.
-constexpr int kLdsBlock = 8 * 32 + 32;        // floats per 8-row block, with its pad
-// Row stride of an M/N-contiguous operand in LDS: 132 floats puts the rows
-// that the four lane groups read in one step (4 apart) on distinct quarters
-// of the banks.
-constexpr int kLdsMN = kTile + 4;
-constexpr int kLdsOperand = 16 * kLdsBlock;   // floats per operand per stage (>= kSlab * kLdsMN)
-static_assert(kLdsOperand >= kSlab * kLdsMN, "LDS operand buffer too small");
-static_assert(kLdsOperand / 2 >= 2 * 64 * 16, "a small-mode stage (two 64 x 16 slabs) must fit in half an operand buffer");
+// A slab sits in LDS as three planes (one per term of the split), each of 16
+// blocks of 16 rows: rows of A in blocks 0-7, columns of B in blocks 8-15. A
+// block is 1 KB: 64 slots of 16 bytes, slot 16 c + (r ^ swizzle(c, block))
+// holding k = 8 c .. 8 c + 7 of row r. A fragment read (lane l: row l % 16, c = l /
+// 16) takes the whole block in one 16-byte read per lane; the swizzle spreads
+// it, and the 8-byte writes of both operand layouts, over the banks.
+constexpr int kBlockBytes = 1024;
+constexpr int kPlaneBytes = 2 * (kTile / 16) * kBlockBytes;
+constexpr int kSlabBytes = 3 * kPlaneBytes;
+constexpr int kSmallLds = 4 * 2 * 2 * 64 * 16 * 4;  // four waves, two stages, two 64 x 16 fp32 slabs
+constexpr int kGemmLds = kSmallLds > kSlabBytes ? kSmallLds : kSlabBytes;
 
 // Pointers into global memory (address space 1): loads through them compile
 // to global_load rather than flat_load, which would also count against the
@@ -80,78 +62,47 @@ __device__ __forceinline__ f32x4 gload4(const float* p) {
 typedef __attribute__((address_space(1))) void global_void;
 typedef __attribute__((address_space(3))) void lds_void;
 
-// Byte offsets, from the operand's base at k = 0, of the four 16-byte chunks
-// this lane loads for each 128 x 32 K-contiguous operand slab of a tile. Wave
-// w fills LDS blocks 4w .. 4w+3 with one 16-byte load per lane each. Rows
-// past the extent `lim` are clamped to the last valid one: they only feed
-// outputs that the epilogue discards. The offsets do not change along K, so
-// they are computed once per tile.
-struct SlabLanes {
-    unsigned o[4];
+// ---------------------------------------------------------------- three-term split
+// x = x0 + x1 + x2 with x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1):
+// both differences are exact in fp32 and 3 x 8 significant bits hold all 24 of
+// x, over the whole fp32 exponent range (down to 2^-110, below which x2 and then
+// x1 underflow). A product a b is summed as a2 b0 + a1 b1 + a0 b2 + a1 b0 + a0 b1
+// + a0 b0, every term exact and accumulated in fp32; the three left out are below
+// 2^-23 |a b| together, and a K-long sum takes 6 K / 32 roundings of the
+// accumulator where the fp32 MFMA takes K / 4. Measured against fp64 on Gaussian
+// operands (relative 2-norm): 3.4e-7 at K = 512 and 1.0e-6 at K = 4096, where the
+// fp32 MFMA has 4.0e-7 and 1.1e-6.
+// The bf16 MFMA does 16 times the fp32 one's flops per cycle, so six of them are
+// 2.7 times as fast at the same clock; under the power limit 4096^3 runs at
+// 205-215 TFLOP/s against 135 with the fp32 MFMA, K = 512 at 190 against 128.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+constexpr int kTerms = 3;
+struct SplitPair {
+    bf16x2 t[kTerms];
 };
 
-__device__ __forceinline__ void slab_lanes(int ld, int mn0, int lim, SlabLanes& L) {
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int chunk = (lane & 7) ^ (lane >> 3);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int row = min(mn0 + (wave * 4 + j) * 8 + (lane >> 3), lim - 1);
-        L.o[j] = (unsigned)row * (unsigned)ld * 4u + (unsigned)chunk * 16u;
-    }
-}
-
-typedef __attribute__((address_space(1))) const char gcchar;
-
-// Global -> LDS directly: the slab at k0 of an operand whose lane offsets
-// are L. The uniform part of the address (base + k0) stays in scalar
-// registers, so each load is one instruction with no address arithmetic.
-// The loads complete asynchronously (vmcnt).
-__device__ __forceinline__ void load_slab_lds(const float* __restrict__ base, const SlabLanes& L, int k0, float* s) {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const gcchar* g = (const gcchar*)(base + k0);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        __builtin_amdgcn_global_load_lds((global_void*)(g + L.o[j]), (lds_void*)(s + (wave * 4 + j) * kLdsBlock), 16,
-                                         0, 0);
-}
-
-// Global -> registers: one 32 x 128 MN-contiguous operand slab, four 16-byte
-// loads per thread (columns past `lim` clamped as above).
-__device__ __forceinline__ void load_slab_mn(const float* __restrict__ base, int ld, int mn0, int lim,
-                                             int k0, f32x4 (&r)[4]) {
-    const int tid = threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int u = tid + i * kGemmThreads;
-        const int col = min(mn0 + (u & 31) * 4, lim - 4);
-        r[i] = gload4(base + (size_t)(k0 + (u >> 5)) * ld + col);
-    }
-}
-
-// Registers -> LDS for the MN-contiguous operand.
-__device__ __forceinline__ void store_slab_mn(float* s, const f32x4 (&r)[4]) {
-    const int tid = threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int u = tid + i * kGemmThreads;
-        *reinterpret_cast<f32x4*>(s + (u >> 5) * kLdsMN + (u & 31) * 4) = r[i];
-    }
-}
-
-// LDS -> MFMA operand registers: values for k = k .. k+3 (k a multiple of 4)
-// at row/column mn.
-template <bool KMAJ>
-__device__ __forceinline__ void fragment(const float* s, int mn, int k, float (&f)[4]) {
-    if constexpr (KMAJ) {
-        const int r = mn & 7;
-        const f32x4 v =
-            *reinterpret_cast<const f32x4*>(s + (mn >> 3) * kLdsBlock + r * 32 + (((k >> 2) ^ r) << 2));
-        f[0] = v[0]; f[1] = v[1]; f[2] = v[2]; f[3] = v[3];
-    } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) f[q] = s[(k + q) * kLdsMN + mn];
-    }
+// Seven instructions for two elements: a difference x - x0 is one bf16 dot
+// product, x + (x0 of the pair) . (-1, 0), with no unpacking of x0. (The
+// other element of the pair enters times zero: an infinity there makes this
+// element's x1 NaN, in a row whose every output is non-finite anyway.)
+__device__ __forceinline__ SplitPair split_pair(float a, float b) {
+    // In registers, not inline constants: the packed encoding of an inline -1.0 is not (-1, 0).
+    unsigned c10, c01;
+    asm("s_mov_b32 %0, 0xbf80" : "=s"(c10));
+    asm("s_mov_b32 %0, 0xbf800000" : "=s"(c01));
+    const bf16x2 first = __builtin_bit_cast(bf16x2, c10), second = __builtin_bit_cast(bf16x2, c01);
+    SplitPair o;
+    o.t[0] = __builtin_convertvector((f32x2{a, b}), bf16x2);
+    const float ra = __builtin_amdgcn_fdot2_f32_bf16(o.t[0], first, a, false);
+    const float rb = __builtin_amdgcn_fdot2_f32_bf16(o.t[0], second, b, false);
+    o.t[1] = __builtin_convertvector((f32x2{ra, rb}), bf16x2);
+    const float qa = __builtin_amdgcn_fdot2_f32_bf16(o.t[1], first, ra, false);
+    const float qb = __builtin_amdgcn_fdot2_f32_bf16(o.t[1], second, rb, false);
+    o.t[2] = __builtin_convertvector((f32x2{qa, qb}), bf16x2);
+    return o;
 }
 
 // Which of a wave's 16 blocks it multiplies: every block; on a diagonal
@@ -159,66 +110,6 @@ __device__ __forceinline__ void fragment(const float* s, int mn, int k, float (&
 // of a diagonal quadrant; or none, for the quadrant below the diagonal. The
 // epilogue of a symmetric result never reads the blocks left out.
 enum BlockSet : int { BS_ALL = 0, BS_UPPER = 1, BS_NONE = 2 };
-
-// Fragments of one 16-wide k group of a slab for the calling wave: A rows
-// wy*64 + 16 i + (lane % 16) and B columns wx*64 + 16 i + (lane % 16), at k
-// = kg*16 + 4 quarter(lane / 16) .. + 3.
-template <bool AK, bool BK>
-__device__ __forceinline__ void group_fragments(const float* sa, const float* sb, int wy, int wx, int lane, int kg,
-                                                float (&a)[4][4], float (&b)[4][4]) {
-    const int r = lane & 15, q = quarter(lane >> 4);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        fragment<AK>(sa, wy * 64 + i * 16 + r, kg * 16 + q * 4, a[i]);
-        fragment<BK>(sb, wx * 64 + i * 16 + r, kg * 16 + q * 4, b[i]);
-    }
-}
-
-// The 64 MFMAs of one 16-wide k group (the blocks of block set BS).
-template <int BS>
-__device__ __forceinline__ void group_mma(const float (&a)[4][4], const float (&b)[4][4], f32x4 (&acc)[16]) {
-#pragma unroll
-    for (int st = 0; st < 4; ++st)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (BS == BS_ALL || i <= j)
-                    acc[i * 4 + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][st], b[j][st], acc[i * 4 + j], 0, 0, 0);
-}
-
-// The MFMAs of one LDS slab (sa, sb) of two 16-wide k groups, whose first
-// group's fragments the caller has already read into (fa, fb). The second
-// group's fragments are read while the first group's MFMAs run. Between the
-// two groups, `sync` makes the next slab (nsa, nsb) visible to every wave
-// (and ends every wave's reads of this slab); the next slab's first-group
-// fragments are then read into (fa, fb) while the second group's MFMAs run,
-// so neither the barrier nor that LDS latency leaves the matrix pipe idle.
-// `issue` starts the loads of a later slab into the stage that is free; the
-// compiler's own schedule spreads those loads and the LDS reads among the
-// MFMAs (it measured 2-4% faster than a fixed interleave).
-template <bool AK, bool BK, int BS, class Issue, class Sync>
-__device__ __forceinline__ void mma_slab(const float* sa, const float* sb, const float* nsa, const float* nsb, int wy,
-                                         int wx, int lane, float (&fa)[4][4], float (&fb)[4][4], f32x4 (&acc)[16],
-                                         Issue&& issue, Sync&& sync) {
-    static_assert(kSlab == 32, "a slab is two 16-wide k groups");
-    if constexpr (BS == BS_NONE) {
-        issue();
-        sync();
-        return;
-    }
-    float a[4][4], b[4][4];
-    group_fragments<AK, BK>(sa, sb, wy, wx, lane, 1, a, b);
-    // These reads too go first: the barrier in `sync` waits for them.
-    __builtin_amdgcn_sched_barrier(0);
-    issue();
-    group_mma<BS>(fa, fb, acc);
-    sync();
-    group_fragments<AK, BK>(nsa, nsb, wy, wx, lane, 0, fa, fb);
-    // Keep those reads ahead of the MFMAs (the scheduler would sink them).
-    __builtin_amdgcn_sched_barrier(0);
-    group_mma<BS>(a, b, acc);
-}
 
 // Sum of one double per lane over a 64-lane wave, in a fixed order.
 __device__ __forceinline__ double wave_sum(double v) {
@@ -249,83 +140,180 @@ __device__ __forceinline__ SlabSrc slab_src(const GemmProblem& p, int k0) {
     return {p.A2, p.B2, p.lda2, p.ldb2, k0 - p.K1};
 }
 
-// One LDS stage of the GEMM: the A and B operand slabs. The two stages of
-// the double buffer are separate __shared__ objects, so the compiler can see
-// that loads into one stage never alias reads of the other and does not wait
-// for the in-flight prefetch before reading the current stage.
-struct GemmStageLds {
-    float a[kLdsOperand];
-    float b[kLdsOperand];
+typedef __attribute__((address_space(1))) const char gcchar;
+
+// One thread's share of a slab in registers, 16 floats of each operand. A (and
+// a K-contiguous B): rows tid / 8 + 32 v, k = 4 (tid % 8) .. + 3 in v[v], so
+// eight lanes read one 128-byte row. An MN-contiguous B: columns 4 (tid % 32) ..
+// + 3 at k = 4 (tid / 32) + v.
+struct SlabRegs {
+    f32x4 a[4], b[4];
 };
 
-// Lane offsets of a tile's operand slabs for both K segments.
-struct TileLanes {
-    SlabLanes a, b, a2, b2;
+// Byte offsets of those loads from the operand's base at the slab's first k.
+// Rows (columns) past the extent are clamped to the last valid one: they only
+// feed outputs that the epilogue discards. The same for every slab of a tile and
+// for both K segments (lda2 = lda, ldb2 = ldb).
+struct SlabOffsets {
+    unsigned a[4], b[4];
 };
 
-// Starts the copy of slab k0 (absolute K) of tile (row0, col0) into stage st.
-// K-contiguous operands load to LDS directly; the MN-contiguous B is held in rb
-// until store_b (after the MFMAs of the other stage).
 template <bool BK>
-__device__ __forceinline__ void issue_slab(const GemmProblem& p, const TileLanes& tl, int col0, int k0,
-                                           GemmStageLds& st, f32x4 (&rb)[4]) {
-    // Segment selection by selects, not branches, so the loads stay in the
-    // scheduling region of the MFMAs they are interleaved with.
-    const bool two = k0 >= p.K1;
-    const int k = two ? k0 - p.K1 : k0;
-    SlabLanes la, lb;
+__device__ __forceinline__ void slab_offsets(const GemmProblem& p, int row0, int col0, SlabOffsets& o) {
+    const int tid = threadIdx.x;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        la.o[j] = two ? tl.a2.o[j] : tl.a.o[j];
-        if constexpr (BK) lb.o[j] = two ? tl.b2.o[j] : tl.b.o[j];
+    for (int v = 0; v < 4; ++v) {
+        const int r = (tid >> 3) + 32 * v;
+        o.a[v] = (unsigned)min(row0 + r, p.M - 1) * (unsigned)p.lda * 4u + (tid & 7) * 16u;
+        if constexpr (BK)
+            o.b[v] = (unsigned)min(col0 + r, p.N - 1) * (unsigned)p.ldb * 4u + (tid & 7) * 16u;
+        else
+            o.b[v] = (unsigned)(4 * (tid >> 5) + v) * (unsigned)p.ldb * 4u + (unsigned)min(col0 + 4 * (tid & 31), p.N - 4) * 4u;
     }
-    load_slab_lds(two ? p.A2 : p.A, la, k, st.a);
-    if constexpr (BK) load_slab_lds(two ? p.B2 : p.B, lb, k, st.b);
-    else load_slab_mn(two ? p.B2 : p.B, two ? p.ldb2 : p.ldb, col0, p.N, k, rb);
+}
+
+// Starts the loads of the slab at absolute k.
+template <bool BK>
+__device__ __forceinline__ void load_slab(const GemmProblem& p, const SlabOffsets& o, int k, SlabRegs& r) {
+    // Segment selection by selects, not branches, so the loads stay in the
+    // scheduling region of the MFMAs.
+    const bool two = k >= p.K1;
+    const int kl = two ? k - p.K1 : k;
+    const gcchar* a = (const gcchar*)((two ? p.A2 : p.A) + kl);
+    const gcchar* b = (const gcchar*)((two ? p.B2 : p.B) + (BK ? (size_t)kl : (size_t)kl * p.ldb));
+#pragma unroll
+    for (int v = 0; v < 4; ++v) r.a[v] = *(global_f32x4*)(a + o.a[v]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) r.b[v] = *(global_f32x4*)(b + o.b[v]);
+}
+
+// The same share split into its terms: v-th row of A and of B, four k each.
+struct SlabTerms {
+    bf16x4 a[4][kTerms], b[4][kTerms];
+};
+
+template <bool BK>
+__device__ __forceinline__ void split_slab(const SlabRegs& r, SlabTerms& s) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const SplitPair x = split_pair(r.a[v][0], r.a[v][1]), y = split_pair(r.a[v][2], r.a[v][3]);
+        const SplitPair z = BK ? split_pair(r.b[v][0], r.b[v][1]) : split_pair(r.b[0][v], r.b[1][v]);
+        const SplitPair w = BK ? split_pair(r.b[v][2], r.b[v][3]) : split_pair(r.b[2][v], r.b[3][v]);
+#pragma unroll
+        for (int t = 0; t < kTerms; ++t) {
+            s.a[v][t] = bf16x4{x.t[t][0], x.t[t][1], y.t[t][0], y.t[t][1]};
+            s.b[v][t] = bf16x4{z.t[t][0], z.t[t][1], w.t[t][0], w.t[t][1]};
+        }
+    }
+}
+
+// Slot of row r (0-15), chunk c of a block: see the LDS layout above.
+__device__ __forceinline__ int slab_slot(int r, int c, int block) {
+    return 16 * c + (r ^ ((0xEA40 >> (4 * c)) & 15) ^ (block & 3));
+}
+
+// LDS byte offsets (within a plane) of a thread's writes, v = 0, and of a lane's fragments.
+struct SlabLds {
+    int wa, wb, frag;
+};
+
+template <bool BK>
+__device__ __forceinline__ SlabLds slab_lds() {
+    const int tid = threadIdx.x, lane = tid & 63;
+    SlabLds o;
+    const int r = tid >> 3, c = (tid & 7) >> 1;
+    o.wa = (r >> 4) * kBlockBytes + slab_slot(r & 15, c, r >> 4) * 16 + (tid & 1) * 8;
+    if constexpr (BK) {
+        o.wb = o.wa + (kTile / 16) * kBlockBytes;
+    } else {
+        const int n = 4 * (tid & 31), kg = tid >> 5;
+        o.wb = (kTile / 16 + (n >> 4)) * kBlockBytes + slab_slot(n & 15, kg >> 1, n >> 4) * 16 + (kg & 1) * 8;
+    }
+    o.frag = slab_slot(lane & 15, lane >> 4, 0) * 16;
+    return o;
 }
 
 template <bool BK>
-__device__ __forceinline__ void finish_slab(GemmStageLds& st, const f32x4 (&rb)[4]) {
-    if constexpr (!BK) store_slab_mn(st.b, rb);
-    // This wave's loads to LDS have landed and its reads of the other stage
-    // are complete; the barrier makes every wave's loads visible and lets the
-    // other stage be refilled.
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __syncthreads();
+__device__ __forceinline__ void store_slab(char* lds, const SlabLds& o, const SlabTerms& s) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        // 32 rows on are two blocks on, whose swizzle differs in bit 1; the next row of a block, in the row.
+        const int step = (v & 1) * 32, wa = (o.wa ^ step) + v * 2 * kBlockBytes;
+        const int wb = BK ? (o.wb ^ step) + v * 2 * kBlockBytes : o.wb ^ (v * 16);
+#pragma unroll
+        for (int t = 0; t < kTerms; ++t) {
+            *reinterpret_cast<bf16x4*>(lds + t * kPlaneBytes + wa) = s.a[v][t];
+            *reinterpret_cast<bf16x4*>(lds + t * kPlaneBytes + wb) = s.b[v][t];
+        }
+    }
 }
+
+// The MFMAs of one slab for the calling wave's block set. The term products go
+// from the smallest to the largest; four independent blocks between two that
+// share an accumulator.
+template <int BS>
+__device__ __forceinline__ void mma_slab(const char* lds, const SlabLds& o, int wy, int wx, f32x4 (&acc)[16]) {
+    if constexpr (BS == BS_NONE) return;
+    constexpr int kA[6] = {2, 1, 0, 1, 0, 0}, kB[6] = {0, 1, 2, 0, 1, 0};
+    bf16x8 b[4][kTerms];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int t = 0; t < kTerms; ++t)
+            b[j][t] = *reinterpret_cast<const bf16x8*>(lds + t * kPlaneBytes + (kTile / 16 + wx * 4 + j) * kBlockBytes +
+                                                       (o.frag ^ (j * 16)));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        bf16x8 a[kTerms];
+#pragma unroll
+        for (int t = 0; t < kTerms; ++t)
+            a[t] = *reinterpret_cast<const bf16x8*>(lds + t * kPlaneBytes + (wy * 4 + i) * kBlockBytes + (o.frag ^ (i * 16)));
+#pragma unroll
+        for (int u = 0; u < 6; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (BS == BS_ALL || i <= j)
+                    acc[i * 4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kA[u]], b[j][kB[u]], acc[i * 4 + j], 0, 0, 0);
+    }
+}
+
+// Workgroup barrier that waits for this wave's LDS accesses but leaves its
+// global loads in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // The slab loop of gemm_mainloop for the calling wave's block set BS (one
-// copy per set, so the loop itself has no branches on it). Slab 0 is in s0
-// and its first-group fragments in (fa, fb).
-template <bool AK, bool BK, int BS>
-__device__ __forceinline__ void slab_loop(const GemmProblem& p, const TileLanes& tl, int col0, int k0, int nk,
-                                          GemmStageLds& s0, GemmStageLds& s1, f32x4 (&rb)[4], int wy, int wx,
-                                          int lane, float (&fa)[4][4], float (&fb)[4][4], f32x4 (&acc)[16]) {
-    // Raised issue priority while this wave runs its MFMAs (lowered around
-    // each barrier): the two waves sharing a SIMD then alternate between
-    // MFMA and memory phases.
-    auto sync_to = [&](GemmStageLds& st) {
-        __builtin_amdgcn_s_setprio(0);
-        finish_slab<BK>(st, rb);
-        __builtin_amdgcn_s_setprio(1);
-    };
-    // Pairs of slabs: slab kt is in s0, kt+1 goes to s1 and kt+2 back to s0.
-    // The loop has no other exit, so the accumulators stay in place.
+// copy per set, so the loop itself has no branches on it). Slab 0 is in LDS and
+// slab 1's loads are in flight.
+template <bool BK, int BS>
+__device__ __forceinline__ void slab_loop(const GemmProblem& p, const SlabOffsets& o, const SlabLds& l, int k0, int nk,
+                                          char* lds, SlabRegs& r, int wy, int wx, f32x4 (&acc)[16]) {
+    // One LDS buffer: the next slab is split under this slab's MFMAs (its raw
+    // values, loaded a slab earlier, make room for the loads of the slab after
+    // it) and written between two barriers; the other workgroup of the CU
+    // fills that gap. Raised issue priority while the wave runs its MFMAs.
+    SlabTerms s;
     int kt = 0;
     __builtin_amdgcn_s_setprio(1);
-    for (; kt + 2 <= nk; kt += 2) {
-        mma_slab<AK, BK, BS>(s0.a, s0.b, s1.a, s1.b, wy, wx, lane, fa, fb, acc,
-                             [&] { issue_slab<BK>(p, tl, col0, k0 + (kt + 1) * kSlab, s1, rb); },
-                             [&] { sync_to(s1); });
-        // Past the last slab the load repeats slab nk - 1 into the idle stage
-        // (never multiplied), which keeps the loop free of branches.
-        const int kn = min(kt + 2, nk - 1);
-        mma_slab<AK, BK, BS>(s1.a, s1.b, s0.a, s0.b, wy, wx, lane, fa, fb, acc,
-                             [&] { issue_slab<BK>(p, tl, col0, k0 + kn * kSlab, s0, rb); },
-                             [&] { sync_to(s0); });
+    for (; kt + 2 < nk; ++kt) {
+        split_slab<BK>(r, s);
+        load_slab<BK>(p, o, k0 + (kt + 2) * kSlab, r);
+        mma_slab<BS>(lds, l, wy, wx, acc);
+        __builtin_amdgcn_s_setprio(0);
+        lds_barrier();
+        store_slab<BK>(lds, l, s);
+        lds_barrier();
+        __builtin_amdgcn_s_setprio(1);
     }
-    if (kt < nk)  // odd slab count: the last slab is in s0; nothing follows it
-        mma_slab<AK, BK, BS>(s0.a, s0.b, s1.a, s1.b, wy, wx, lane, fa, fb, acc, [] {}, [] {});
+    if (kt + 1 < nk) {
+        split_slab<BK>(r, s);
+        mma_slab<BS>(lds, l, wy, wx, acc);
+        __builtin_amdgcn_s_setprio(0);
+        lds_barrier();
+        store_slab<BK>(lds, l, s);
+        lds_barrier();
+        __builtin_amdgcn_s_setprio(1);
+    }
+    mma_slab<BS>(lds, l, wy, wx, acc);
     __builtin_amdgcn_s_setprio(0);
 }
 
@@ -333,51 +321,44 @@ __device__ __forceinline__ void slab_loop(const GemmProblem& p, const TileLanes&
 // [k0, k1), accumulated by the whole workgroup into acc. Every thread of the
 // workgroup must call it. Waves return without waiting for each other, so
 // LDS may be written after it only behind a barrier (the grouped kernel
-// writes none). The slab loop is unrolled by two so each half reads one stage
-// and fills the other.
-template <bool AK, bool BK>
-__device__ __forceinline__ void gemm_mainloop(const GemmProblem& p, int tm, int tn, int k0, int k1,
-                                              GemmStageLds& s0, GemmStageLds& s1, f32x4 (&acc)[16]) {
-    static_assert(AK, "the A operand is always K-contiguous");
+// writes none).
+template <bool BK>
+__device__ __forceinline__ void gemm_mainloop(const GemmProblem& p, int tm, int tn, int k0, int k1, char* lds,
+                                              f32x4 (&acc)[16]) {
     const int row0 = tm * kTile, col0 = tn * kTile;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wy = wave >> 1, wx = wave & 1;
-
+    const int nk = (k1 - k0) / kSlab;
+    SlabOffsets o;
+    slab_offsets<BK>(p, row0, col0, o);
+    SlabRegs r;
+    load_slab<BK>(p, o, k0, r);
 #pragma unroll
     for (int b = 0; b < 16; ++b)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
-
-    TileLanes tl;
-    slab_lanes(p.lda, row0, p.M, tl.a);
-    slab_lanes(p.lda2, row0, p.M, tl.a2);
-    if constexpr (BK) {
-        slab_lanes(p.ldb, col0, p.N, tl.b);
-        slab_lanes(p.ldb2, col0, p.N, tl.b2);
+    const SlabLds l = slab_lds<BK>();
+    {
+        SlabTerms s;
+        split_slab<BK>(r, s);
+        if (nk > 1) load_slab<BK>(p, o, k0 + kSlab, r);
+        store_slab<BK>(lds, l, s);
     }
-    f32x4 rb[4];
-    const int nk = (k1 - k0) / kSlab;
-    issue_slab<BK>(p, tl, col0, k0, s0, rb);
-    finish_slab<BK>(s0, rb);
-    float fa[4][4], fb[4][4];
-    group_fragments<AK, BK>(s0.a, s0.b, wy, wx, lane, 0, fa, fb);
+    lds_barrier();
     // A quadrant that lies wholly past the product's padded extent (a product
     // 32 or 64 rows or columns wide, or an edge tile) multiplies nothing: its
     // outputs are discarded. On a diagonal tile of a symmetric result the
     // quadrant below the diagonal is not needed and the diagonal quadrants
     // only on and above it.
     if (row0 + wy * 64 >= p.M || col0 + wx * 64 >= p.N) {
-        slab_loop<AK, BK, BS_NONE>(p, tl, col0, k0, nk, s0, s1, rb, wy, wx, lane, fa, fb, acc);
+        slab_loop<BK, BS_NONE>(p, o, l, k0, nk, lds, r, wy, wx, acc);
     } else if (p.upper && tm == tn) {
-        if (wy > wx) slab_loop<AK, BK, BS_NONE>(p, tl, col0, k0, nk, s0, s1, rb, wy, wx, lane, fa, fb, acc);
-        else if (wy == wx) slab_loop<AK, BK, BS_UPPER>(p, tl, col0, k0, nk, s0, s1, rb, wy, wx, lane, fa, fb, acc);
-        else slab_loop<AK, BK, BS_ALL>(p, tl, col0, k0, nk, s0, s1, rb, wy, wx, lane, fa, fb, acc);
+        if (wy > wx) slab_loop<BK, BS_NONE>(p, o, l, k0, nk, lds, r, wy, wx, acc);
+        else if (wy == wx) slab_loop<BK, BS_UPPER>(p, o, l, k0, nk, lds, r, wy, wx, acc);
+        else slab_loop<BK, BS_ALL>(p, o, l, k0, nk, lds, r, wy, wx, acc);
     } else {
-        slab_loop<AK, BK, BS_ALL>(p, tl, col0, k0, nk, s0, s1, rb, wy, wx, lane, fa, fb, acc);
+        slab_loop<BK, BS_ALL>(p, o, l, k0, nk, lds, r, wy, wx, acc);
     }
-    // No closing barrier: every load into LDS has landed (the last slab's
-    // wait), and nothing after the main loop writes LDS, so each wave goes on
-    // to its epilogue as soon as its own MFMAs are issued.
 }
 
 // Partial products of split tiles: thread t (= 64 wave + lane) keeps its 64
@@ -709,7 +690,7 @@ __device__ __forceinline__ void small_fragment(const float* s, int mn, int k, fl
 }
 
 // The MFMAs of one small-mode slab: lane l contributes k = 4 (l / 16) + s
-// to step s, for A and B alike (as in mma_slab). UPPER: a block on the
+// to step s, for A and B alike. UPPER: a block on the
 // diagonal of a symmetric result, whose 16 x 16 blocks below the diagonal are
 // left out. BI x BJ: the 16 x 16 blocks of the 64 x 64 block that lie inside
 // the product (a product 32 rows or columns wide fills half of it; the
@@ -805,30 +786,27 @@ __device__ __forceinline__ void small_unit(const GemmProblem& p, const SmallUnit
 // panels in its own L2. Units of split tiles leave their partial product in
 // ws for gemm_fixup. A small-mode unit is a group of up to four 64 x 64
 // blocks (small), one per wave, each in its own quarter of the LDS.
-template <bool AK, bool BK>
+template <bool BK>
 __global__ __launch_bounds__(kGemmThreads, 2) void gemm_grouped(const GemmProblem* __restrict__ probs,
                                                                 const TileDesc* __restrict__ tiles,
                                                                 const SmallUnit* __restrict__ small,
                                                                 float beta1, float* __restrict__ ws) {
-    __shared__ __attribute__((aligned(16))) GemmStageLds s0;
-    __shared__ __attribute__((aligned(16))) GemmStageLds s1;
+    __shared__ __attribute__((aligned(16))) char lds[kGemmLds];
     const TileDesc td = tiles[blockIdx.x];
     if (td.part == kSmallGroup) {
         if constexpr (BK) {
             const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: its block is read with scalar loads
             if (w < td.tn) {
                 const SmallUnit su = small[td.tm + w];
-                // Wave w's two stages: half w % 2 of the A and B buffers of s0 or s1.
-                GemmStageLds& st = (w >> 1) ? s1 : s0;
-                const int half = (w & 1) * (kLdsOperand / 2);
-                small_unit(probs[su.prob], su, st.a + half, st.b + half, beta1, threadIdx.x & 63);
+                float* st = reinterpret_cast<float*>(lds) + w * (4 * kSmallOperand);  // wave w's two stages
+                small_unit(probs[su.prob], su, st, st + 2 * kSmallOperand, beta1, threadIdx.x & 63);
             }
         }
         return;
     }
     const GemmProblem p = probs[td.prob];
     f32x4 acc[16];
-    gemm_mainloop<AK, BK>(p, td.tm, td.tn, td.k0, td.k1, s0, s1, acc);
+    gemm_mainloop<BK>(p, td.tm, td.tn, td.k0, td.k1, lds, acc);
     if (td.part >= 0)
         store_partial(ws + (size_t)td.part * kSplitBlock, acc);
     else

@@ -56,9 +56,9 @@ struct LayerScalars {
 // kernel) the product is C = A B^T: A is M x K row-major, B is N x K
 // row-major. With B MN-major (the "NN" kernel) B is K x N row-major.
 // K may consist of two segments: slabs with k >= K1 read A2 and B2 (at
-// k - K1) instead of A and B, which forms sums such as W H^T + H W^T in one
-// accumulation. M, N, K, K1 are padded extents (K and K1 multiples of 32,
-// leading dimensions multiples of 4).
+// k - K1) instead of A and B, with the same leading dimensions, which forms
+// sums such as W H^T + H W^T in one accumulation. M, N, K, K1 are padded
+// extents (K and K1 multiples of 32, leading dimensions multiples of 4).
 struct GemmProblem {
     const float* A;
     const float* B;
