@@ -48,11 +48,11 @@
 //             update's own terms instead (low-rank preconditioning)
 //   lfinal    ||m||, ||m_SGD||, grafted step g
 //   weight    theta <- theta (1 - lr wd) - g m
-// When every factor has padded size up to hp.lds_chain_max (at most 128), the
-// levels are replaced by LDS chain kernels, which run each factor's whole
-// explicit-order update in one workgroup with its matrices in LDS
-// (lds_chain_kernel up to 64, lds_chain128_kernel for 96 and 128; one launch
-// each for all their factors).
+// When every factor has padded size up to hp.lds_chain_max (at most 128), none of
+// these launches runs: the small-context kernels take the whole step with their
+// matrices in LDS (up to 64: small_step64_kernel, one workgroup per layer; up to
+// 128: small_chain128_kernel, one per factor, then small_apply128_kernel, one
+// per layer).
 // Non-update steps run stage-in, precond, lfinal and weight only.
 #include <hip/hip_runtime.h>
 
@@ -132,7 +132,7 @@ struct FactorHost {
     int layer, side, d, dp, k, kp;
     bool expl = true;
     bool squared = false;  // (not explicit) the squared order: A^2 formed, the chain in steps of A^2
-    bool chain = false;  // small: the whole update in one workgroup (an LDS chain kernel), explicit order
+    bool chain = false;  // in a small context: the whole update in one team of waves, explicit order
     // Low-rank preconditioning on update steps (factored, symmetric, d > 3k): the
     // layer's A_new H comes from the chain's A H, W, Q and H^T W (see add_factored).
     bool lrp = false;
@@ -172,13 +172,13 @@ struct jorge_ctx {
     std::vector<FlatChunk> flat_chunks;
     std::vector<int> stage_batch_start, flat_batch_start;  // first block of each layer batch
     std::vector<SymTile> sym_tiles;
-    // factors of the grouped levels, of the LDS chain (padded size <= 64) and of
-    // the LDS chain for padded sizes 96 and 128
-    std::vector<int> grouped, chain, chain2;
+    // Factors of the grouped levels; in a small context (none of those), its
+    // factors, batch by batch of kPtrBatch layers, largest first in each.
+    std::vector<int> grouped, chain;
     int* dgrouped = nullptr;
     int* dchain = nullptr;
-    int* dchain2 = nullptr;
-    double chain_flops = 0.0;  // algorithmic flops of the chains' factor updates
+    int small = 0;  // 64 or 128: a small context of that size class (0: the grouped levels)
+    double chain_flops = 0.0;  // algorithmic flops of a small context's update step
     float* splitws = nullptr;     // partial products of split tiles (shared by the stages, in turn)
     int64_t splitws_blocks = 0;
     // Per stage: products with both operands K-major, and (literal mode only)
@@ -662,7 +662,7 @@ jorge_status validate_hparams(const jorge_hparams* hp) {
         return JORGE_ERR_INVALID_ARGUMENT;
     if (hp->factor_form == JORGE_FORM_SQUARED && hp->symmetrize != 1) return JORGE_ERR_INVALID_ARGUMENT;
     if (hp->split_k != 0 && hp->split_k != 1) return JORGE_ERR_INVALID_ARGUMENT;
-    if (hp->lds_chain_max < 0 || hp->lds_chain_max > kChain2Max) return JORGE_ERR_INVALID_ARGUMENT;
+    if (hp->lds_chain_max < 0 || hp->lds_chain_max > Team128::D) return JORGE_ERR_INVALID_ARGUMENT;
     if (hp->precond_lowrank != 0 && hp->precond_lowrank != 1) return JORGE_ERR_INVALID_ARGUMENT;
     if (hp->series_order != 2 && hp->series_order != 3) return JORGE_ERR_INVALID_ARGUMENT;
     return JORGE_OK;
@@ -706,16 +706,14 @@ size_t plan(jorge_ctx* c) {
         return o;
     };
     const bool sym = c->hp.symmetrize != 0;
-    // The LDS chains take the factor updates (explicit order, one workgroup per
-    // factor) when every factor of the context has padded size up to
-    // lds_chain_max, replacing the grouped levels altogether (sizes 96 and 128
-    // need symmetric factors). With any larger factor present the levels run
-    // anyway, and the small factors' tiles fill slots of theirs that would
-    // otherwise idle: taking the small factors out to the chains, on a second
-    // stream beside the levels or before them, measured no faster.
+    // The small-context kernels take the step when every factor of the context
+    // has padded size up to lds_chain_max (sizes 96 and 128 need symmetric
+    // factors). With any larger factor present the levels run anyway, and the
+    // small factors' tiles fill slots of theirs that would otherwise idle.
     int max_dp = 0;
     for (const auto& L : c->layers) max_dp = std::max(max_dp, std::max(L.mp, L.np));
-    const bool all_small = max_dp <= c->hp.lds_chain_max && (max_dp <= kChainMax || sym);
+    const bool all_small = max_dp <= c->hp.lds_chain_max && (max_dp <= Team64::D || sym);
+    c->small = !all_small ? 0 : max_dp <= Team64::D ? Team64::D : Team128::D;
     for (auto& L : c->layers) {
         for (int side = 0; side < 2; ++side) {
             FactorHost F{};
@@ -738,7 +736,7 @@ size_t plan(jorge_ctx* c) {
             const size_t dd = (size_t)F.dp * F.dp * sizeof(float);
             F.off_A = take(dd);
             if (F.chain) {
-                F.nparts = 1;  // unused: the chain kernel reduces ||X|| itself
+                F.nparts = 1;  // unused: the team reduces ||X|| itself
                 // the explicit order's algorithmic flops (symmetric products counted once)
                 const double d = F.d, k = F.k;
                 c->chain_flops += d * d * k + (sym ? 2.0 : 4.0) * d * d * d +
@@ -771,9 +769,13 @@ size_t plan(jorge_ctx* c) {
         }
         const size_t padded = (size_t)L.mp * L.np * sizeof(float);
         const size_t dense = (size_t)L.m * L.n * sizeof(float);
-        L.off_Gp = take(padded);
-        L.off_Gpt = take(padded);
-        L.off_T = take(padded);
+        if (!c->small) {
+            L.off_Gp = take(padded);
+            L.off_Gpt = take(padded);
+            L.off_T = take(padded);
+        } else {
+            c->chain_flops += 2.0 * L.m * L.n * ((double)L.m + L.n);  // L G R
+        }
         L.off_mom = take(dense);
         L.off_msgd = take(dense);
         L.n_part_m = tile_count(L.mp, L.np);
@@ -987,7 +989,7 @@ void build_tables(jorge_ctx* c, std::vector<LayerDev>& ld, std::vector<FactorDev
         d.partials = at<double>(c, F.off_part);
         d.Z = (F.expl && !F.chain) ? at<float>(c, F.off_w[1]) : nullptr;
         const auto& L = c->layers[F.layer];
-        d.H = at<float>(c, F.side == 0 ? L.off_Gp : L.off_Gpt);
+        d.H = c->small ? nullptr : at<float>(c, F.side == 0 ? L.off_Gp : L.off_Gpt);
         d.d = F.d;
         d.dp = F.dp;
         d.k = F.k;
@@ -999,9 +1001,11 @@ void build_tables(jorge_ctx* c, std::vector<LayerDev>& ld, std::vector<FactorDev
     for (int li = 0; li < nl; ++li) {
         auto& L = c->layers[li];
         LayerDev d{};
-        d.Gp = at<float>(c, L.off_Gp);
-        d.Gpt = at<float>(c, L.off_Gpt);
-        d.T = at<float>(c, L.off_T);
+        if (!c->small) {
+            d.Gp = at<float>(c, L.off_Gp);
+            d.Gpt = at<float>(c, L.off_Gpt);
+            d.T = at<float>(c, L.off_T);
+        }
         d.mom = at<float>(c, L.off_mom);
         d.msgd = at<float>(c, L.off_msgd);
         d.part_m = at<double>(c, L.off_part_m);
@@ -1012,6 +1016,16 @@ void build_tables(jorge_ctx* c, std::vector<LayerDev>& ld, std::vector<FactorDev
         d.n_part_m = L.n_part_m;
         d.n_part_sgd = L.n_part_sgd;
         ld.push_back(d);
+    }
+    if (c->small) {
+        // Each batch's factors, largest first.
+        c->chain.resize(c->factors.size());
+        for (size_t i = 0; i < c->chain.size(); ++i) c->chain[i] = (int)i;
+        std::stable_sort(c->chain.begin(), c->chain.end(), [&](int a, int b) {
+            if (a / (2 * kPtrBatch) != b / (2 * kPtrBatch)) return a < b;
+            return c->factors[a].dp > c->factors[b].dp;
+        });
+        return;
     }
     // Per-layer block lists, batched by kPtrBatch layers (user pointers go in kernel arguments).
     for (int li = 0; li < nl; ++li) {
@@ -1041,10 +1055,6 @@ void build_tables(jorge_ctx* c, std::vector<LayerDev>& ld, std::vector<FactorDev
         // H row-major (d x k) and H^T row-major (k x d): G and G^T for L, the reverse for R.
         const float* Hr = F.side == 0 ? l.Gp : l.Gpt;
         const float* Ht = F.side == 0 ? l.Gpt : l.Gp;
-        if (F.chain) {
-            (F.dp <= kChainMax ? c->chain : c->chain2).push_back(fi);
-            continue;
-        }
         c->grouped.push_back(fi);
         if (F.expl) {
             add_explicit(c, F, fd[fi], Hr);
@@ -1053,7 +1063,7 @@ void build_tables(jorge_ctx* c, std::vector<LayerDev>& ld, std::vector<FactorDev
             const FactorHost& O = c->factors[F.side == 0 ? L.fR : L.fL];
             // (The explicit factor keeps its statistic until the next step's gram level,
             // past the low-rank preconditioning that reads Q.)
-            const float* Mo = (O.expl && !O.chain) ? at<float>(c, O.off_w[0]) : nullptr;
+            const float* Mo = O.expl ? at<float>(c, O.off_w[0]) : nullptr;
             F.nparts = add_factored(c, F, fd[fi], Hr, Ht, Mo);
             fd[fi].nparts = F.nparts;
         }
@@ -1293,20 +1303,26 @@ std::string check_tables(const jorge_ctx* c, const std::vector<FactorDev>& fd) {
     for (const FactorDev& F : fd)
         if (!in_buffer(c, F.partials, (int64_t)F.nparts * kWaveSlots * (int64_t)sizeof(double)) || F.nparts < 1)
             return "factor partials";
-    // The LDS chain kernels: A (dp x dp), H (dp x kp), scalars; dp <= 64 for
-    // lds_chain_kernel, 64 < dp <= 128 (symmetric factors) for lds_chain128_kernel.
-    for (int which = 0; which < 2; ++which)
-        for (int fi : which ? c->chain2 : c->chain) {
+    // The small-context kernels: every factor (index 2 layer + side) once, of a size
+    // its team takes, with its state, and each layer's momenta.
+    if (c->small) {
+        std::vector<char> seen(fd.size(), 0);
+        for (size_t i = 0; i < c->chain.size(); ++i) {
+            const int fi = c->chain[i];
+            if (fi < 0 || fi >= (int)fd.size() || seen[fi]++ || fi / (2 * kPtrBatch) != (int)i / (2 * kPtrBatch))
+                return "small context factor list";
             const FactorDev& F = fd[fi];
-            const bool size_ok = which ? (F.dp > kChainMax && F.dp <= kChain2Max && c->hp.symmetrize)
-                                       : F.dp <= kChainMax;
-            if (!size_ok || F.dp % 32 || F.kp % kSlab || F.kp < kSlab ||
+            const auto& L = c->layers[fi / 2];
+            const int64_t dense = (int64_t)L.m * L.n * (int64_t)sizeof(float);
+            if ((fi & 1 ? L.fR : L.fL) != fi || F.dp > c->small || F.kp > c->small || F.dp % 32 || F.kp % 32 ||
+                (c->small > Team64::D && !c->hp.symmetrize) ||
                 !in_buffer(c, F.A, (int64_t)F.dp * F.dp * (int64_t)sizeof(float)) ||
-                !in_buffer(c, F.H, (int64_t)F.dp * F.kp * (int64_t)sizeof(float)) ||
-                !in_buffer(c, F.sc, (int64_t)sizeof(FactorScalars)))
-                return "lds chain factor";
+                !in_buffer(c, F.sc, (int64_t)sizeof(FactorScalars)) || !in_buffer(c, c->arena + L.off_mom, dense) ||
+                !in_buffer(c, c->arena + L.off_msgd, dense))
+                return "small context factor";
         }
-    if (c->grouped.size() + c->chain.size() + c->chain2.size() != fd.size()) return "factor lists";
+    }
+    if (c->grouped.size() + c->chain.size() != fd.size()) return "factor lists";
     return "";
 }
 
@@ -1402,7 +1418,6 @@ jorge_status upload_tables(jorge_ctx* c, const std::vector<LayerDev>& ld, const 
     if ((st = upload(c, c->sym_tiles, &c->dsym)) != JORGE_OK) return st;
     if ((st = upload(c, c->grouped, &c->dgrouped)) != JORGE_OK) return st;
     if ((st = upload(c, c->chain, &c->dchain)) != JORGE_OK) return st;
-    if ((st = upload(c, c->chain2, &c->dchain2)) != JORGE_OK) return st;
     for (int i = 0; i < ST_COUNT; ++i)
         for (GemmStage* s : {&c->nt[i], &c->nn[i]})
             if ((st = upload_stage(c, *s)) != JORGE_OK) return st;
@@ -1412,8 +1427,7 @@ jorge_status upload_tables(jorge_ctx* c, const std::vector<LayerDev>& ld, const 
 // What upload_tables places in a lent pool.
 size_t tables_bytes(const jorge_ctx* c, const std::vector<LayerDev>& ld, const std::vector<FactorDev>& fd) {
     size_t b = table_bytes(ld) + table_bytes(fd) + table_bytes(c->stage_tiles) + table_bytes(c->flat_chunks) +
-               table_bytes(c->sym_tiles) + table_bytes(c->grouped) + table_bytes(c->chain) +
-               table_bytes(c->chain2);
+               table_bytes(c->sym_tiles) + table_bytes(c->grouped) + table_bytes(c->chain);
     for (int i = 0; i < ST_COUNT; ++i)
         for (const GemmStage* s : {&c->nt[i], &c->nn[i]})
             b += table_bytes(s->probs) + table_bytes(s->fix) + table_bytes(s->small) + table_bytes(s->tiles);
@@ -1441,7 +1455,6 @@ void free_ctx(jorge_ctx* c) {
     if (c->dsym) (void)hipFree(c->dsym);
     if (c->dgrouped) (void)hipFree(c->dgrouped);
     if (c->dchain) (void)hipFree(c->dchain);
-    if (c->dchain2) (void)hipFree(c->dchain2);
     if (c->arena) (void)hipFree(c->arena);
     for (auto& l : c->pending) {
         (void)hipEventDestroy(l.start);
@@ -1460,22 +1473,6 @@ jorge_status launch_stage(jorge_ctx* c, int stage, float beta1) {
 
 jorge_status run_update(jorge_ctx* c, double beta2) {
     jorge_status s;
-    // The LDS chains: every factor of the context (the levels below are then empty).
-    if (!c->chain2.empty()) {
-        TimedLaunch tl(c, ST_LDS_CHAIN);
-        hipLaunchKernelGGL(lds_chain128_kernel, dim3((unsigned)c->chain2.size()), dim3(kC2Threads), 0, c->stream,
-                           c->dfactors, c->dchain2, beta2, (int)c->hp.beta_mode, (int)c->hp.series_order);
-        tl.finish();
-        JORGE_HIP(c, hipGetLastError());
-    }
-    if (!c->chain.empty()) {
-        TimedLaunch tl(c, ST_LDS_CHAIN);
-        hipLaunchKernelGGL(lds_chain_kernel, dim3((unsigned)c->chain.size()), dim3(kGemmThreads), 0, c->stream,
-                           c->dfactors, c->dchain, beta2, (int)c->hp.beta_mode, (int)c->hp.symmetrize,
-                           (int)c->hp.series_order);
-        tl.finish();
-        JORGE_HIP(c, hipGetLastError());
-    }
     for (int lv : kLevels) {
         if (lv == ST_POLY && !c->grouped.empty()) {  // every grouped factor's nu is complete after chain5
             TimedLaunch tl(c, ST_FFINAL);
@@ -1505,11 +1502,55 @@ struct NoallocDevice {
 };
 NoallocDevice g_noalloc[kMaxDevices];
 
+// The whole step of a small context (a factor-updating one or not).
+jorge_status launch_small(jorge_ctx* c, float* const* params, const float* const* grads, bool update, double lr,
+                          double beta2, double beta1, double weight_decay) {
+    const int nl = (int)c->layers.size();
+    const StepScalars sc{lr, weight_decay, (float)beta1, (int)c->hp.graft};
+    for (int i = 0; i < nl; ++i)
+        if ((reinterpret_cast<uint64_t>(params[i]) | reinterpret_cast<uint64_t>(grads[i])) >> 48)
+            return fail(c, JORGE_ERR_UNSUPPORTED, "a tensor's address has more than 48 bits");
+    for (int l0 = 0; l0 < nl; l0 += kPtrBatch) {
+        const int n = std::min(kPtrBatch, nl - l0);
+        PtrPack pp{};
+        for (int i = 0; i < n; ++i) {
+            pp.set(2 * i, reinterpret_cast<uint64_t>(grads[l0 + i]));
+            pp.set(2 * i + 1, reinterpret_cast<uint64_t>(params[l0 + i]));
+        }
+        if (c->small == Team64::D) {
+            TimedLaunch tl(c, ST_LDS_CHAIN);
+            hipLaunchKernelGGL(small_step64_kernel, dim3(n), dim3(kSmallThreads), 0, c->stream, c->dlayers, c->dfactors,
+                               l0, pp, sc, (int)update, beta2, (int)c->hp.beta_mode, (int)c->hp.symmetrize,
+                               (int)c->hp.series_order);
+            tl.finish();
+            JORGE_HIP(c, hipGetLastError());
+            continue;
+        }
+        if (update) {
+            PtrBatch pb{};
+            for (int i = 0; i < n; ++i) pb.p[i] = grads[l0 + i];
+            TimedLaunch tl(c, ST_LDS_CHAIN);
+            hipLaunchKernelGGL(small_chain128_kernel, dim3(2 * n), dim3(kSmallThreads), 0, c->stream, c->dfactors,
+                               c->dchain + 2 * l0, c->dlayers, l0, pb, beta2, (int)c->hp.beta_mode,
+                               (int)c->hp.series_order);
+            tl.finish();
+            JORGE_HIP(c, hipGetLastError());
+        }
+        TimedLaunch tl(c, ST_LDS_CHAIN);
+        hipLaunchKernelGGL(small_apply128_kernel, dim3(n), dim3(kSmallThreads), 0, c->stream, c->dlayers, c->dfactors,
+                           l0, pp, sc);
+        tl.finish();
+        JORGE_HIP(c, hipGetLastError());
+    }
+    return JORGE_OK;
+}
+
 // The launches of step t (everything jorge_step queues after validating).
 jorge_status launch_step(jorge_ctx* c, float* const* params, const float* const* grads, int64_t t, double lr,
                          double beta2, double beta1, double weight_decay) {
     const int nl = (int)c->layers.size();
     const bool update = (t - 1) % c->hp.precond_interval == 0;
+    if (c->small) return launch_small(c, params, grads, update, lr, beta2, beta1, weight_decay);
     const int nbatch = (nl + kPtrBatch - 1) / kPtrBatch;
     for (int b = 0; b < nbatch; ++b) {
         PtrBatch pb{};
@@ -1582,7 +1623,7 @@ jorge_status jorge_hparams_default(jorge_hparams* hp) {
     hp->symmetrize = 1;
     hp->factor_form = JORGE_FORM_AUTO;
     hp->split_k = 1;
-    hp->lds_chain_max = kChain2Max;
+    hp->lds_chain_max = Team128::D;
     hp->precond_lowrank = 1;
     hp->series_order = 2;
     return JORGE_OK;

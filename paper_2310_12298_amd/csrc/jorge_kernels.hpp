@@ -137,11 +137,11 @@ __device__ __forceinline__ FactorScalars factor_scalars(double nu, double beta2,
     if (dyn) {
         out.beta = nu / (nu + 1.0);
         out.c = 1.0 / nu;
-        out.s = pow(1.0 + 1.0 / nu, 0.25);
+        out.s = sqrt(sqrt(1.0 + 1.0 / nu));  // (1 + 1/nu)^(1/4)
     } else {
         out.beta = beta2;
         out.c = (1.0 - beta2) / beta2;
-        out.s = pow(beta2, -0.25);
+        out.s = 1.0 / sqrt(sqrt(beta2));     // beta2^(-1/4)
     }
     out.nu = nu;
     out.a = (float)(0.25 * out.c);
@@ -223,450 +223,537 @@ __global__ __launch_bounds__(kEwThreads) void symmetrize_kernel(const FactorDev*
     symmetrize_pair(f[st.factor], st.ti, st.tj, symmetrize, za, zb);
 }
 
-// ---------------------------------------------------------------- LDS chain
-// The whole update of a small factor (padded size dp <= 64) by one
-// workgroup, in the explicit order of Algorithm 2 with every matrix resident
-// in LDS: M = H H^T (H streamed from global memory in 32-column slabs),
-// A^2, A^4, X = A^4 M with ||X||_F, (beta, c, s) (Appendix A.1, Eq. 8-9),
-// P = I - (c/4) X + (5c^2/32) X X (Eq. 6), Z = s A P and A <- (Z + Z^T)/2
-// (or Z). With series order 3, P = I - a X + X V with V = b X - e X X keeps
-// the cubic term of Eq. 5. One launch replaces the grouped levels for these
-// factors.
-// Each of the four waves owns one 32 x 32 block of a 64 x 64 product
-// (v_mfma_f32_32x32x2_f32); blocks outside dp are skipped.
-constexpr int kChainMax = 64;
-constexpr int kChainLd = kChainMax + 1;          // LDS row stride: column reads hit 32 distinct banks
-constexpr int kChainMat = kChainMax * kChainLd;  // floats per LDS matrix
-constexpr int kChainSlabLd = kSlab + 1;
+// ---------------------------------------------------------------- small contexts
+// Contexts whose factors all have padded size <= 128. A factor's whole update
+// runs in one team of waves, in the explicit order of Algorithm 2 with its
+// matrices in LDS: A^2, A^4, M = H H^T, X = A^4 M with ||X||_F, (beta, c, s)
+// (Appendix A.1, Eq. 8-9), P = I - (c/4) X + (5c^2/32) X X (Eq. 6; with series
+// order 3, P = I - a X + X V, V = b X - e X X), Z = s A P and A <- (Z + Z^T)/2 (or
+// Z). The rest of the step (m_SGD, L G R, momentum, norms, grafted weight update)
+// runs in one workgroup per layer, which holds the gradient in LDS and sums the
+// norms itself, so nothing of the step but its state passes through memory.
+//
+// Every product is C = A B with both operands held in LDS as fp32 rows that
+// are contiguous in k: A's rows and B's columns (the rows of B^T). They are
+// split into bf16 terms as they are read (split_pair_trunc): a piece of 16 BI x
+// 16 BJ costs BI + BJ splits per 6 BI BJ MFMAs. What bounds a team is the chain
+// of six dependent products with barriers between them.
 
-struct ChainLds {
-    float A[kChainMat];
-    float M[kChainMat];
-    float T1[kChainMat];
-    float T2[kChainMat];
-    float H[kChainMax * kChainSlabLd];
-    double red[4];
-    float coef[4];  // a, b, s, e
+// A team of WAVES waves works on matrices of at most D x D; its product is cut
+// into pieces of 16 BI x 16 BJ, one per wave, GRID_X to a row.
+template <int D_, int WAVES_, int BI_, int BJ_>
+struct Team {
+    static constexpr int D = D_, WAVES = WAVES_, BI = BI_, BJ = BJ_, THREADS = 64 * WAVES_;
+    static constexpr int GRID_X = D_ / (16 * BJ_);
+    static constexpr int LD = D_ + 4;              // LDS row stride: 16-byte reads of 16 rows fall in distinct bank quads
+    static constexpr int MAT = D_ * LD;            // floats per LDS matrix
+    static constexpr int AV = D_ * D_ / 4 / THREADS;  // 16-byte pieces of a factor per thread
+    static constexpr int GV = D_ * D_ / THREADS;      // gradient elements per thread
+    static_assert(WAVES_ / GRID_X * 16 * BI_ == D_, "the pieces cover the product");
 };
+typedef Team<64, 4, 2, 2> Team64;     // a factor of a layer with m, n <= 64
+typedef Team<128, 8, 4, 2> Team128;   // a factor up to 128; the rest of a layer's step
+typedef Team<64, 8, 2, 1> Apply64;    // the rest of the step of a layer with m, n <= 64
+constexpr int kSmallThreads = 512;
 
-// acc += A (rows wy*32.., lda) x B (cols wx*32.., ldb) over k in [0, K): both
-// operands in LDS; BT reads B transposed (B[k][col] = Bm[col][k]).
-// K is a multiple of 32; each group of 16 k has all its LDS reads issued
-// before its 8 MFMAs.
-template <bool BT>
-__device__ __forceinline__ void chain_mma(const float* a, int lda, const float* b, int ldb, int K, int wy, int wx,
-                                          f32x16& acc) {
-    const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
-    for (int t0 = 0; t0 < K; t0 += 16) {
-        float av[8], bv[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int t = t0 + 2 * u + h;
-            av[u] = a[(wy * 32 + r) * lda + t];
-            bv[u] = BT ? b[(wx * 32 + r) * ldb + t] : b[t * ldb + wx * 32 + r];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u], bv[u], acc, 0, 0, 0);
-    }
-}
-
-// C (LDS) = the wave's accumulator block; f(row, col, value) gives the stored value.
-template <typename Fn>
-__device__ __forceinline__ void chain_store(float* c, int wy, int wx, const f32x16& acc, Fn f) {
-    const int lane = threadIdx.x & 63, h = lane >> 5;
-    const int col = wx * 32 + (lane & 31);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int row = wy * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
-        c[row * kChainLd + col] = f(row, col, acc[e]);
-    }
-}
-
-__global__ __launch_bounds__(kGemmThreads) void lds_chain_kernel(const FactorDev* __restrict__ f,
-                                                                 const int* __restrict__ list, double beta2,
-                                                                 int mode, int symmetrize, int order) {
-    __shared__ __attribute__((aligned(16))) ChainLds sm;
-    const FactorDev F = f[list[blockIdx.x]];
-    const int dp = F.dp, tid = threadIdx.x;
-    const int wave = tid >> 6, wy = wave >> 1, wx = wave & 1;
-    const bool active = wy * 32 < dp && wx * 32 < dp;  // this wave's block lies inside dp x dp
-    auto zero = [](f32x16& a) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) a[e] = 0.0f;
-    };
-
-    for (int e = tid; e < dp * dp; e += kGemmThreads) sm.A[(e / dp) * kChainLd + e % dp] = F.A[e];
-
-    // M = H H^T, H streamed in slabs of 32 columns: each thread holds its
-    // (up to) 8 floats of the next slab in registers while the current one is
-    // multiplied. Thread t covers rows t/8 and 32 + t/8, columns 4 (t%8) .. +3.
-    f32x16 acc;
-    zero(acc);
-    const int hr = tid >> 3, hc = (tid & 7) * 4;
-    f32x4 hv[2];
-    auto load_h = [&](int k0) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int r = hr + 32 * q;
-            if (r < dp) hv[q] = *(const f32x4*)(F.H + (size_t)r * F.kp + k0 + hc);
-        }
-    };
-    load_h(0);
-    for (int k0 = 0; k0 < F.kp; k0 += kSlab) {
-        __syncthreads();  // the previous slab's products are done with sm.H
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int r = hr + 32 * q;
-            if (r < dp) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sm.H[r * kChainSlabLd + hc + e] = hv[q][e];
-            }
-        }
-        __syncthreads();
-        if (k0 + kSlab < F.kp) load_h(k0 + kSlab);
-        if (active) chain_mma<true>(sm.H, kChainSlabLd, sm.H, kChainSlabLd, kSlab, wy, wx, acc);
-    }
-    if (active) chain_store(sm.M, wy, wx, acc, [](int, int, float v) { return v; });
-    __syncthreads();
-    // A^2 -> T1, A^4 -> T2
-    zero(acc);
-    if (active) {
-        chain_mma<false>(sm.A, kChainLd, sm.A, kChainLd, dp, wy, wx, acc);
-        chain_store(sm.T1, wy, wx, acc, [](int, int, float v) { return v; });
-    }
-    __syncthreads();
-    zero(acc);
-    if (active) {
-        chain_mma<false>(sm.T1, kChainLd, sm.T1, kChainLd, dp, wy, wx, acc);
-        chain_store(sm.T2, wy, wx, acc, [](int, int, float v) { return v; });
-    }
-    __syncthreads();
-    // X = A^4 M -> T1, with ||X||_F^2
-    zero(acc);
-    double part = 0.0;
-    if (active) {
-        chain_mma<false>(sm.T2, kChainLd, sm.M, kChainLd, dp, wy, wx, acc);
-        chain_store(sm.T1, wy, wx, acc, [&](int, int, float v) {
-            part += (double)v * (double)v;
-            return v;
-        });
-    }
-    const double nu2 = block_sum_256(part, sm.red);
-    if (tid == 0) {
-        const FactorScalars fs = factor_scalars(sqrt(nu2), beta2, mode);
-        *F.sc = fs;
-        sm.coef[0] = fs.a;
-        sm.coef[1] = fs.b;
-        sm.coef[2] = fs.sf;
-        sm.coef[3] = fs.e;
-    }
-    __syncthreads();
-    const float a = sm.coef[0], b = sm.coef[1], sf = sm.coef[2], ce = sm.coef[3];
-    const int d = F.d;
-    // P (the matrix the product with A reads) and Z, in buffers free at that point.
-    float* P = sm.T2;
-    float* Z = sm.M;
-    if (order == 3) {
-        // V = b X - e X X -> T2, then P = I - a X + X V -> M
-        zero(acc);
-        if (active) {
-            chain_mma<false>(sm.T1, kChainLd, sm.T1, kChainLd, dp, wy, wx, acc);
-            chain_store(sm.T2, wy, wx, acc,
-                        [&](int row, int col, float v) { return b * sm.T1[row * kChainLd + col] - ce * v; });
-        }
-        __syncthreads();
-        zero(acc);
-        if (active) {
-            chain_mma<false>(sm.T1, kChainLd, sm.T2, kChainLd, dp, wy, wx, acc);
-            chain_store(sm.M, wy, wx, acc, [&](int row, int col, float v) {
-                const float id = (row == col && row < d) ? 1.0f : 0.0f;
-                return (id - a * sm.T1[row * kChainLd + col]) + v;
-            });
-        }
-        P = sm.M;
-        Z = sm.T1;
-    } else {
-        // P = I - a X + b X X -> T2
-        zero(acc);
-        if (active) {
-            chain_mma<false>(sm.T1, kChainLd, sm.T1, kChainLd, dp, wy, wx, acc);
-            chain_store(sm.T2, wy, wx, acc, [&](int row, int col, float v) {
-                const float id = (row == col && row < d) ? 1.0f : 0.0f;
-                return (id - a * sm.T1[row * kChainLd + col]) + b * v;
-            });
-        }
-    }
-    __syncthreads();
-    // Z = s A P
-    zero(acc);
-    if (active) {
-        chain_mma<false>(sm.A, kChainLd, P, kChainLd, dp, wy, wx, acc);
-        chain_store(Z, wy, wx, acc, [&](int, int, float v) { return sf * v; });
-    }
-    __syncthreads();
-    // A <- (Z + Z^T)/2 or Z; fp32 addition commutes, so the result is bitwise symmetric.
-    for (int e = tid; e < dp * dp; e += kGemmThreads) {
-        const int r = e / dp, c = e % dp;
-        const float z = Z[r * kChainLd + c];
-        F.A[e] = symmetrize ? 0.5f * (z + Z[c * kChainLd + r]) : z;
-    }
-}
-
-// ---------------------------------------------------------------- LDS chain, sizes 96 and 128
-// The same whole-factor update (explicit order of Algorithm 2, symmetric
-// factors) for padded sizes 64 < dp <= 128, by one workgroup of eight waves
-// (two per SIMD, so one wave's MFMAs run while the other waits at a barrier
-// or for memory). Two dp x dp matrices stay in LDS and A is read from global
-// memory when a product needs it: M = H H^T (H streamed in 32-column slabs,
-// the next slab held in registers while the current one is multiplied), A^2,
-// A^4, X = A^4 M with ||X||_F, (beta, c, s) (Appendix A.1, Eq. 8-9),
-// P = I - (c/4) X + (5c^2/32) X X (Eq. 6; with series order 3,
-// P = I - a X + X V, V = b X - e X X), Z = s A P and A <- (Z + Z^T)/2.
-// Every product is C = A B with both operands held as rows that are
-// contiguous in k: A's rows, and B's columns, i.e. the rows of B^T. The
-// symmetric operands (A, A^2, A^4, M) are their own transposes; X is stored
-// beside X^T, and P and V only transposed.
-// Wave w owns the 64 x 32 piece at rows 64 (w / 4), columns 32 (w % 4) of
-// the product, as 4 x 2 blocks of v_mfma_f32_16x16x4_f32; lane l reads 16
-// bytes of its row for k = k0 + 4 (l / 16) .. + 3 and feeds them to the four
-// steps of a 16-deep k group (A and B alike, so every A[i][k] B[k][j] is
-// formed once). Blocks outside dp are skipped.
-constexpr int kChain2Max = 128;
-constexpr int kC2Threads = 512;          // eight waves
-constexpr int kC2Waves = kC2Threads / 64;
-constexpr int kC2PieceCols = 32;         // a wave's piece: 64 rows x 32 columns
-constexpr int kC2Ld = kChain2Max + 4;    // LDS row stride: 16-byte reads of 16 rows fall in distinct bank quads
-constexpr int kC2Mat = kChain2Max * kC2Ld;
-constexpr int kC2HLd = kSlab + 4;        // H slab row stride
-
-struct Chain2Lds {
-    float m0[kC2Mat];
-    float m1[kC2Mat];
-    float h[kChain2Max * kC2HLd];
-    double red[kC2Waves];
-    float coef[4];  // a, b, s, e
+// A wave's piece of an M x N product (M, N multiples of 32): first row and
+// column, and how many of its 16-row blocks lie inside (0: none of the piece).
+struct Piece {
+    int row, col, nbi;
 };
-
-// Fragments of one 16-deep k group: lane l's 16 bytes of rows 16 i + l % 16
-// of its piece (A) and of its columns (B), at k = k0 + 4 (l / 16) .. + 3.
-template <int NBI, int NBJ>
-__device__ __forceinline__ void c2_frags(const float* pa, int lda, const float* pb, int ldb, int k0, f32x4 (&fa)[NBI],
-                                         f32x4 (&fb)[NBJ]) {
-#pragma unroll
-    for (int i = 0; i < NBI; ++i) fa[i] = *reinterpret_cast<const f32x4*>(pa + 16 * i * lda + k0);
-#pragma unroll
-    for (int j = 0; j < NBJ; ++j) fb[j] = *reinterpret_cast<const f32x4*>(pb + 16 * j * ldb + k0);
+template <class T>
+__device__ __forceinline__ Piece piece_of(int wave, int M, int N) {
+    Piece p;
+    p.row = wave / T::GRID_X * (16 * T::BI);
+    p.col = wave % T::GRID_X * (16 * T::BJ);
+    p.nbi = p.col < N ? max(0, min(T::BI, (M - p.row) / 16)) : 0;
+    return p;
 }
 
-template <int NBI, int NBJ>
-__device__ __forceinline__ void c2_group(const f32x4 (&fa)[NBI], const f32x4 (&fb)[NBJ], f32x4 (&acc)[8]) {
+// The three-term split by truncation: x0 and x1 are the upper halves of x and of
+// the exact difference x - x0, x2 the upper half of what is left (8 bits, so
+// exact). Eleven instructions for two elements against split_pair's seven, but
+// all of the plain VALU, which takes two waves' instructions at once and runs
+// beside the MFMAs; the conversions and dot products of split_pair hold up both.
+// Measured with two waves per SIMD, cycles for 24 pairs and 48 MFMAs of each:
+// 2528 by truncation, 4012 with split_pair (MFMAs alone 1564). The staged GEMM
+// splits each element a quarter as often per MFMA and runs no faster with it.
+__device__ __forceinline__ SplitPair split_pair_trunc(float a, float b) {
+    SplitPair o;
+    unsigned ua, ub;
 #pragma unroll
-    for (int st = 0; st < 4; ++st)
+    for (int t = 0; t < kTerms; ++t) {
+        ua = __builtin_bit_cast(unsigned, a);
+        ub = __builtin_bit_cast(unsigned, b);
+        o.t[t] = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(ub, ua, 0x07060302));
+        a -= __builtin_bit_cast(float, ua & 0xffff0000u);
+        b -= __builtin_bit_cast(float, ub & 0xffff0000u);
+    }
+    return o;
+}
+
+struct SplitOct {
+    bf16x8 t[kTerms];
+};
+__device__ __forceinline__ SplitOct split_oct(f32x4 u, f32x4 v) {
+    const SplitPair a = split_pair_trunc(u[0], u[1]), b = split_pair_trunc(u[2], u[3]);
+    const SplitPair c = split_pair_trunc(v[0], v[1]), d = split_pair_trunc(v[2], v[3]);
+    SplitOct o;
+#pragma unroll
+    for (int t = 0; t < kTerms; ++t)
+        o.t[t] = bf16x8{a.t[t][0], a.t[t][1], b.t[t][0], b.t[t][1], c.t[t][0], c.t[t][1], d.t[t][0], d.t[t][1]};
+    return o;
+}
+
+// acc += a (rows) x b^T (rows) over k in [0, K), K a multiple of 32, for NBI of
+// the piece's block rows. Lane l takes k = k0 + 4 (l / 16) .. + 3 and k0 + 16 + 4
+// (l / 16) .. + 3 of row l % 16 of a block, for a and b alike, so every product
+// is formed once. The next 32 k are read while the current ones are multiplied.
+template <class T, int NBI>
+__device__ __forceinline__ void piece_mma_n(const float* a, const float* b, int K, f32x4 (&acc)[T::BI * T::BJ]) {
+    constexpr int LD = T::LD, BJ = T::BJ;
+    constexpr int kA[6] = {2, 1, 0, 1, 0, 0}, kB[6] = {0, 1, 2, 0, 1, 0};
+    const int lane = threadIdx.x & 63;
+    const float* pa = a + (lane & 15) * LD + 4 * (lane >> 4);
+    const float* pb = b + (lane & 15) * LD + 4 * (lane >> 4);
+    f32x4 fa[NBI][2], fb[BJ][2];
+    auto read = [&](int k0) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int j = 0; j < BJ; ++j) fb[j][h] = *reinterpret_cast<const f32x4*>(pb + 16 * j * LD + k0 + 16 * h);
+#pragma unroll
+            for (int i = 0; i < NBI; ++i) fa[i][h] = *reinterpret_cast<const f32x4*>(pa + 16 * i * LD + k0 + 16 * h);
+        }
+    };
+    read(0);
+    for (int k0 = 0; k0 < K; k0 += 32) {
+        SplitOct sb[BJ], sa[NBI];
+#pragma unroll
+        for (int j = 0; j < BJ; ++j) sb[j] = split_oct(fb[j][0], fb[j][1]);
+#pragma unroll
+        for (int i = 0; i < NBI; ++i) sa[i] = split_oct(fa[i][0], fa[i][1]);
+        read(k0 + 32 < K ? k0 + 32 : 0);  // past the end: group 0 again, never multiplied
 #pragma unroll
         for (int i = 0; i < NBI; ++i)
 #pragma unroll
-            for (int j = 0; j < NBJ; ++j)
-                acc[i * 2 + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][st], fb[j][st], acc[i * 2 + j], 0, 0, 0);
-}
-
-// acc += a (rows, stride lda) x b^T (rows, stride ldb) over k in [0, K) (K a
-// multiple of 32) for the NBI x NBJ blocks of the calling wave's piece that
-// lie inside the product. The next group's fragments are read while the
-// current group's MFMAs run.
-template <int NBI, int NBJ>
-__device__ __forceinline__ void c2_mma_t(const float* a, int lda, const float* b, int ldb, int K, int wy, int wx,
-                                         f32x4 (&acc)[8]) {
-    const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
-    const float* pa = a + (wy * 64 + r) * lda + 4 * q;
-    const float* pb = b + (wx * kC2PieceCols + r) * ldb + 4 * q;
-    f32x4 fa0[NBI], fb0[NBJ], fa1[NBI], fb1[NBJ];
-    c2_frags<NBI, NBJ>(pa, lda, pb, ldb, 0, fa0, fb0);
-    for (int k0 = 0; k0 < K; k0 += 32) {
-        c2_frags<NBI, NBJ>(pa, lda, pb, ldb, k0 + 16, fa1, fb1);
-        __builtin_amdgcn_sched_barrier(0);
-        c2_group<NBI, NBJ>(fa0, fb0, acc);
-        // past the last group the read repeats group 0 (never multiplied): no branch in the loop
-        c2_frags<NBI, NBJ>(pa, lda, pb, ldb, k0 + 32 < K ? k0 + 32 : 0, fa0, fb0);
-        __builtin_amdgcn_sched_barrier(0);
-        c2_group<NBI, NBJ>(fa1, fb1, acc);
+            for (int u = 0; u < 6; ++u)
+#pragma unroll
+                for (int j = 0; j < BJ; ++j)
+                    acc[i * BJ + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sa[i].t[kA[u]], sb[j].t[kB[u]],
+                                                                             acc[i * BJ + j], 0, 0, 0);
     }
 }
 
-// The wave's part of a product: nbi (2 or 4) x 2 of its 4 x 2 blocks lie
-// inside it (uniform per wave); a wave with none returns.
-__device__ __forceinline__ void c2_mma(const float* a, int lda, const float* b, int ldb, int K, int wy, int wx,
-                                       int nbi, f32x4 (&acc)[8]) {
-    if (nbi == 4) c2_mma_t<4, 2>(a, lda, b, ldb, K, wy, wx, acc);
-    else if (nbi == 2) c2_mma_t<2, 2>(a, lda, b, ldb, K, wy, wx, acc);
-}
-
-__device__ __forceinline__ void c2_zero(f32x4 (&acc)[8]) {
+// The wave's piece of a product (acc from zero); a piece outside it does nothing.
+template <class T>
+__device__ __forceinline__ void piece_mma(const Piece& p, const float* a, const float* b, int K,
+                                          f32x4 (&acc)[T::BI * T::BJ]) {
 #pragma unroll
-    for (int b = 0; b < 8; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int i = 0; i < T::BI * T::BJ; ++i) acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const float* pa = a + p.row * T::LD;
+    const float* pb = b + p.col * T::LD;
+    if (p.nbi == T::BI) piece_mma_n<T, T::BI>(pa, pb, K, acc);
+    else if (T::BI > 2 && p.nbi == 2) piece_mma_n<T, 2>(pa, pb, K, acc);
 }
 
-// The wave's blocks to LDS: m[row][col] = f(row, col, value), row-major
-// (stride kC2Ld); with T, m[col][row] instead (four consecutive rows of a
-// column are one 16-byte store).
-template <bool T, typename Fn>
-__device__ __forceinline__ void c2_store(float* m, int wy, int wx, int nbi, const f32x4 (&acc)[8], Fn f) {
+// Every element of the wave's piece: f(row, col, block, e), e-th of four
+// consecutive rows of a column.
+template <class T, typename Fn>
+__device__ __forceinline__ void piece_each(const Piece& p, Fn f) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < T::BI; ++i) {
+        if (i >= p.nbi) continue;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            if (i >= nbi) continue;
-            const int row = wy * 64 + 16 * i + 4 * (lane >> 4), col = wx * kC2PieceCols + 16 * j + (lane & 15);
-            f32x4 v;
+        for (int j = 0; j < T::BJ; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = f(row + e, col, acc[i * 2 + j][e]);
-            if constexpr (T) {
-                *reinterpret_cast<f32x4*>(m + col * kC2Ld + row) = v;
+            for (int e = 0; e < 4; ++e)
+                f(p.row + 16 * i + 4 * (lane >> 4) + e, p.col + 16 * j + (lane & 15), i * T::BJ + j, e);
+    }
+}
+
+// The wave's blocks to LDS: m[row][col], or with TR m[col][row] (four
+// consecutive rows of a column are one 16-byte store).
+template <class T, bool TR>
+__device__ __forceinline__ void piece_store(const Piece& p, float* m, const f32x4 (&v)[T::BI * T::BJ]) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < T::BI; ++i) {
+        if (i >= p.nbi) continue;
+#pragma unroll
+        for (int j = 0; j < T::BJ; ++j) {
+            const int row = p.row + 16 * i + 4 * (lane >> 4), col = p.col + 16 * j + (lane & 15);
+            if constexpr (TR) {
+                *reinterpret_cast<f32x4*>(m + col * T::LD + row) = v[i * T::BJ + j];
             } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) m[(row + e) * kC2Ld + col] = v[e];
+                for (int e = 0; e < 4; ++e) m[(row + e) * T::LD + col] = v[i * T::BJ + j][e];
             }
         }
-}
-
-// A (dp x dp, global, row stride dp) into LDS rows of stride kC2Ld.
-__device__ __forceinline__ void c2_load_a(float* m, const float* __restrict__ A, int dp) {
-    const int nv = dp * dp / 4;
-    for (int v = threadIdx.x; v < nv; v += kC2Threads) {
-        const int e = 4 * v, r = e / dp, c = e - r * dp;
-        *reinterpret_cast<f32x4*>(m + r * kC2Ld + c) = gload4(A + e);
     }
 }
 
-// Sum of one double per thread over the workgroup's eight waves, in a fixed order.
-__device__ __forceinline__ double c2_block_sum(double v, double* red) {
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
-}
-
-__global__ __launch_bounds__(kC2Threads) void lds_chain128_kernel(const FactorDev* __restrict__ f,
-                                                                  const int* __restrict__ list, double beta2,
-                                                                  int mode, int order) {
-    static_assert(kC2Waves == 8, "the block sum and the piece layout assume eight waves");
-    __shared__ __attribute__((aligned(16))) Chain2Lds sm;
-    const FactorDev F = f[list[blockIdx.x]];
-    const int dp = F.dp, d = F.d, tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wy = wave >> 2, wx = wave & 3;
-    // 16-row blocks of this wave's piece inside dp (dp is 96 or 128: 2 or 4);
-    // its two 16-column blocks are inside dp or outside it together.
-    const int nbi = min(4, (dp - wy * 64) / 16);
-    const bool active = nbi > 0 && wx * kC2PieceCols < dp;
-    f32x4 acc[8];
-
-    // M = H H^T, H (dp x kp, row stride kp) in 32-column slabs; thread t
-    // moves two 16-byte pieces of each slab: row (t + 512 p) / 8, columns
-    // 4 ((t + 512 p) % 8) .. + 3.
-    c2_zero(acc);
-    f32x4 hv[2];
-    auto load_h = [&](int k0) {
+// A factor (dp x dp, global) through registers to LDS rows, or with tr its
+// transpose: thread t holds columns 4 (t % (D / 4)) .. + 3 of rows t / (D / 4) + i (4
+// THREADS / D). Positions outside are read from the nearest one inside, and land
+// in rows and columns of the LDS matrix that no product reads.
+template <class T>
+__device__ __forceinline__ void factor_load(int t, const float* __restrict__ A, int dp, f32x4 (&r)[T::AV]) {
+    const int c = min(4 * (t % (T::D / 4)), dp - 4);
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int u = tid + kC2Threads * p, r = u >> 3;
-            if (r < dp) hv[p] = gload4(F.H + (size_t)r * F.kp + k0 + 4 * (u & 7));
-        }
-    };
-    load_h(0);
-    for (int k0 = 0; k0 < F.kp; k0 += kSlab) {
-        __syncthreads();  // every wave is done with the previous slab
+    for (int i = 0; i < T::AV; ++i) {
+        const int row = min(t / (T::D / 4) + i * (4 * T::THREADS / T::D), dp - 1);
+        r[i] = *(global_f32x4*)((const gcchar*)A + 4u * (unsigned)(row * dp + c));
+    }
+}
+template <class T>
+__device__ __forceinline__ void factor_store(int t, const f32x4 (&r)[T::AV], float* m, bool tr) {
+    const int c = 4 * (t % (T::D / 4));
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int u = tid + kC2Threads * p, r = u >> 3;
-            if (r < dp) *reinterpret_cast<f32x4*>(sm.h + r * kC2HLd + 4 * (u & 7)) = hv[p];
+    for (int i = 0; i < T::AV; ++i) {
+        const int row = t / (T::D / 4) + i * (4 * T::THREADS / T::D);
+        if (tr) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) m[(c + q) * T::LD + row] = r[i][q];
+        } else {
+            *reinterpret_cast<f32x4*>(m + row * T::LD + c) = r[i];
         }
-        __syncthreads();
-        if (k0 + kSlab < F.kp) load_h(k0 + kSlab);
-        if (active) c2_mma(sm.h, kC2HLd, sm.h, kC2HLd, kSlab, wy, wx, nbi, acc);
     }
-    if (active) c2_store<false>(sm.m0, wy, wx, nbi, acc, [](int, int, float v) { return v; });
-    c2_load_a(sm.m1, F.A, dp);
+}
+
+// The gradient (dense m x n, any alignment) through registers: thread t holds
+// column t % D of rows t / D + i (THREADS / D), zero outside the layer. The loads are
+// unconditional (positions outside read the nearest one inside), so all are in
+// flight at once.
+template <class T>
+__device__ __forceinline__ void grad_load(int t, const float* __restrict__ G, int m, int n, float (&r)[T::GV]) {
+    const int c = t % T::D, cc = min(c, n - 1);
+#pragma unroll
+    for (int i = 0; i < T::GV; ++i) {
+        const int row = t / T::D + i * (T::THREADS / T::D);
+        r[i] = ld_at(G, 4u * (unsigned)(min(row, m - 1) * n + cc));
+    }
+#pragma unroll
+    for (int i = 0; i < T::GV; ++i) {
+        const int row = t / T::D + i * (T::THREADS / T::D);
+        r[i] = (row < m && c < n) ? r[i] : 0.0f;
+    }
+}
+// To LDS rows, or with tr its transpose (the whole D x D matrix, zero outside the layer).
+template <class T>
+__device__ __forceinline__ void grad_store(int t, const float (&r)[T::GV], float* l, bool tr) {
+    const int c = t % T::D;
+#pragma unroll
+    for (int i = 0; i < T::GV; ++i) {
+        const int row = t / T::D + i * (T::THREADS / T::D);
+        l[tr ? c * T::LD + row : row * T::LD + c] = r[i];
+    }
+}
+
+// Sum of one double per thread over the first N waves of red, in index order (after a barrier).
+template <int N>
+__device__ __forceinline__ double sum_waves(const double* red) {
+    double v = red[0];
+#pragma unroll
+    for (int w = 1; w < N; ++w) v += red[w];
+    return v;
+}
+
+// One factor's update by a team (threads t = 0 .. T::THREADS - 1, wave = t / 64).
+// m0, m1: two LDS matrices of T::MAT floats; red: T::WAVES doubles. g: the layer's
+// gradient in the team's registers. Every thread of the
+// workgroup calls it (all its teams meet the same barriers). On return the new
+// factor is in global memory and, for side R of a non-symmetric factor
+// transposed, in m1 (behind a barrier).
+template <class T>
+__device__ __forceinline__ void chain_update(const FactorDev& F, int side, int t, int wave, const float (&g)[T::GV],
+                                             double beta2, int mode, int symmetrize, int order, float* m0, float* m1,
+                                             double* red) {
+    constexpr int NB = T::BI * T::BJ;
+    const int dp = F.dp, kp = F.kp, d = F.d;
+    const Piece p = piece_of<T>(wave, dp, dp);
+    f32x4 av[T::AV], acc[NB];
+    factor_load<T>(t, F.A, dp, av);
+    factor_store<T>(t, av, m0, false);
+    if (!symmetrize) factor_store<T>(t, av, m1, true);
     __syncthreads();
-    // A^2 and A^4, each over the last in m1
-    for (int pw = 0; pw < 2; ++pw) {
-        c2_zero(acc);
-        if (active) c2_mma(sm.m1, kC2Ld, sm.m1, kC2Ld, dp, wy, wx, nbi, acc);
-        __syncthreads();
-        if (active) c2_store<false>(sm.m1, wy, wx, nbi, acc, [](int, int, float v) { return v; });
-        __syncthreads();
-    }
-    // X = A^4 M (M symmetric: its rows are its columns) with ||X||_F^2; X to
-    // m0, X^T to m1.
-    c2_zero(acc);
+    // A^2 and A^4, each over the last in m0 (its transpose in m1 when not symmetric)
+    piece_mma<T>(p, m0, symmetrize ? m0 : m1, dp, acc);
+    __syncthreads();
+    piece_store<T, false>(p, m0, acc);
+    if (!symmetrize) piece_store<T, true>(p, m1, acc);
+    __syncthreads();
+    piece_mma<T>(p, m0, symmetrize ? m0 : m1, dp, acc);
+    __syncthreads();
+    piece_store<T, false>(p, m0, acc);
+    // H: G for L_hat, G^T for R_hat
+    grad_store<T>(t, g, m1, side != 0);
+    __syncthreads();
+    // M = H H^T
+    piece_mma<T>(p, m1, m1, kp, acc);
+    __syncthreads();
+    piece_store<T, false>(p, m1, acc);
+    __syncthreads();
+    // X = A^4 M (M symmetric: its rows are its columns) with ||X||_F^2; the wave
+    // keeps its piece of X in x.
+    f32x4 x[NB];
+    piece_mma<T>(p, m0, m1, dp, x);
     double part = 0.0;
-    if (active) {
-        c2_mma(sm.m1, kC2Ld, sm.m0, kC2Ld, dp, wy, wx, nbi, acc);
 #pragma unroll
-        for (int b = 0; b < 8; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) part += (double)acc[b][e] * (double)acc[b][e];
-    }
-    const double nu2 = c2_block_sum(part, sm.red);  // (its barrier also ends the reads of m0 and m1)
-    if (active) {
-        c2_store<false>(sm.m0, wy, wx, nbi, acc, [](int, int, float v) { return v; });
-        c2_store<true>(sm.m1, wy, wx, nbi, acc, [](int, int, float v) { return v; });
-    }
-    if (tid == 0) {
-        const FactorScalars fs = factor_scalars(sqrt(nu2), beta2, mode);
-        *F.sc = fs;
-        sm.coef[0] = fs.a;
-        sm.coef[1] = fs.b;
-        sm.coef[2] = fs.sf;
-        sm.coef[3] = fs.e;
-    }
+        for (int e = 0; e < 4; ++e) part += (double)x[b][e] * (double)x[b][e];
+    part = wave_sum(part);
+    if ((t & 63) == 0) red[wave] = part;
     __syncthreads();
-    const float a = sm.coef[0], b = sm.coef[1], sf = sm.coef[2], ce = sm.coef[3];
-    const float* X = sm.m0;
-    // X X (B = X, whose rows-in-k are the rows of X^T in m1)
-    c2_zero(acc);
-    if (active) c2_mma(sm.m0, kC2Ld, sm.m1, kC2Ld, dp, wy, wx, nbi, acc);
+    piece_store<T, false>(p, m0, x);
+    piece_store<T, true>(p, m1, x);
+    // A again, for Z: its loads run under the next product.
+    f32x4 av2[T::AV];
+    factor_load<T>(t, F.A, dp, av2);
+    const FactorScalars fs = factor_scalars(sqrt(sum_waves<T::WAVES>(red)), beta2, mode);
+    if (t == 0) *F.sc = fs;
+    const float a = fs.a, b = fs.b, sf = fs.sf, ce = fs.e;
     __syncthreads();
+    // X X (B = X: its rows in k are the rows of X^T in m1)
+    piece_mma<T>(p, m0, m1, dp, acc);
+    float bb = b;
     if (order == 3) {
         // V = b X - e X X, stored transposed over X^T; then X V
-        if (active)
-            c2_store<true>(sm.m1, wy, wx, nbi, acc,
-                           [&](int row, int col, float v) { return b * X[row * kC2Ld + col] - ce * v; });
         __syncthreads();
-        c2_zero(acc);
-        if (active) c2_mma(sm.m0, kC2Ld, sm.m1, kC2Ld, dp, wy, wx, nbi, acc);
-        __syncthreads();
-        // P = I - a X + X V, stored transposed
-        if (active)
-            c2_store<true>(sm.m1, wy, wx, nbi, acc, [&](int row, int col, float v) {
-                const float id = (row == col && row < d) ? 1.0f : 0.0f;
-                return (id - a * X[row * kC2Ld + col]) + v;
-            });
-    } else {
-        // P = I - a X + b X X, stored transposed
-        if (active)
-            c2_store<true>(sm.m1, wy, wx, nbi, acc, [&](int row, int col, float v) {
-                const float id = (row == col && row < d) ? 1.0f : 0.0f;
-                return (id - a * X[row * kC2Ld + col]) + b * v;
-            });
-    }
-    __syncthreads();  // every read of X is done: A can replace it
-    c2_load_a(sm.m0, F.A, dp);
-    __syncthreads();
-    // Z = s A P (B = P: its rows-in-k are the rows of P^T in m1)
-    c2_zero(acc);
-    if (active) c2_mma(sm.m0, kC2Ld, sm.m1, kC2Ld, dp, wy, wx, nbi, acc);
-    __syncthreads();
-    if (active) c2_store<false>(sm.m0, wy, wx, nbi, acc, [&](int, int, float v) { return sf * v; });
-    __syncthreads();
-    // A <- (Z + Z^T)/2: fp32 addition commutes, so the result is bitwise symmetric.
-    const int nv = dp * dp / 4;
-    for (int v = tid; v < nv; v += kC2Threads) {
-        const int e = 4 * v, r = e / dp, c = e - r * dp;
-        f32x4 o;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = 0.5f * (sm.m0[r * kC2Ld + c + q] + sm.m0[(c + q) * kC2Ld + r]);
-        *(gfloat4*)(F.A + e) = o;
+        for (int q = 0; q < NB; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[q][e] = b * x[q][e] - ce * acc[q][e];
+        piece_store<T, true>(p, m1, acc);
+        __syncthreads();
+        piece_mma<T>(p, m0, m1, dp, acc);
+        bb = 1.0f;
     }
+    __syncthreads();
+    // P = I - a X + b X X (or I - a X + X V), stored transposed; A takes X's place
+    piece_each<T>(p, [&](int row, int col, int q, int e) {
+        const float id = (row == col && row < d) ? 1.0f : 0.0f;
+        acc[q][e] = (id - a * x[q][e]) + bb * acc[q][e];
+    });
+    piece_store<T, true>(p, m1, acc);
+    factor_store<T>(t, av2, m0, false);
+    __syncthreads();
+    // Z = s A P (B = P: its rows in k are the rows of P^T in m1)
+    piece_mma<T>(p, m0, m1, dp, acc);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NB; ++q) acc[q] = acc[q] * sf;
+    piece_store<T, false>(p, m0, acc);
+    __syncthreads();
+    // A <- (Z + Z^T)/2 or Z, in the accumulators' layout: four consecutive rows of a
+    // column of Z^T are one 16-byte read of m0, and of the symmetric result one
+    // 16-byte store. fp32 addition commutes, so the result is bitwise symmetric.
+    const int lane = t & 63;
+#pragma unroll
+    for (int i = 0; i < T::BI; ++i) {
+        if (i >= p.nbi) continue;
+#pragma unroll
+        for (int j = 0; j < T::BJ; ++j) {
+            const int row = p.row + 16 * i + 4 * (lane >> 4), col = p.col + 16 * j + (lane & 15);
+            f32x4& z = acc[i * T::BJ + j];
+            if (symmetrize) {
+                const f32x4 zt = *reinterpret_cast<const f32x4*>(m0 + col * T::LD + row);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) z[e] = 0.5f * (z[e] + zt[e]);
+                st4_at(F.A, 4u * (unsigned)(col * dp + row), z);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) st_at(F.A, 4u * (unsigned)((row + e) * dp + col), z[e]);
+            }
+        }
+    }
+    if (symmetrize || side != 0) piece_store<T, true>(p, m1, acc);
+    else piece_store<T, false>(p, m1, acc);
+    __syncthreads();
+}
+
+// Scalars of a step that the layer kernels take by value.
+struct StepScalars {
+    double lr, wd;
+    float beta1;
+    int graft;
+};
+
+// (norm_m, norm_sgd) to the grafted step g (Algorithm 3) and the decoupled decay
+// rate lr * wd (Section 4), with the layer's non-finite flag.
+__device__ __forceinline__ LayerScalars layer_scalars(double nm, double ns, double lr, double wd, int graft,
+                                                      int* nonfinite) {
+    // A NaN or infinity anywhere in this step's G reaches m_SGD = beta1 m_SGD + G,
+    // and with it this norm: the layer's flag records it for the host.
+    if (!isfinite(ns)) *nonfinite = 1;
+    double g = lr;
+    if (graft) g = nm > 0.0 ? lr * ns / nm : 0.0;
+    LayerScalars out;
+    out.norm_m = nm;
+    out.norm_sgd = ns;
+    out.g = g;
+    out.gf = (float)g;
+    out.lw = (float)(lr * wd);
+    return out;
+}
+
+// m_SGD <- beta1 m_SGD + G by a workgroup holding the gradient as grad_load
+// leaves it. Returns the thread's share of ||m_SGD||^2.
+template <class T>
+__device__ __forceinline__ double msgd_update(const LayerDev& L, const float (&g)[T::GV], float beta1) {
+    const int t = threadIdx.x, c = t % T::D;
+    float ms[T::GV];
+#pragma unroll
+    for (int i = 0; i < T::GV; ++i) {
+        const int row = t / T::D + i * (T::THREADS / T::D);
+        ms[i] = ld_at(L.msgd, 4u * (unsigned)(min(row, L.m - 1) * L.n + min(c, L.n - 1)));
+    }
+    double part = 0.0;
+#pragma unroll
+    for (int i = 0; i < T::GV; ++i) {
+        const int row = t / T::D + i * (T::THREADS / T::D);
+        if (row < L.m && c < L.n) {
+            const float v = beta1 * ms[i] + g[i];
+            st_at(L.msgd, 4u * (unsigned)(row * L.n + c), v);
+            part += (double)v * (double)v;
+        }
+    }
+    return part;
+}
+
+// The rest of a layer's step by a workgroup of eight waves, given L_hat (rows)
+// in lm, G^T (np x mp rows) in gm, and tm free for T = L_hat G (tm may be lm).
+// R_hat's transpose (rows) is in rm or, with R_LATE, R_hat (symmetric) is read
+// from global memory into rm = gm once G^T has been used. ps: the thread's share
+// of ||m_SGD||^2. red: 16 doubles.
+//   m <- beta1 m + (1 - beta1) L_hat G R_hat; theta <- theta - (lr wd theta + g m)
+// (see weight_kernel).
+template <class T, bool R_LATE>
+__device__ __forceinline__ void layer_apply(const LayerDev& L, const FactorDev& FR, float* __restrict__ theta,
+                                            double ps, const StepScalars& sc, const float* lm, float* gm, float* tm,
+                                            float* rm, double* red, float* coef) {
+    constexpr int NB = T::BI * T::BJ;
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int m = L.m, n = L.n;
+    const Piece p = piece_of<T>(wave, L.mp, L.np);
+    // The state this thread updates, in the accumulators' layout.
+    f32x4 mo[NB], th[NB];
+    piece_each<T>(p, [&](int row, int col, int q, int e) {
+        const unsigned at = 4u * (unsigned)(min(row, m - 1) * n + min(col, n - 1));  // outside: read, not used
+        mo[q][e] = ld_at(L.mom, at);
+        th[q][e] = ld_at(theta, at);
+    });
+    f32x4 acc[NB];
+    piece_mma<T>(p, lm, gm, L.mp, acc);  // T = L_hat G
+    f32x4 rv[T::AV];
+    if constexpr (R_LATE) factor_load<T>(t, FR.A, FR.dp, rv);
+    __syncthreads();
+    piece_store<T, false>(p, tm, acc);
+    if constexpr (R_LATE) factor_store<T>(t, rv, rm, false);
+    __syncthreads();
+    piece_mma<T>(p, tm, rm, L.np, acc);  // G~ = T R_hat
+    double pm = 0.0;
+    piece_each<T>(p, [&](int row, int col, int q, int e) {
+        if (row < m && col < n) {
+            const float v = sc.beta1 * mo[q][e] + (1.0f - sc.beta1) * acc[q][e];
+            mo[q][e] = v;
+            st_at(L.mom, 4u * (unsigned)(row * n + col), v);
+            pm += (double)v * (double)v;
+        }
+    });
+    pm = wave_sum(pm);
+    ps = wave_sum(ps);
+    if ((t & 63) == 0) {
+        red[wave] = pm;
+        red[T::WAVES + wave] = ps;
+    }
+    __syncthreads();
+    if (t == 0) {
+        const LayerScalars s = layer_scalars(sqrt(sum_waves<T::WAVES>(red)), sqrt(sum_waves<T::WAVES>(red + T::WAVES)),
+                                             sc.lr, sc.wd, sc.graft, L.nonfinite);
+        *L.ls = s;
+        coef[0] = s.gf;
+        coef[1] = s.lw;
+    }
+    __syncthreads();
+    const float gf = coef[0], lw = coef[1];
+    piece_each<T>(p, [&](int row, int col, int q, int e) {
+        if (row < m && col < n)
+            st_at(theta, 4u * (unsigned)(row * n + col), th[q][e] - (lw * th[q][e] + gf * mo[q][e]));
+    });
+}
+
+// Layers with m, n <= 64: the whole step in one workgroup, L_hat's update in its
+// first four waves and R_hat's in the other four.
+__global__ __launch_bounds__(kSmallThreads) void small_step64_kernel(const LayerDev* __restrict__ layers,
+                                                                     const FactorDev* __restrict__ f, int layer_base,
+                                                                     PtrPack ptrs, StepScalars sc, int update,
+                                                                     double beta2, int mode, int symmetrize,
+                                                                     int order) {
+    __shared__ __attribute__((aligned(16))) float mat[4][Team64::MAT];
+    __shared__ double red[16];
+    __shared__ float coef[2];
+    const int li = layer_base + blockIdx.x;
+    const LayerDev L = layers[li];
+    const float* G = ptrs.grad(blockIdx.x);
+    const int tid = threadIdx.x, team = __builtin_amdgcn_readfirstlane(tid >> 8), t = tid & 255;
+    const FactorDev F = f[2 * li + team];
+    float ga[Apply64::GV];
+    grad_load<Apply64>(tid, G, L.m, L.n, ga);
+    const double ps = msgd_update<Apply64>(L, ga, sc.beta1);
+    if (update) {
+        float gt[Team64::GV];
+        grad_load<Team64>(t, G, L.m, L.n, gt);
+        chain_update<Team64>(F, team, t, __builtin_amdgcn_readfirstlane(t >> 6), gt, beta2, mode, symmetrize, order,
+                             mat[2 * team], mat[2 * team + 1], red + 4 * team);
+    } else {
+        f32x4 av[Team64::AV];
+        factor_load<Team64>(t, F.A, F.dp, av);
+        factor_store<Team64>(t, av, mat[2 * team + 1], team != 0 && !symmetrize);
+    }
+    grad_store<Apply64>(tid, ga, mat[0], true);
+    __syncthreads();
+    layer_apply<Apply64, false>(L, F, ptrs.param(blockIdx.x), ps, sc, mat[1], mat[0], mat[2], mat[3], red, coef);
+}
+
+// Layers up to 128 (symmetric factors): each factor's update in a workgroup of
+// its own (blockIdx.x: one of the batch's factors, largest first) ...
+__global__ __launch_bounds__(kSmallThreads) void small_chain128_kernel(const FactorDev* __restrict__ f,
+                                                                       const int* __restrict__ list,
+                                                                       const LayerDev* __restrict__ layers,
+                                                                       int layer_base, PtrBatch grads, double beta2,
+                                                                       int mode, int order) {
+    __shared__ __attribute__((aligned(16))) float mat[2][Team128::MAT];
+    __shared__ double red[Team128::WAVES];
+    const int fi = list[blockIdx.x], li = fi >> 1;
+    const FactorDev F = f[fi];
+    float g[Team128::GV];
+    grad_load<Team128>(threadIdx.x, grads.p[li - layer_base], layers[li].m, layers[li].n, g);
+    chain_update<Team128>(F, fi & 1, threadIdx.x, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g, beta2, mode, 1,
+                          order, mat[0], mat[1], red);
+}
+
+// ... and the rest of each layer's step in one.
+__global__ __launch_bounds__(kSmallThreads) void small_apply128_kernel(const LayerDev* __restrict__ layers,
+                                                                       const FactorDev* __restrict__ f, int layer_base,
+                                                                       PtrPack ptrs, StepScalars sc) {
+    __shared__ __attribute__((aligned(16))) float mat[2][Team128::MAT];
+    __shared__ double red[16];
+    __shared__ float coef[2];
+    const int li = layer_base + blockIdx.x, t = threadIdx.x;
+    const LayerDev L = layers[li];
+    const FactorDev FL = f[2 * li], FR = f[2 * li + 1];
+    float g[Team128::GV];
+    grad_load<Team128>(t, ptrs.grad(blockIdx.x), L.m, L.n, g);
+    f32x4 av[Team128::AV];
+    factor_load<Team128>(t, FL.A, FL.dp, av);
+    const double ps = msgd_update<Team128>(L, g, sc.beta1);
+    factor_store<Team128>(t, av, mat[0], false);
+    grad_store<Team128>(t, g, mat[1], true);
+    __syncthreads();
+    layer_apply<Team128, true>(L, FR, ptrs.param(blockIdx.x), ps, sc, mat[0], mat[1], mat[0], mat[1], red, coef);
 }
 
 // Per-layer norms of m and m_SGD from their partial sums, and the grafted
@@ -678,18 +765,7 @@ __global__ void layer_finalize_kernel(const LayerDev* __restrict__ layers, doubl
     const double nm = sqrt(wave_sum_array(L.part_m, L.n_part_m * kWaveSlots));
     const double ns = sqrt(wave_sum_array(L.part_sgd, L.n_part_sgd));
     if (threadIdx.x != 0) return;
-    // A NaN or infinity anywhere in this step's G reaches m_SGD = beta1 m_SGD + G,
-    // and with it this norm: the layer's flag records it for the host.
-    if (!isfinite(ns)) *L.nonfinite = 1;
-    double g = lr;
-    if (graft) g = nm > 0.0 ? lr * ns / nm : 0.0;
-    LayerScalars out;
-    out.norm_m = nm;
-    out.norm_sgd = ns;
-    out.g = g;
-    out.gf = (float)g;
-    out.lw = (float)(lr * wd);
-    *L.ls = out;
+    *L.ls = layer_scalars(nm, ns, lr, wd, graft, L.nonfinite);
 }
 
 // theta <- theta (1 - lr wd) - g m over a flat chunk of one layer, evaluated as

@@ -1,6 +1,7 @@
 // Plain structs shared by the host runtime and the gfx950 kernels.
 #pragma once
 
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace jorge {
@@ -195,6 +196,20 @@ struct PtrBatch {
 };
 struct MutPtrBatch {
     float* p[kPtrBatch];
+};
+// Gradient and parameter pointers of up to kPtrBatch layers in 3 KB (both as
+// full pointers would take the whole 4 KB): 48 bits each, which is what a user
+// address has. Gradient of layer i at 2 i, parameter at 2 i + 1.
+struct PtrPack {
+    uint32_t lo[2 * kPtrBatch];
+    uint16_t hi[2 * kPtrBatch];
+    __host__ void set(int i, uint64_t v) {
+        lo[i] = (uint32_t)v;
+        hi[i] = (uint16_t)(v >> 32);
+    }
+    __device__ uint64_t get(int i) const { return (uint64_t)lo[i] | (uint64_t)hi[i] << 32; }
+    __device__ const float* grad(int i) const { return reinterpret_cast<const float*>(get(2 * i)); }
+    __device__ float* param(int i) const { return reinterpret_cast<float*>(get(2 * i + 1)); }
 };
 
 }  // namespace jorge
