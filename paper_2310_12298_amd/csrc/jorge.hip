@@ -61,6 +61,7 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <queue>
@@ -193,11 +194,13 @@ struct jorge_ctx {
     std::string last_error;
     hipEvent_t order_event = nullptr;  // orders a stream switch (jorge_set_stream)
     // jorge_step_noalloc: every device pointer of the context lies in lent
-    // memory (free_ctx frees none), and the device tables go to a pool there
-    // (upload() copies into it) instead of allocations of their own.
+    // memory (free_ctx frees none), and the device tables have places in a pool
+    // there instead of allocations of their own: upload() puts their contents
+    // into image, the pool's contents as one block.
     bool lent = false;
     char* pool = nullptr;
-    size_t pool_bytes = 0, pool_used = 0;
+    size_t pool_bytes = 0;
+    std::vector<char> image;
     // A step failed after its first launch: part of the state may be updated
     // and part not. Further steps are refused until jorge_set_step.
     bool poisoned = false;
@@ -1383,12 +1386,13 @@ jorge_status upload(jorge_ctx* c, const std::vector<T>& v, T** dptr) {
     *dptr = nullptr;
     if (v.empty()) return JORGE_OK;
     const size_t bytes = v.size() * sizeof(T);
-    if (c->pool) {  // stream-ordered copy into the lent pool; the caller keeps v alive until it is done
-        if (c->pool_used + bytes > c->pool_bytes)
+    if (c->pool) {
+        const size_t at = c->image.size();
+        if (at + bytes > c->pool_bytes)
             return fail(c, JORGE_ERR_UNSUPPORTED, "launch tables exceed the scratch left for them");
-        *dptr = reinterpret_cast<T*>(c->pool + c->pool_used);
-        c->pool_used = (size_t)round_up((int64_t)(c->pool_used + bytes), kAlign);
-        JORGE_HIP(c, hipMemcpyAsync(*dptr, v.data(), bytes, hipMemcpyHostToDevice, c->stream));
+        *dptr = reinterpret_cast<T*>(c->pool + at);
+        c->image.resize((size_t)round_up((int64_t)(at + bytes), kAlign));
+        std::memcpy(c->image.data() + at, v.data(), bytes);
         return JORGE_OK;
     }
     JORGE_HIP(c, hipMalloc(reinterpret_cast<void**>(dptr), bytes));
@@ -1494,13 +1498,37 @@ jorge_status run_update(jorge_ctx* c, double beta2) {
 }
 
 // jorge_step_noalloc: per device, the scratch's device address (set on the
-// first call on that device) and the lock that serialises calls.
+// first call on that device), the lock that serialises calls, and the plans of
+// the last few kinds of layer (shape and options), newest first. Building a plan
+// (layout, launch tables, split model) and uploading its tables took 1.7 of the
+// 2.0 ms of a 256 x 1024 call; a caller that steps the layers of one model in turn
+// finds them here. Host memory only, some 100 KB each, bounded by kNoallocPlans
+// per device and freed at process end.
 constexpr int kMaxDevices = 64;
+constexpr size_t kNoallocPlans = 16;
+struct NoallocPlan {
+    jorge_shape shape{};
+    jorge_hparams hp{};
+    jorge_ctx* ctx = nullptr;
+    ~NoallocPlan() { free_ctx(ctx); }  // host side only: every device pointer lies in the scratch
+};
 struct NoallocDevice {
     std::mutex mu;
     char* base = nullptr;
+    std::vector<std::unique_ptr<NoallocPlan>> plans;
+    // The plan whose tables and zero padding the scratch holds (null: none).
+    const NoallocPlan* resident = nullptr;
 };
 NoallocDevice g_noalloc[kMaxDevices];
+
+bool same_plan(const NoallocPlan& p, const jorge_shape& s, const jorge_hparams& h) {
+    const jorge_hparams& a = p.hp;
+    return p.shape.rows == s.rows && p.shape.cols == s.cols && a.eps == h.eps &&
+           a.precond_interval == h.precond_interval && a.beta_mode == h.beta_mode && a.graft == h.graft &&
+           a.symmetrize == h.symmetrize && a.factor_form == h.factor_form && a.split_k == h.split_k &&
+           a.lds_chain_max == h.lds_chain_max && a.precond_lowrank == h.precond_lowrank &&
+           a.series_order == h.series_order;
+}
 
 // The whole step of a small context (a factor-updating one or not).
 jorge_status launch_small(jorge_ctx* c, float* const* params, const float* const* grads, bool update, double lr,
@@ -1608,6 +1636,32 @@ void state_view(jorge_ctx* c, int32_t layer, int32_t kind, float** p, int64_t* r
         *cols = L.n;
         *ld = L.n;
     }
+}
+
+// The plan of one kind of layer in the scratch at base: the arena at its start,
+// then the split workspace, then the launch tables.
+jorge_status build_noalloc(const jorge_shape& shape, const jorge_hparams& h, char* base, int dev, NoallocPlan& p) {
+    jorge_ctx* c = p.ctx = new (std::nothrow) jorge_ctx();
+    if (!c) return JORGE_ERR_OUT_OF_MEMORY;
+    p.shape = shape;
+    p.hp = h;
+    c->hp = h;
+    c->device = dev;
+    c->lent = true;
+    jorge_status st = layout_context(c, &shape, 1);
+    if (st != JORGE_OK) return st;
+    c->arena = base;
+    std::vector<LayerDev> ld;
+    std::vector<FactorDev> fd;
+    if ((st = tables_context(c, ld, fd)) != JORGE_OK) return st;
+    const size_t arena = (size_t)round_up((int64_t)c->arena_bytes, kAlign);
+    const size_t split = (size_t)round_up(c->splitws_blocks * kSplitBlock * (int64_t)sizeof(float), kAlign);
+    const size_t need = arena + split + tables_bytes(c, ld, fd);
+    if (need > (size_t)JORGE_NOALLOC_SCRATCH_BYTES) return JORGE_ERR_UNSUPPORTED;
+    c->splitws = c->splitws_blocks > 0 ? reinterpret_cast<float*>(base + arena) : nullptr;
+    c->pool = base + arena + split;
+    c->pool_bytes = JORGE_NOALLOC_SCRATCH_BYTES - arena - split;
+    return upload_tables(c, ld, fd);
 }
 
 }  // namespace
@@ -1764,72 +1818,71 @@ jorge_status jorge_step_noalloc(const jorge_shape* shape, const jorge_hparams* h
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return JORGE_ERR_HIP;
         g_noalloc[dev].base = static_cast<char*>(ptr);
     }
-    char* const base = g_noalloc[dev].base;
-    jorge_ctx* c = new (std::nothrow) jorge_ctx();
-    if (!c) return JORGE_ERR_OUT_OF_MEMORY;
-    struct Owner {  // on every return: waits for queued work (it reads c's host tables), frees c
+    NoallocDevice& D = g_noalloc[dev];
+    const NoallocPlan* plan = nullptr;
+    try {
+        auto it = std::find_if(D.plans.begin(), D.plans.end(), [&](const std::unique_ptr<NoallocPlan>& p) {
+            return same_plan(*p, *shape, h);
+        });
+        if (it == D.plans.end()) {
+            std::unique_ptr<NoallocPlan> p(new NoallocPlan);
+            if ((st = build_noalloc(*shape, h, D.base, dev, *p)) != JORGE_OK) return st;
+            D.plans.insert(D.plans.begin(), std::move(p));
+            if (D.plans.size() > kNoallocPlans) {
+                if (D.resident == D.plans.back().get()) D.resident = nullptr;
+                D.plans.pop_back();
+            }
+        } else {
+            std::rotate(D.plans.begin(), it, it + 1);
+        }
+        plan = D.plans.front().get();
+    } catch (const std::bad_alloc&) {
+        return JORGE_ERR_OUT_OF_MEMORY;
+    }
+    jorge_ctx* const c = plan->ctx;
+    c->stream = reinterpret_cast<hipStream_t>(hip_stream);
+    const bool resident = D.resident == plan;
+    D.resident = nullptr;  // until this call has ended well
+    struct Drain {         // on an early return: waits for queued work, which reads c's tables and the scratch
         jorge_ctx* c;
         bool synced = false;
-        ~Owner() {
-            if (c->lent && !synced) (void)hipStreamSynchronize(c->stream);
-            free_ctx(c);  // host side only: every device pointer of c lies in the scratch
+        ~Drain() {
+            if (!synced) (void)hipStreamSynchronize(c->stream);
         }
-    } owner{c};
-    c->hp = h;
-    c->stream = reinterpret_cast<hipStream_t>(hip_stream);
-    c->device = dev;
-    if ((st = layout_context(c, shape, 1)) != JORGE_OK) return st;
-    // Everything below lies in the scratch: the arena at its start, then the
-    // split workspace, then the launch tables.
-    c->lent = true;
-    c->arena = base;
-    std::vector<LayerDev> ld;
-    std::vector<FactorDev> fd;
-    if ((st = tables_context(c, ld, fd)) != JORGE_OK) return st;
-    const size_t arena = (size_t)round_up((int64_t)c->arena_bytes, kAlign);
-    const size_t split = (size_t)round_up(c->splitws_blocks * kSplitBlock * (int64_t)sizeof(float), kAlign);
-    const size_t need = arena + split + tables_bytes(c, ld, fd);
-    if (need > (size_t)JORGE_NOALLOC_SCRATCH_BYTES) {
-        char msg[160];
-        std::snprintf(msg, sizeof msg, "jorge_step_noalloc: a %lld x %lld layer needs %zu bytes of scratch, above %lld",
-                      (long long)shape->rows, (long long)shape->cols, need, (long long)JORGE_NOALLOC_SCRATCH_BYTES);
-        return fail(c, JORGE_ERR_UNSUPPORTED, msg);
+    } drain{c};
+    if (!resident) {
+        // The scratch holds another layer's contents: the tables, and zeros where
+        // padding and partial sums must start at zero. (A step rewrites whatever
+        // else it reads; the factors' padding is cleared with every call below.)
+        const size_t words = c->arena_bytes / 16;
+        hipLaunchKernelGGL(zero_kernel, dim3((unsigned)std::min<size_t>((words + kEwThreads - 1) / kEwThreads, 4096)),
+                           dim3(kEwThreads), 0, c->stream, reinterpret_cast<f32x4*>(c->arena), words);
+        JORGE_HIP(c, hipGetLastError());
+        JORGE_HIP(c, hipMemcpyAsync(c->pool, c->image.data(), c->image.size(), hipMemcpyHostToDevice, c->stream));
     }
-    c->splitws = c->splitws_blocks > 0 ? reinterpret_cast<float*>(base + arena) : nullptr;
-    c->pool = base + arena + split;
-    c->pool_bytes = JORGE_NOALLOC_SCRATCH_BYTES - arena - split;
-    // The scratch keeps the last call's contents: the arena's padding and
-    // partial sums must start at zero.
-    const size_t words = c->arena_bytes / 16;
-    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)std::min<size_t>((words + kEwThreads - 1) / kEwThreads, 4096)),
-                       dim3(kEwThreads), 0, c->stream, reinterpret_cast<f32x4*>(base), words);
-    JORGE_HIP(c, hipGetLastError());
-    if ((st = upload_tables(c, ld, fd)) != JORGE_OK) return st;
     // The caller's state in (dense row-major) and, after the step, out.
     const auto& Lh = c->layers[0];
     const int m = Lh.m, n = Lh.n;
-    float* const A[2] = {at<float>(c, c->factors[Lh.fL].off_A), at<float>(c, c->factors[Lh.fR].off_A)};
-    float* const U[2] = {L, R};
-    const int dims[2] = {m, n}, lds[2] = {Lh.mp, Lh.np};
-    float* const mm = at<float>(c, Lh.off_mom);
-    float* const ms = at<float>(c, Lh.off_msgd);
-    const size_t mn = (size_t)m * n * sizeof(float);
-    for (int s = 0; s < 2; ++s)
-        JORGE_HIP(c, hipMemcpy2DAsync(A[s], lds[s] * sizeof(float), U[s], dims[s] * sizeof(float),
-                                      dims[s] * sizeof(float), dims[s], hipMemcpyDeviceToDevice, c->stream));
-    JORGE_HIP(c, hipMemcpyAsync(mm, mom, mn, hipMemcpyDeviceToDevice, c->stream));
-    JORGE_HIP(c, hipMemcpyAsync(ms, mom_sgd, mn, hipMemcpyDeviceToDevice, c->stream));
+    LentState ls{};
+    float* const user[4] = {L, R, mom, mom_sgd};
+    float* const held[4] = {at<float>(c, c->factors[Lh.fL].off_A), at<float>(c, c->factors[Lh.fR].off_A),
+                            at<float>(c, Lh.off_mom), at<float>(c, Lh.off_msgd)};
+    const int rows[4] = {m, n, m, m}, cols[4] = {m, n, n, n}, lds[4] = {Lh.mp, Lh.np, n, n};
+    const int prows[4] = {Lh.mp, Lh.np, m, m};
+    for (int i = 0; i < 4; ++i) ls.t[i] = {user[i], held[i], rows[i], cols[i], prows[i], lds[i]};
+    const int64_t most = std::max<int64_t>((int64_t)Lh.mp * Lh.mp, std::max<int64_t>((int64_t)Lh.np * Lh.np, (int64_t)m * n));
+    const dim3 grid((unsigned)std::min<int64_t>((most + kEwThreads - 1) / kEwThreads, 512), 4);
+    hipLaunchKernelGGL(lent_state_kernel, grid, dim3(kEwThreads), 0, c->stream, ls, 0);
+    JORGE_HIP(c, hipGetLastError());
     float* const params[1] = {theta};
     const float* const grads[1] = {grad};
     if ((st = launch_step(c, params, grads, t, lr, beta2, beta1, weight_decay)) != JORGE_OK) return st;
-    for (int s = 0; s < 2; ++s)
-        JORGE_HIP(c, hipMemcpy2DAsync(U[s], dims[s] * sizeof(float), A[s], lds[s] * sizeof(float),
-                                      dims[s] * sizeof(float), dims[s], hipMemcpyDeviceToDevice, c->stream));
-    JORGE_HIP(c, hipMemcpyAsync(mom, mm, mn, hipMemcpyDeviceToDevice, c->stream));
-    JORGE_HIP(c, hipMemcpyAsync(mom_sgd, ms, mn, hipMemcpyDeviceToDevice, c->stream));
-    // The host tables the copies above read, and the scratch, are reused once this returns.
+    hipLaunchKernelGGL(lent_state_kernel, grid, dim3(kEwThreads), 0, c->stream, ls, 1);
+    JORGE_HIP(c, hipGetLastError());
+    // The scratch is reused once this returns.
     JORGE_HIP(c, hipStreamSynchronize(c->stream));
-    owner.synced = true;
+    drain.synced = true;
+    D.resident = plan;
     return JORGE_OK;
 }
 

@@ -24,6 +24,26 @@ __global__ __launch_bounds__(kEwThreads) void zero_kernel(f32x4* __restrict__ p,
     for (size_t i = (size_t)blockIdx.x * kEwThreads + threadIdx.x; i < n; i += (size_t)gridDim.x * kEwThreads) p[i] = z;
 }
 
+// One layer's state copied between the caller's dense tensors and the library's
+// scratch: in (out = 0), each tensor with its padding set to zero, or out. One row
+// of workgroups (blockIdx.y) per tensor.
+struct LentState {
+    struct {
+        float* user;  // dense rows x cols
+        float* held;  // prows x ld, rows x cols of it valid
+        int rows, cols, prows, ld;
+    } t[4];
+};
+__global__ __launch_bounds__(kEwThreads) void lent_state_kernel(LentState s, int out) {
+    const auto& t = s.t[blockIdx.y];
+    const unsigned width = out ? t.cols : t.ld, n = width * (unsigned)(out ? t.rows : t.prows);
+    for (unsigned i = blockIdx.x * kEwThreads + threadIdx.x; i < n; i += gridDim.x * kEwThreads) {
+        const unsigned r = i / width, c = i - r * width;
+        if (out) t.user[i] = t.held[r * (unsigned)t.ld + c];
+        else t.held[i] = r < (unsigned)t.rows && c < (unsigned)t.cols ? t.user[r * (unsigned)t.cols + c] : 0.0f;
+    }
+}
+
 // A_hat = eps^(-1/4) I on the valid diagonal of every factor (the arena is zeroed before).
 __global__ void init_factors_kernel(const FactorDev* __restrict__ f, float l0) {
     const FactorDev F = f[blockIdx.x];
