@@ -46,8 +46,6 @@ constexpr int kGemmThreads = 256;
 constexpr int kBlockBytes = 1024;
 constexpr int kPlaneBytes = 2 * (kTile / 16) * kBlockBytes;
 constexpr int kSlabBytes = 3 * kPlaneBytes;
-constexpr int kSmallLds = 4 * 2 * 2 * 64 * 16 * 4;  // four waves, two stages, two 64 x 16 fp32 slabs
-constexpr int kGemmLds = kSmallLds > kSlabBytes ? kSmallLds : kSlabBytes;
 
 // Pointers into global memory (address space 1): loads through them compile
 // to global_load rather than flat_load, which would also count against the
@@ -58,9 +56,6 @@ typedef __attribute__((address_space(1))) const float global_f32;
 __device__ __forceinline__ f32x4 gload4(const float* p) {
     return *(global_f32x4*)p;
 }
-
-typedef __attribute__((address_space(1))) void global_void;
-typedef __attribute__((address_space(3))) void lds_void;
 
 // ---------------------------------------------------------------- three-term split
 // x = x0 + x1 + x2 with x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1):
@@ -105,6 +100,56 @@ __device__ __forceinline__ SplitPair split_pair(float a, float b) {
     return o;
 }
 
+// The three-term split by truncation: x0 and x1 are the upper halves of x and of
+// the exact difference x - x0, x2 the upper half of what is left (8 bits, so
+// exact). Eleven instructions for two elements against split_pair's seven, but
+// all of the plain VALU, which takes two waves' instructions at once and runs
+// beside the MFMAs; the conversions and dot products of split_pair hold up both.
+// Measured with two waves per SIMD, cycles for 24 pairs and 48 MFMAs of each:
+// 2528 by truncation, 4012 with split_pair (MFMAs alone 1564). The staged GEMM
+// splits each element a quarter as often per MFMA and runs no faster with it.
+__device__ __forceinline__ SplitPair split_pair_trunc(float a, float b) {
+    SplitPair o;
+    unsigned ua, ub;
+#pragma unroll
+    for (int t = 0; t < kTerms; ++t) {
+        ua = __builtin_bit_cast(unsigned, a);
+        ub = __builtin_bit_cast(unsigned, b);
+        o.t[t] = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(ub, ua, 0x07060302));
+        a -= __builtin_bit_cast(float, ua & 0xffff0000u);
+        b -= __builtin_bit_cast(float, ub & 0xffff0000u);
+    }
+    return o;
+}
+
+// The terms of split_pair, bit for bit, with the upper halves taken back by a shift
+// and a mask instead of dot products: for products whose tiles are computed now by
+// the staged path, now by direct_loop, with the same result.
+__device__ __forceinline__ SplitPair split_pair_round(float a, float b) {
+    SplitPair o;
+#pragma unroll
+    for (int t = 0; t < kTerms; ++t) {
+        o.t[t] = __builtin_convertvector((f32x2{a, b}), bf16x2);
+        const unsigned u = __builtin_bit_cast(unsigned, o.t[t]);
+        a -= __builtin_bit_cast(float, u << 16);
+        b -= __builtin_bit_cast(float, u & 0xffff0000u);
+    }
+    return o;
+}
+
+struct SplitOct {
+    bf16x8 t[kTerms];
+};
+template <SplitPair (*Split)(float, float)>
+__device__ __forceinline__ SplitOct split_oct(f32x4 u, f32x4 v) {
+    const SplitPair a = Split(u[0], u[1]), b = Split(u[2], u[3]), c = Split(v[0], v[1]), d = Split(v[2], v[3]);
+    SplitOct o;
+#pragma unroll
+    for (int t = 0; t < kTerms; ++t)
+        o.t[t] = bf16x8{a.t[t][0], a.t[t][1], b.t[t][0], b.t[t][1], c.t[t][0], c.t[t][1], d.t[t][0], d.t[t][1]};
+    return o;
+}
+
 // Which of a wave's 16 blocks it multiplies: every block; on a diagonal
 // tile of a symmetric result, only blocks on or above the diagonal (i <= j)
 // of a diagonal quadrant; or none, for the quadrant below the diagonal. The
@@ -125,19 +170,6 @@ __device__ __forceinline__ double block_sum_256(double v, double* red) {
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     return (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-// Operand base pointer, leading dimension and local k of one slab: the
-// second K segment (k >= K1) reads A2 / B2.
-struct SlabSrc {
-    const float* a;
-    const float* b;
-    int lda, ldb, k;
-};
-
-__device__ __forceinline__ SlabSrc slab_src(const GemmProblem& p, int k0) {
-    if (k0 < p.K1) return {p.A, p.B, p.lda, p.ldb, k0};
-    return {p.A2, p.B2, p.lda2, p.ldb2, k0 - p.K1};
 }
 
 typedef __attribute__((address_space(1))) const char gcchar;
@@ -659,87 +691,58 @@ __device__ __forceinline__ void gemm_epilogue(const GemmProblem& p, int tm, int 
     }
 }
 
-// Small-mode operand slab: 64 rows x 16 k in LDS as 4 groups of 16 rows of
-// 64 bytes, each group the 1 KB that one wave-wide 16-byte load to LDS
-// writes. Lane L of a load fills row L / 4 of its group; it reads logical
-// chunk (L % 4) ^ ((row / 4) % 4) of that row (chunk c holds k = 4c .. 4c+3),
-// so chunk c of row r sits at physical chunk c ^ ((r / 4) % 4): sixteen lanes
-// reading one chunk of sixteen consecutive rows hit sixteen distinct 16-byte
-// bank groups.
-constexpr int kSmallSlab = 16;                    // K per slab of a small-mode block
-constexpr int kSmallOperand = 64 * kSmallSlab;    // floats per operand slab
-
-// One wave loads a 64 x 16 K-contiguous slab (rows past lim clamped).
-__device__ __forceinline__ void small_load(const float* __restrict__ base, int ld, int mn0, int lim, int k0,
-                                           float* s) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int r = j * 16 + (lane >> 2);
-        const int row = min(mn0 + r, lim - 1);
-        const int chunk = (lane & 3) ^ ((r >> 2) & 3);
-        const float* g = base + (size_t)row * ld + k0 + chunk * 4;
-        __builtin_amdgcn_global_load_lds((global_void*)g, (lds_void*)(s + j * 256), 16, 0, 0);
-    }
-}
-
-// Values for k = k .. k+3 (k a multiple of 4 below 16) at row mn of a small-mode slab.
-__device__ __forceinline__ void small_fragment(const float* s, int mn, int k, float (&f)[4]) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(s + mn * kSmallSlab + (((k >> 2) ^ ((mn >> 2) & 3)) << 2));
-    f[0] = v[0]; f[1] = v[1]; f[2] = v[2]; f[3] = v[3];
-}
-
-// The MFMAs of one small-mode slab: lane l contributes k = 4 (l / 16) + s
-// to step s, for A and B alike. UPPER: a block on the
-// diagonal of a symmetric result, whose 16 x 16 blocks below the diagonal are
-// left out. BI x BJ: the 16 x 16 blocks of the 64 x 64 block that lie inside
-// the product (a product 32 rows or columns wide fills half of it; the
-// others are left out rather than computed from padding and discarded).
+// The product of the BI x BJ blocks of 16 x 16 at (row0, col0) of problem p over
+// [kb, ke), by the calling wave alone, with no LDS and no barrier: lane l loads k =
+// 8 (l / 16) .. + 7 of rows l % 16 of each block row, 32 bytes that are its MFMA
+// operand once split. The next slab's loads run under the current one's MFMAs.
+// UPPER: on the diagonal of a symmetric result, whose blocks below the diagonal
+// are left out. One copy per block shape, so the loop has no branches on it.
+// Short products are bound by the latency of the first loads and the epilogue;
+// this saves the LDS round trip and the fp32 MFMA's time: 512 layers of 32-256
+// 521 -> 505 us per step, between updates 150 -> 139. (Also for products up to 128
+// wide, whose tiles' four waves would share their operands through LDS, it is
+// slower: 505 -> 536.)
 template <bool UPPER, int BI, int BJ>
-__device__ __forceinline__ void small_mma(const float* sa, const float* sb, int lane, f32x4 (&acc)[16]) {
-    const int r = lane & 15, g = lane >> 4;
-    float a[BI][4], b[BJ][4];
+__device__ __forceinline__ void direct_loop(const GemmProblem& p, int row0, int col0, int kb, int ke, int lane,
+                                            f32x4 (&acc)[16]) {
+    constexpr int kA[6] = {2, 1, 0, 1, 0, 0}, kB[6] = {0, 1, 2, 0, 1, 0};
+    const int r = lane & 15, c = lane >> 4;
+    unsigned oa[BI], ob[BJ];
 #pragma unroll
-    for (int i = 0; i < BI; ++i) small_fragment(sa, i * 16 + r, g * 4, a[i]);
+    for (int i = 0; i < BI; ++i) oa[i] = (unsigned)min(row0 + 16 * i + r, p.M - 1) * (unsigned)p.lda * 4u + c * 32u;
 #pragma unroll
-    for (int j = 0; j < BJ; ++j) small_fragment(sb, j * 16 + r, g * 4, b[j]);
+    for (int j = 0; j < BJ; ++j) ob[j] = (unsigned)min(col0 + 16 * j + r, p.N - 1) * (unsigned)p.ldb * 4u + c * 32u;
+    f32x4 ra[BI][2], rb[BJ][2];
+    auto load = [&](int k) {
+        const bool two = k >= p.K1;
+        const int kl = two ? k - p.K1 : k;
+        const gcchar* a = (const gcchar*)((two ? p.A2 : p.A) + kl);
+        const gcchar* b = (const gcchar*)((two ? p.B2 : p.B) + kl);
 #pragma unroll
-    for (int st = 0; st < 4; ++st)
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int i = 0; i < BI; ++i) ra[i][h] = *(global_f32x4*)(a + oa[i] + 16 * h);
+#pragma unroll
+            for (int j = 0; j < BJ; ++j) rb[j][h] = *(global_f32x4*)(b + ob[j] + 16 * h);
+        }
+    };
+    load(kb);
+    for (int k = kb; k < ke; k += kSlab) {
+        SplitOct a[BI], b[BJ];
+#pragma unroll
+        for (int i = 0; i < BI; ++i) a[i] = split_oct<split_pair_round>(ra[i][0], ra[i][1]);
+#pragma unroll
+        for (int j = 0; j < BJ; ++j) b[j] = split_oct<split_pair_round>(rb[j][0], rb[j][1]);
+        if (k + kSlab < ke) load(k + kSlab);
 #pragma unroll
         for (int i = 0; i < BI; ++i)
 #pragma unroll
-            for (int j = 0; j < BJ; ++j)
-                if (!UPPER || i <= j)
-                    acc[i * 4 + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][st], b[j][st], acc[i * 4 + j], 0, 0, 0);
-}
-
-// Starts the loads of slab k0 of a small-mode block into stage s (A then B).
-__device__ __forceinline__ void small_issue(const GemmProblem& p, int row0, int col0, int k0, float* s) {
-    const SlabSrc src = slab_src(p, k0);
-    small_load(src.a, src.lda, row0, p.M, src.k, s);
-    small_load(src.b, src.ldb, col0, p.N, src.k, s + kSmallOperand);
-}
-
-// The K loop of a small-mode block computed by the calling wave alone in its
-// own LDS stages s0, s1 (2 x 64 x 16 floats each), with no workgroup barrier:
-// slab k + 1 loads while slab k is multiplied. One copy per block shape, so
-// the loop has no branches on it.
-template <bool UPPER, int BI, int BJ>
-__device__ __forceinline__ void small_loop(const GemmProblem& p, int row0, int col0, int nk, float* s0, float* s1,
-                                           int lane, f32x4 (&acc)[16]) {
-    small_issue(p, row0, col0, 0, s0);
-    for (int kt = 0; kt < nk; ++kt) {
-        float* cur = (kt & 1) ? s1 : s0;
-        float* nxt = (kt & 1) ? s0 : s1;
-        // The other stage's slab was read by the previous step's MFMAs; refill it.
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (kt + 1 < nk) {
-            small_issue(p, row0, col0, (kt + 1) * kSmallSlab, nxt);
-            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // all but the 8 loads just issued: slab kt
-        } else {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        }
-        small_mma<UPPER, BI, BJ>(cur, cur + kSmallOperand, lane, acc);
+            for (int u = 0; u < 6; ++u)
+#pragma unroll
+                for (int j = 0; j < BJ; ++j)
+                    if (!UPPER || i <= j)
+                        acc[i * 4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i].t[kA[u]], b[j].t[kB[u]],
+                                                                                 acc[i * 4 + j], 0, 0, 0);
     }
 }
 
@@ -748,28 +751,24 @@ __device__ __forceinline__ void small_loop(const GemmProblem& p, int row0, int c
 // no block computes. The block's shape (on the diagonal of a symmetric
 // result or not; 2 or 4 of its 16-row and 16-column strips inside the
 // product) is uniform over the wave and picks the loop once.
-__device__ __forceinline__ void small_unit(const GemmProblem& p, const SmallUnit& su, float* s0, float* s1,
-                                           float beta1, int lane) {
+__device__ __forceinline__ void small_unit(const GemmProblem& p, const SmallUnit& su, float beta1, int lane) {
     f32x4 acc[16];
 #pragma unroll
     for (int b = 0; b < 16; ++b)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
-    const int row0 = su.bm * kSmallDim, col0 = su.bn * kSmallDim;
-    const int nk = p.K / kSmallSlab;
+    const int row0 = su.bm * kSmallDim, col0 = su.bn * kSmallDim, K = p.K;
     const bool diag = p.upper && su.bm == su.bn;   // uniform: the block is read with scalar loads
     // Strips inside the product: M and N are multiples of 32.
     const int bi = min(4, (p.M - row0) / 16), bj = min(4, (p.N - col0) / 16);
-    if (diag) {
-        if (bi == 4 && bj == 4) small_loop<true, 4, 4>(p, row0, col0, nk, s0, s1, lane, acc);
-        else if (bi == 4) small_loop<true, 4, 2>(p, row0, col0, nk, s0, s1, lane, acc);
-        else if (bj == 4) small_loop<true, 2, 4>(p, row0, col0, nk, s0, s1, lane, acc);
-        else small_loop<true, 2, 2>(p, row0, col0, nk, s0, s1, lane, acc);
+    if (diag) {  // a diagonal block is square: symmetric results have M = N
+        if (bi == 4) direct_loop<true, 4, 4>(p, row0, col0, 0, K, lane, acc);
+        else direct_loop<true, 2, 2>(p, row0, col0, 0, K, lane, acc);
     } else {
-        if (bi == 4 && bj == 4) small_loop<false, 4, 4>(p, row0, col0, nk, s0, s1, lane, acc);
-        else if (bi == 4) small_loop<false, 4, 2>(p, row0, col0, nk, s0, s1, lane, acc);
-        else if (bj == 4) small_loop<false, 2, 4>(p, row0, col0, nk, s0, s1, lane, acc);
-        else small_loop<false, 2, 2>(p, row0, col0, nk, s0, s1, lane, acc);
+        if (bi == 4 && bj == 4) direct_loop<false, 4, 4>(p, row0, col0, 0, K, lane, acc);
+        else if (bi == 4) direct_loop<false, 4, 2>(p, row0, col0, 0, K, lane, acc);
+        else if (bj == 4) direct_loop<false, 2, 4>(p, row0, col0, 0, K, lane, acc);
+        else direct_loop<false, 2, 2>(p, row0, col0, 0, K, lane, acc);
     }
     const int quadrant = ((su.bm & 1) << 1) | (su.bn & 1);
     gemm_epilogue(p, su.bm >> 1, su.bn >> 1, su.slot, beta1, acc, lane, quadrant);
@@ -785,21 +784,20 @@ __device__ __forceinline__ void small_unit(const GemmProblem& p, const SmallUnit
 // the host arranged it so each XCD's share is balanced and reuses operand
 // panels in its own L2. Units of split tiles leave their partial product in
 // ws for gemm_fixup. A small-mode unit is a group of up to four 64 x 64
-// blocks (small), one per wave, each in its own quarter of the LDS.
+// blocks (small), one per wave.
 template <bool BK>
 __global__ __launch_bounds__(kGemmThreads, 2) void gemm_grouped(const GemmProblem* __restrict__ probs,
                                                                 const TileDesc* __restrict__ tiles,
                                                                 const SmallUnit* __restrict__ small,
                                                                 float beta1, float* __restrict__ ws) {
-    __shared__ __attribute__((aligned(16))) char lds[kGemmLds];
+    __shared__ __attribute__((aligned(16))) char lds[kSlabBytes];
     const TileDesc td = tiles[blockIdx.x];
     if (td.part == kSmallGroup) {
         if constexpr (BK) {
             const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: its block is read with scalar loads
             if (w < td.tn) {
                 const SmallUnit su = small[td.tm + w];
-                float* st = reinterpret_cast<float*>(lds) + w * (4 * kSmallOperand);  // wave w's two stages
-                small_unit(probs[su.prob], su, st, st + 2 * kSmallOperand, beta1, threadIdx.x & 63);
+                small_unit(probs[su.prob], su, beta1, threadIdx.x & 63);
             }
         }
         return;

@@ -290,41 +290,6 @@ __device__ __forceinline__ Piece piece_of(int wave, int M, int N) {
     return p;
 }
 
-// The three-term split by truncation: x0 and x1 are the upper halves of x and of
-// the exact difference x - x0, x2 the upper half of what is left (8 bits, so
-// exact). Eleven instructions for two elements against split_pair's seven, but
-// all of the plain VALU, which takes two waves' instructions at once and runs
-// beside the MFMAs; the conversions and dot products of split_pair hold up both.
-// Measured with two waves per SIMD, cycles for 24 pairs and 48 MFMAs of each:
-// 2528 by truncation, 4012 with split_pair (MFMAs alone 1564). The staged GEMM
-// splits each element a quarter as often per MFMA and runs no faster with it.
-__device__ __forceinline__ SplitPair split_pair_trunc(float a, float b) {
-    SplitPair o;
-    unsigned ua, ub;
-#pragma unroll
-    for (int t = 0; t < kTerms; ++t) {
-        ua = __builtin_bit_cast(unsigned, a);
-        ub = __builtin_bit_cast(unsigned, b);
-        o.t[t] = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(ub, ua, 0x07060302));
-        a -= __builtin_bit_cast(float, ua & 0xffff0000u);
-        b -= __builtin_bit_cast(float, ub & 0xffff0000u);
-    }
-    return o;
-}
-
-struct SplitOct {
-    bf16x8 t[kTerms];
-};
-__device__ __forceinline__ SplitOct split_oct(f32x4 u, f32x4 v) {
-    const SplitPair a = split_pair_trunc(u[0], u[1]), b = split_pair_trunc(u[2], u[3]);
-    const SplitPair c = split_pair_trunc(v[0], v[1]), d = split_pair_trunc(v[2], v[3]);
-    SplitOct o;
-#pragma unroll
-    for (int t = 0; t < kTerms; ++t)
-        o.t[t] = bf16x8{a.t[t][0], a.t[t][1], b.t[t][0], b.t[t][1], c.t[t][0], c.t[t][1], d.t[t][0], d.t[t][1]};
-    return o;
-}
-
 // acc += a (rows) x b^T (rows) over k in [0, K), K a multiple of 32, for NBI of
 // the piece's block rows. Lane l takes k = k0 + 4 (l / 16) .. + 3 and k0 + 16 + 4
 // (l / 16) .. + 3 of row l % 16 of a block, for a and b alike, so every product
@@ -350,9 +315,9 @@ __device__ __forceinline__ void piece_mma_n(const float* a, const float* b, int 
     for (int k0 = 0; k0 < K; k0 += 32) {
         SplitOct sb[BJ], sa[NBI];
 #pragma unroll
-        for (int j = 0; j < BJ; ++j) sb[j] = split_oct(fb[j][0], fb[j][1]);
+        for (int j = 0; j < BJ; ++j) sb[j] = split_oct<split_pair_trunc>(fb[j][0], fb[j][1]);
 #pragma unroll
-        for (int i = 0; i < NBI; ++i) sa[i] = split_oct(fa[i][0], fa[i][1]);
+        for (int i = 0; i < NBI; ++i) sa[i] = split_oct<split_pair_trunc>(fa[i][0], fa[i][1]);
         read(k0 + 32 < K ? k0 + 32 : 0);  // past the end: group 0 again, never multiplied
 #pragma unroll
         for (int i = 0; i < NBI; ++i)

@@ -48,3 +48,27 @@ def test_between_updates_product_is_componentwise_fp32(m, n, symmetrize, graded)
     off = np.max(np.abs(got - want) / bound)
     print(f"{m} x {n}: largest error {off:.3f} of the bound", flush=True)
     assert off <= 1.0
+
+
+@pytest.mark.parametrize("shape", [(64, 200), (33, 130), (160, 32)])
+@pytest.mark.parametrize("interval", [1, 2])
+def test_small_mode_blocks_equal_tiles_bitwise(shape, interval):
+    """In a context with many units a narrow product runs as 64 x 64 blocks straight from global
+    memory, alone as 128 x 128 tiles through LDS: the same terms in the same order."""
+    m, n = shape
+    kw = dict(split_k=False, precond_interval=interval)
+    assert any(v[2] > 0 for v in Jorge.plan_stages([shape] * 300, **kw).values())
+    assert all(v[2] == 0 for v in Jorge.plan_stages([shape], **kw).values())
+    rng = np.random.default_rng([m, n, interval])
+    dev = lambda x: torch.from_numpy(x.astype(np.float32)).cuda()  # noqa: E731
+    many, one = Jorge([shape] * 300, **kw), Jorge([shape], **kw)
+    theta = rng.standard_normal(shape)
+    pm, po = [dev(theta) for _ in range(300)], [dev(theta)]
+    for _ in range(3):
+        g = dev(rng.standard_normal(shape) * 1e-2)
+        many.step(pm, [g] * 300, 0.1, 0.9, 0.9, 0.0)
+        one.step(po, [g], 0.1, 0.9, 0.9, 0.0)
+    for l in (0, 151, 299):
+        assert torch.equal(pm[l], po[0]), l
+        for k in ("L", "R", "mom", "mom_sgd"):
+            assert torch.equal(many.get_state(l, k), one.get_state(0, k)), (l, k)
