@@ -184,8 +184,9 @@ jorge_status jorge_plan(const jorge_shape* shapes, int32_t num_layers, const jor
  * launches, split_tiles[i] the number of 128 x 128 tiles split along K (0 when
  * split_k = 0) and small_blocks[i] the number of 64 x 64 blocks computed in
  * small mode (products with at most 64 rows or columns, one wave per block,
- * up to four per unit). A unit is a whole tile, a piece of a split tile or a
- * group of small-mode blocks. units, split_tiles and small_blocks are host
+ * up to four per unit). A unit is a whole tile, a piece of a split tile, a
+ * group of small-mode blocks or, in a stage with little work, a 32 x 32 block
+ * whose workgroup splits K over its waves. units, split_tiles and small_blocks are host
  * arrays of n entries; any may be NULL, not all when n > 0. Same argument
  * rules and errors as jorge_plan. */
 jorge_status jorge_plan_stages(const jorge_shape* shapes, int32_t num_layers, const jorge_hparams* hp,

@@ -66,6 +66,7 @@
 #include <new>
 #include <queue>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "../../include/jorge.h"
@@ -106,12 +107,14 @@ struct GemmStage {
     std::vector<GemmProblem> probs;
     std::vector<TileDesc> tiles;    // work units, in dispatch order once uploaded
     std::vector<SmallUnit> small;   // small-mode blocks (grouped by four into units of tiles)
+    std::vector<SmallUnit> blocks;  // wave-split: the 32 x 32 blocks of every product, in place of all the above
     std::vector<FixupDesc> fix;     // split tiles
     int nparts = 0;                 // split-workspace blocks the stage uses
     double flops = 0.0;             // algorithmic flops of all its products
     GemmProblem* dprobs = nullptr;
     TileDesc* dtiles = nullptr;
     SmallUnit* dsmall = nullptr;
+    SmallUnit* dblocks = nullptr;
     FixupDesc* dfix = nullptr;
     int ntiles() const { return (int)tiles.size(); }
 };
@@ -431,6 +434,8 @@ constexpr int64_t kFixupPartsPerK = 5;
 // A split plan is kept only if the model puts it this much below the unsplit launch
 // (the partial products' traffic also slows the other units, which the model leaves out).
 constexpr double kSplitGain = 0.97;
+// Most work, in 32 x 32 x 32 products, that a level runs wave-split.
+constexpr int64_t kWaveSplitWork = 16384;
 
 // Duration of a list of units (in dispatch order) on ncu CUs: placed one per
 // CU, then a second per CU; later, each unit goes to a CU with a free place,
@@ -634,8 +639,47 @@ void split_stage(GemmStage& st) {
     st.tiles.swap(out);
 }
 
+// Wave-split in place of tiles: a level with fewer tiles than CUs whose whole
+// work is short. Its 32 x 32 blocks, eight waves each, spread it over more CUs than
+// the tiles would and need no second launch; past kWaveSplitWork the tiles' four
+// times better reuse of operands wins. Measured per updating step, tiles (with
+// their fixups) against blocks: 64 x 576 139 -> 76 us, 256 x 256 138 -> 56, 256 x
+// 1024 216 -> 139, 512 x 512 157 -> 102; with four times the limit 768 x 768 (18 432
+// products in its levels) goes from 189 to 213 us and 1024 x 1024 from 270 to 363.
+bool wave_split_pays(const GemmStage& st) {
+    if (!st.kmajor_b || st.tiles.empty() || !st.small.empty() || st.tiles.size() >= (size_t)kCus) return false;
+    int64_t slabs = 0;
+    for (const GemmProblem& p : st.probs) {
+        const int64_t bm = p.M / 32, bn = p.N / 32;
+        slabs += (p.upper ? bm * (bm + 1) / 2 : bm * bn) * (p.K / kSlab);
+    }
+    return slabs <= kWaveSplitWork;
+}
+
+void make_wave_split(GemmStage& st) {
+    for (size_t i = 0; i < st.probs.size(); ++i) {
+        const GemmProblem& p = st.probs[i];
+        int slot = 0;
+        for (int bm = 0; bm * 32 < p.M; ++bm)
+            for (int bn = p.upper ? bm : 0; bn * 32 < p.N; ++bn) st.blocks.push_back({(int)i, bm, bn, slot++, 0, 0, 0, 0});
+    }
+    // Longest K first (all of a problem's blocks stay together).
+    std::stable_sort(st.blocks.begin(), st.blocks.end(), [&](const SmallUnit& a, const SmallUnit& b) {
+        return st.probs[a.prob].K > st.probs[b.prob].K;
+    });
+    st.tiles.clear();
+}
+
 template <bool BK>
 jorge_status launch_gemm(jorge_ctx* c, const GemmStage& st, int stage, float beta1) {
+    if (!st.blocks.empty()) {
+        TimedLaunch tl(c, stage);
+        hipLaunchKernelGGL(gemm_wave_split, dim3((unsigned)st.blocks.size()), dim3(kWaveSplitThreads), 0, c->stream,
+                           st.dprobs, st.dblocks, beta1);
+        tl.finish();
+        JORGE_HIP(c, hipGetLastError());
+        return JORGE_OK;
+    }
     if (st.ntiles() == 0) return JORGE_OK;
     TimedLaunch tl(c, stage);
     hipLaunchKernelGGL((gemm_grouped<BK>), dim3(st.ntiles()), dim3(kGemmThreads), 0, c->stream,
@@ -765,7 +809,7 @@ size_t plan(jorge_ctx* c) {
                 F.off_v2t = take(kk);  // H^T W, k x k
                 F.off_xa = take(kd);   // A_new H, d x k
             }
-            F.off_part = take((size_t)F.nparts * kWaveSlots * sizeof(double));
+            F.off_part = take((size_t)F.nparts * kBlockSlots * sizeof(double));
             F.off_sc = take(sizeof(FactorScalars));
             (side == 0 ? L.fL : L.fR) = (int)c->factors.size();
             c->factors.push_back(F);
@@ -782,7 +826,7 @@ size_t plan(jorge_ctx* c) {
         L.off_mom = take(dense);
         L.off_msgd = take(dense);
         L.n_part_m = tile_count(L.mp, L.np);
-        L.off_part_m = take((size_t)L.n_part_m * kWaveSlots * sizeof(double));
+        L.off_part_m = take((size_t)L.n_part_m * kBlockSlots * sizeof(double));
         L.n_part_sgd = ((L.m + 63) / 64) * ((L.n + 63) / 64);
         L.off_part_sgd = take((size_t)L.n_part_sgd * sizeof(double));
         L.off_ls = take(sizeof(LayerScalars));
@@ -855,7 +899,7 @@ void add_explicit(jorge_ctx* c, const FactorHost& F, const FactorDev& fd, const 
 // Mo: the other factor's statistic when that factor is in the explicit order
 // (H^T H is exactly it: G^T G for L_hat, G G^T for R_hat; kp x kp, ld kp,
 // computed in the gram level and kept until the next step's), or null.
-int add_factored(jorge_ctx* c, const FactorHost& F, const FactorDev& fd, const float* Hr, const float* Ht,
+void add_factored(jorge_ctx* c, const FactorHost& F, const FactorDev& fd, const float* Hr, const float* Ht,
                  const float* Mo) {
     const bool sym = c->hp.symmetrize != 0;
     const int dp = F.dp, kp = F.kp;
@@ -924,7 +968,7 @@ int add_factored(jorge_ctx* c, const FactorHost& F, const FactorDev& fd, const f
     add_problem(c->nt[last], y5, 2 * k * d * d);
     GemmProblem nu = product(Yt4, dp, Yt4, dp, kp, kp, dp);
     nu.X = Q; nu.ldx = kp; nu.flags = EF_DOT; nu.upper = 1; nu.partials = fd.partials;
-    const int slots = add_problem(c->nt[last], nu, k * k * d);
+    add_problem(c->nt[last], nu, k * k * d);
     // Literal mode (factored order only): S^T = U^T H = Yt_4 H (general).
     if (!sym) {
         GemmProblem s = product(Yt4, dp, Ht, dp, kp, kp, dp);
@@ -979,7 +1023,6 @@ int add_factored(jorge_ctx* c, const FactorHost& F, const FactorDev& fd, const f
         u.coef = CO_LITUPD;
         add_problem(c->nt[ST_UPDATE], u, 2 * d * d * k);
     }
-    return slots;
 }
 
 // Fills the host-side launch tables (device pointers already known).
@@ -1067,8 +1110,7 @@ void build_tables(jorge_ctx* c, std::vector<LayerDev>& ld, std::vector<FactorDev
             // (The explicit factor keeps its statistic until the next step's gram level,
             // past the low-rank preconditioning that reads Q.)
             const float* Mo = O.expl ? at<float>(c, O.off_w[0]) : nullptr;
-            F.nparts = add_factored(c, F, fd[fi], Hr, Ht, Mo);
-            fd[fi].nparts = F.nparts;
+            add_factored(c, F, fd[fi], Hr, Ht, Mo);
         }
     }
     // Preconditioning, largest layers first.
@@ -1171,6 +1213,33 @@ std::string check_stage(const jorge_ctx* c, const GemmStage& st, bool bk, const 
              !in_buffer(c, p.mom, fl((int64_t)(p.valid_m - 1) * p.ldmom + p.valid_n - 1))))
             return where + "momentum";
         if (p.coef != CO_ONE && !in_buffer(c, p.sc, (int64_t)sizeof(FactorScalars))) return where + "scalars";
+    }
+    // A wave-split launch: every 32 x 32 block of every problem once, each with its
+    // own partial-sum slot, and nothing else.
+    if (!st.blocks.empty()) {
+        if (!bk || !st.tiles.empty() || !st.small.empty() || !st.fix.empty() || st.nparts)
+            return std::string(name) + ": wave-split stage";
+        std::vector<std::vector<char>> seen(st.probs.size()), slots(st.probs.size());
+        size_t total = 0;
+        for (size_t i = 0; i < st.probs.size(); ++i) {
+            const GemmProblem& p = st.probs[i];
+            const size_t bm = p.M / 32, bn = p.N / 32, n = p.upper ? bm * (bm + 1) / 2 : bm * bn;
+            seen[i].assign(bm * bn, 0);
+            slots[i].assign(n, 0);
+            total += n;
+            if ((p.flags & (EF_NORM | EF_DOT | EF_MOMENTUM)) &&
+                !in_buffer(c, p.partials, (int64_t)n * (int64_t)sizeof(double)))
+                return std::string(name) + ": wave-split partial sums";
+        }
+        for (const SmallUnit& u : st.blocks) {
+            if (u.prob < 0 || u.prob >= (int)st.probs.size()) return std::string(name) + ": wave-split problem";
+            const GemmProblem& p = st.probs[u.prob];
+            if (u.bm < 0 || u.bn < 0 || u.bm >= p.M / 32 || u.bn >= p.N / 32 || (p.upper && u.bm > u.bn) ||
+                u.slot < 0 || (size_t)u.slot >= slots[u.prob].size() || slots[u.prob][u.slot]++ ||
+                seen[u.prob][(size_t)u.bm * (p.N / 32) + u.bn]++)
+                return std::string(name) + ": wave-split block";
+        }
+        return total == st.blocks.size() ? "" : std::string(name) + ": wave-split coverage";
     }
     // Every tile of every problem is covered exactly once: whole, or by split
     // units whose K ranges tile [0, K) and whose parts match one fixup.
@@ -1304,7 +1373,7 @@ std::string check_tables(const jorge_ctx* c, const std::vector<FactorDev>& fd) {
             return "symmetrize tile";
     }
     for (const FactorDev& F : fd)
-        if (!in_buffer(c, F.partials, (int64_t)F.nparts * kWaveSlots * (int64_t)sizeof(double)) || F.nparts < 1)
+        if (!in_buffer(c, F.partials, (int64_t)F.nparts * (int64_t)sizeof(double)) || F.nparts < 1)
             return "factor partials";
     // The small-context kernels: every factor (index 2 layer + side) once, of a size
     // its team takes, with its state, and each layer's momenta.
@@ -1347,18 +1416,48 @@ jorge_status layout_context(jorge_ctx* c, const jorge_shape* shapes, int32_t num
     return JORGE_OK;
 }
 
+// How many partial sums each factor's ||X|| and each layer's ||m|| have, from the
+// way the launch that writes them runs.
+void count_partials(jorge_ctx* c, std::vector<LayerDev>& ld, std::vector<FactorDev>& fd) {
+    std::unordered_map<const double*, int> count;
+    for (int i = 0; i < ST_COUNT; ++i)
+        for (const GemmStage* st : {&c->nt[i], &c->nn[i]})
+            for (const GemmProblem& p : st->probs)
+                if (p.flags & (EF_NORM | EF_DOT | EF_MOMENTUM)) {
+                    const int64_t u = st->blocks.empty() ? kTile : 32, a = (p.M + u - 1) / u, b = (p.N + u - 1) / u;
+                    count[p.partials] = (int)(p.upper ? a * (a + 1) / 2 : a * b) * (st->blocks.empty() ? kWaveSlots : 1);
+                }
+    for (FactorDev& F : fd)
+        if (count.count(F.partials)) F.nparts = count[F.partials];
+    for (LayerDev& L : ld)
+        if (count.count(L.part_m)) L.n_part_m = count[L.part_m];
+}
+
 // Launch tables for the arena at c->arena, checked on the host.
 jorge_status tables_context(jorge_ctx* c, std::vector<LayerDev>& ld, std::vector<FactorDev>& fd) {
     try {
         for (int i = 0; i < ST_COUNT; ++i) c->nt[i].kmajor_b = true;
         build_tables(c, ld, fd);
+        // Wave-split is a way of splitting K, so split_k = 0 excludes it. The two
+        // launches that write a layer's momentum norm (on updating and on other
+        // steps) are wave-split together, so the norm has one count of partial sums.
+        const bool norm_pair = (c->nt[ST_PRECOND_R].tiles.empty() || wave_split_pays(c->nt[ST_PRECOND_R])) &&
+                               (c->nt[ST_UPRECOND_R].tiles.empty() || wave_split_pays(c->nt[ST_UPRECOND_R])) &&
+                               c->nn[ST_PRECOND_R].tiles.empty() && c->nn[ST_UPRECOND_R].tiles.empty();
+        auto wave_split = [&](const GemmStage* st) {
+            if (!c->hp.split_k) return false;
+            if (st == &c->nt[ST_PRECOND_R] || st == &c->nt[ST_UPRECOND_R]) return norm_pair && !st->tiles.empty();
+            return wave_split_pays(*st);
+        };
         for (int i = 0; i < ST_COUNT; ++i)
             for (GemmStage* st : {&c->nt[i], &c->nn[i]}) {
                 make_small(*st);
-                if (c->hp.split_k) split_stage(*st);
+                if (wave_split(st)) make_wave_split(*st);
+                else if (c->hp.split_k) split_stage(*st);
                 order_for_xcds(st->tiles);
                 c->splitws_blocks = std::max<int64_t>(c->splitws_blocks, st->nparts);
             }
+        count_partials(c, ld, fd);
         const std::string e = check_tables(c, fd);
         if (!e.empty()) return fail(c, JORGE_ERR_HIP, "launch table check failed: " + e);
     } catch (const std::bad_alloc&) {
@@ -1409,6 +1508,7 @@ jorge_status upload_stage(jorge_ctx* c, GemmStage& st) {
     if (s != JORGE_OK) return s;
     if ((s = upload(c, st.fix, &st.dfix)) != JORGE_OK) return s;
     if ((s = upload(c, st.small, &st.dsmall)) != JORGE_OK) return s;
+    if ((s = upload(c, st.blocks, &st.dblocks)) != JORGE_OK) return s;
     return upload(c, st.tiles, &st.dtiles);
 }
 
@@ -1434,7 +1534,7 @@ size_t tables_bytes(const jorge_ctx* c, const std::vector<LayerDev>& ld, const s
                table_bytes(c->sym_tiles) + table_bytes(c->grouped) + table_bytes(c->chain);
     for (int i = 0; i < ST_COUNT; ++i)
         for (const GemmStage* s : {&c->nt[i], &c->nn[i]})
-            b += table_bytes(s->probs) + table_bytes(s->fix) + table_bytes(s->small) + table_bytes(s->tiles);
+            b += table_bytes(s->probs) + table_bytes(s->fix) + table_bytes(s->small) + table_bytes(s->blocks) + table_bytes(s->tiles);
     return b;
 }
 
@@ -1449,6 +1549,7 @@ void free_ctx(jorge_ctx* c) {
             if (st->dprobs) (void)hipFree(st->dprobs);
             if (st->dtiles) (void)hipFree(st->dtiles);
             if (st->dsmall) (void)hipFree(st->dsmall);
+            if (st->dblocks) (void)hipFree(st->dblocks);
             if (st->dfix) (void)hipFree(st->dfix);
         }
     if (c->splitws) (void)hipFree(c->splitws);
@@ -1768,7 +1869,8 @@ jorge_status jorge_plan_stages(const jorge_shape* shapes, int32_t num_layers, co
     const jorge_status st = plan_only(shapes, num_layers, hp, &c);
     if (st != JORGE_OK) return st;
     for (int i = 0; i < std::min<int>(n, ST_COUNT); ++i) {
-        if (units) units[i] = (int64_t)c->nt[i].tiles.size() + (int64_t)c->nn[i].tiles.size();
+        if (units)
+            units[i] = (int64_t)c->nt[i].tiles.size() + (int64_t)c->nn[i].tiles.size() + (int64_t)c->nt[i].blocks.size();
         if (split_tiles) split_tiles[i] = (int64_t)c->nt[i].fix.size() + (int64_t)c->nn[i].fix.size();
         if (small_blocks) small_blocks[i] = (int64_t)c->nt[i].small.size() + (int64_t)c->nn[i].small.size();
     }

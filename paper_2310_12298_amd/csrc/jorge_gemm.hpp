@@ -30,9 +30,16 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // the quadrant) is one v_mfma_f32_16x16x4_f32 accumulator, in which lane l
 // holds column l % 16, rows 4 (l / 16) .. 4 (l / 16) + 3. Each lane thus
 // holds, for each of its 16 blocks, four consecutive rows of one column.
-// Row and column of the first of those four values, relative to the tile:
-__device__ __forceinline__ int acc_row(int b, int lane, int wy) { return wy * 64 + (b >> 2) * 16 + (lane >> 4) * 4; }
-__device__ __forceinline__ int acc_col(int b, int lane, int wx) { return wx * 64 + (b & 3) * 16 + (lane & 15); }
+// Where a lane's accumulators lie in the result: the first of block b's four
+// values is at row + 16 (b / 4), col + 16 (b % 4).
+struct Place {
+    int row, col;
+    bool diag;  // on a diagonal tile or block of the result (row = col may occur in it)
+};
+// Of quadrant `wave` of the 128 x 128 tile (tm, tn).
+__device__ __forceinline__ Place place_of(int tm, int tn, int lane, int wave) {
+    return {tm * 128 + (wave >> 1) * 64 + (lane >> 4) * 4, tn * 128 + (wave & 1) * 64 + (lane & 15), tm == tn};
+}
 
 constexpr int kTile = 128;                    // tile rows = tile columns
 constexpr int kSlab = 32;                     // K per LDS stage
@@ -107,7 +114,8 @@ __device__ __forceinline__ SplitPair split_pair(float a, float b) {
 // beside the MFMAs; the conversions and dot products of split_pair hold up both.
 // Measured with two waves per SIMD, cycles for 24 pairs and 48 MFMAs of each:
 // 2528 by truncation, 4012 with split_pair (MFMAs alone 1564). The staged GEMM
-// splits each element a quarter as often per MFMA and runs no faster with it.
+// splits each element a quarter as often per MFMA, in a clump before them, and is
+// slower with it (ResNet-50's step 5.5 -> 7.2 ms).
 __device__ __forceinline__ SplitPair split_pair_trunc(float a, float b) {
     SplitPair o;
     unsigned ua, ub;
@@ -437,15 +445,13 @@ __device__ __forceinline__ void st4_at(float* base, unsigned byte_off, f32x4 v) 
 // Offsets are 32-bit (every matrix has fewer than 2^32 elements) from
 // uniform base pointers; per-element masks are only evaluated on edge tiles
 // and on diagonal tiles of symmetric results.
-template <int F, bool UP, bool MASKED>
-__device__ __forceinline__ double epilogue_body(const GemmProblem& p, int tm, int tn, const f32x4 (&acc)[16],
-                                                float ci, float cx, float cc, int lane, int wave) {
+template <int F, bool UP, bool MASKED, int NB>
+__device__ __forceinline__ double epilogue_body(const GemmProblem& p, const Place& at, const f32x4 (&acc)[NB],
+                                                float ci, float cx, float cc) {
     constexpr bool kReadX = (F & EF_READX) != 0;
     constexpr bool kRead = (F & (EF_READX | EF_DOT)) != 0;
-    const int row0 = tm * kTile, col0 = tn * kTile;
-    const int wy = wave >> 1, wx = wave & 1;
-    const bool diag = MASKED && UP && tm == tn;
-    const bool ident = kReadX && ci != 0.f && tm == tn;
+    const bool diag = MASKED && UP && at.diag;
+    const bool ident = kReadX && ci != 0.f && at.diag;
     constexpr double w_off = UP ? 2.0 : 1.0;   // off-diagonal tiles of a symmetric result
     float* C = p.C;
     float* C2 = p.C2;
@@ -459,14 +465,14 @@ __device__ __forceinline__ double epilogue_body(const GemmProblem& p, int tm, in
     // Masked tiles clamp positions outside M x N to the last row and column
     // and drop those values; every position the thread uses is also one it
     // writes, and no other thread writes it.
-    f32x4 xv[16];
+    f32x4 xv[NB];
     if constexpr (kRead) {
 #pragma unroll
-        for (int b = 0; b < 16; ++b) {
-            const int col = col0 + acc_col(b, lane, wx);
+        for (int b = 0; b < NB; ++b) {
+            const int col = at.col + (b & 3) * 16;
             const int colc = MASKED ? min(col, p.N - 1) : col;
             // rowb .. rowb+3 are all inside M when rowb is (M is a multiple of 4).
-            const int rowb = row0 + acc_row(b, lane, wy);
+            const int rowb = at.row + (b >> 2) * 16;
             const int rowc = MASKED ? min(rowb, p.M - 4) : rowb;
             const unsigned ox = (unsigned)rowc * sx + 4u * (unsigned)colc;
 #pragma unroll
@@ -476,9 +482,9 @@ __device__ __forceinline__ double epilogue_body(const GemmProblem& p, int tm, in
 
     double part = 0.0;
 #pragma unroll
-    for (int b = 0; b < 16; ++b) {
-        const int col = col0 + acc_col(b, lane, wx);
-        const int rowb = row0 + acc_row(b, lane, wy);
+    for (int b = 0; b < NB; ++b) {
+        const int col = at.col + (b & 3) * 16;
+        const int rowb = at.row + (b >> 2) * 16;
         // rowb .. rowb+3 are all inside M when rowb is (M is a multiple of 4).
         if (MASKED && (rowb >= p.M || col >= p.N)) continue;
         // X at positions this thread writes (read and written by the same thread).
@@ -530,23 +536,22 @@ __device__ __forceinline__ double epilogue_body(const GemmProblem& p, int tm, in
 
 // The epilogue for a flag combination without a compiled body (not used by
 // the launch tables the library builds; kept so every combination works).
-__device__ __forceinline__ double epilogue_generic(const GemmProblem& p, int tm, int tn, const f32x4 (&acc)[16],
-                                                float ci, float cx, float cc, int lane, int wave) {
+template <int NB>
+__device__ __forceinline__ double epilogue_generic(const GemmProblem& p, const Place& at, const f32x4 (&acc)[NB],
+                                                   float ci, float cx, float cc) {
     double part = 0.0;
     const int F = p.flags;
     const bool up = p.upper != 0;
-    const int row0 = tm * kTile, col0 = tn * kTile;
-    const int wy = wave >> 1, wx = wave & 1;
     float* C = p.C;
     float* C2 = p.C2;
     const float* X = p.X;
     const unsigned sc = 4u * p.ldc, sc2 = 4u * p.ldc2, sx = 4u * p.ldx;
 #pragma unroll
-    for (int b = 0; b < 16; ++b) {
-        const int col = col0 + acc_col(b, lane, wx);
+    for (int b = 0; b < NB; ++b) {
+        const int col = at.col + (b & 3) * 16;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int row = row0 + acc_row(b, lane, wy) + e;
+            const int row = at.row + (b >> 2) * 16 + e;
             if (row >= p.M || col >= p.N || (up && row > col)) continue;
             const float v = acc[b][e];
             const float xe = (F & (EF_READX | EF_DOT)) ? ld_at(X, (unsigned)row * sx + 4u * (unsigned)col) : 0.f;
@@ -566,36 +571,34 @@ __device__ __forceinline__ double epilogue_generic(const GemmProblem& p, int tm,
 }
 
 // m = beta1 m + (1 - beta1) acc on the dense valid_m x valid_n momentum.
-template <bool MASKED>
-__device__ __forceinline__ double epilogue_momentum(const GemmProblem& p, int tm, int tn,
-                                                    const f32x4 (&acc)[16], float beta1, int lane, int wave) {
-    const int row0 = tm * kTile, col0 = tn * kTile;
-    const int wy = wave >> 1, wx = wave & 1;
+template <bool MASKED, int NB>
+__device__ __forceinline__ double epilogue_momentum(const GemmProblem& p, const Place& at, const f32x4 (&acc)[NB],
+                                                    float beta1) {
     float* mom = p.mom;
     const unsigned sm = 4u * p.ldmom;
     // All of this thread's momentum values are loaded before any is stored
     // (one memory round trip per tile); masked tiles clamp positions outside
     // the dense valid_m x valid_n momentum to its last row and column and
     // drop those values.
-    f32x4 mv[16];
+    f32x4 mv[NB];
 #pragma unroll
-    for (int b = 0; b < 16; ++b) {
-        const int col = col0 + acc_col(b, lane, wx);
+    for (int b = 0; b < NB; ++b) {
+        const int col = at.col + (b & 3) * 16;
         const int colc = MASKED ? min(col, p.valid_n - 1) : col;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int row = row0 + acc_row(b, lane, wy) + e;
+            const int row = at.row + (b >> 2) * 16 + e;
             const int rowc = MASKED ? min(row, p.valid_m - 1) : row;
             mv[b][e] = ld_at(mom, (unsigned)rowc * sm + 4u * (unsigned)colc);
         }
     }
     double part = 0.0;
 #pragma unroll
-    for (int b = 0; b < 16; ++b) {
-        const int col = col0 + acc_col(b, lane, wx);
+    for (int b = 0; b < NB; ++b) {
+        const int col = at.col + (b & 3) * 16;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int row = row0 + acc_row(b, lane, wy) + e;
+            const int row = at.row + (b >> 2) * 16 + e;
             if (MASKED && !(row < p.valid_m && col < p.valid_n)) continue;
             const unsigned o = (unsigned)row * sm + 4u * (unsigned)col;
             const float mn = beta1 * mv[b][e] + (1.0f - beta1) * acc[b][e];
@@ -606,11 +609,10 @@ __device__ __forceinline__ double epilogue_momentum(const GemmProblem& p, int tm
     return part;
 }
 
-// The epilogue of quadrant `wave` of tile (tm, tn) of problem p for the
-// product in acc (this lane's accumulators); beta1 is the momentum of
-// EF_MOMENTUM. One uniform switch picks the compiled body for the problem's
-// flags. The wave's partial sum (norm, dot product) goes to sub-slot `wave`
-// of the tile's slot.
+// The epilogue of problem p for the product in acc at `at` (this lane's NB
+// blocks); beta1 is the momentum of EF_MOMENTUM, [row_end, col_end) bounds the tile.
+// One uniform switch picks the compiled body for the problem's flags. Returns
+// the lane's share of the partial sum (norm, dot product).
 //
 // Symmetric results (p.upper): only tiles with tm <= tn are computed. An
 // element (row, col) with row <= col is written at (row, col) and at
@@ -618,16 +620,17 @@ __device__ __forceinline__ double epilogue_momentum(const GemmProblem& p, int tm
 // so the stored matrix is bitwise symmetric whatever the product's rounding.
 // The epilogue reads X only at the positions it is about to write, by the
 // same thread, so X may alias C (an in-place update).
-__device__ __forceinline__ void gemm_epilogue(const GemmProblem& p, int tm, int tn, int slot, float beta1,
-                                              const f32x4 (&acc)[16], int lane, int wave) {
+template <int NB>
+__device__ __forceinline__ double gemm_epilogue_part(const GemmProblem& p, const Place& at, int row_end, int col_end,
+                                                     float beta1, const f32x4 (&acc)[NB]) {
     const int flags = p.flags;
     double part = 0.0;
     if (flags & EF_MOMENTUM) {
         // Interior tiles of the dense valid_m x valid_n momentum need no masks.
-        if ((tm + 1) * kTile <= p.valid_m && (tn + 1) * kTile <= p.valid_n)
-            part = epilogue_momentum<false>(p, tm, tn, acc, beta1, lane, wave);
+        if (row_end <= p.valid_m && col_end <= p.valid_n)
+            part = epilogue_momentum<false>(p, at, acc, beta1);
         else
-            part = epilogue_momentum<true>(p, tm, tn, acc, beta1, lane, wave);
+            part = epilogue_momentum<true>(p, at, acc, beta1);
     } else {
         float ci = 0.f, cx = 0.f, cc = 1.f;
         if (p.coef != CO_ONE) {
@@ -645,47 +648,54 @@ __device__ __forceinline__ void gemm_epilogue(const GemmProblem& p, int tm, int 
             }
         }
         const int key = flags | (p.upper ? 256 : 0);
-        const bool masked = (tm + 1) * kTile > p.M || (tn + 1) * kTile > p.N || (p.upper && tm == tn);
+        const bool masked = row_end > p.M || col_end > p.N || (p.upper && at.diag);
         switch (key) {
-            case EF_STORE: part = masked ? epilogue_body<EF_STORE, false, true>(p, tm, tn, acc, ci, cx, cc, lane, wave)
-                            : epilogue_body<EF_STORE, false, false>(p, tm, tn, acc, ci, cx, cc, lane, wave); break;
-            case EF_STORE | 256: part = masked ? epilogue_body<EF_STORE, true, true>(p, tm, tn, acc, ci, cx, cc, lane, wave)
-                            : epilogue_body<EF_STORE, true, false>(p, tm, tn, acc, ci, cx, cc, lane, wave); break;
-            case EF_STORE_T: part = masked ? epilogue_body<EF_STORE_T, false, true>(p, tm, tn, acc, ci, cx, cc, lane, wave)
-                            : epilogue_body<EF_STORE_T, false, false>(p, tm, tn, acc, ci, cx, cc, lane, wave); break;
-            case EF_DOT | 256: part = masked ? epilogue_body<EF_DOT, true, true>(p, tm, tn, acc, ci, cx, cc, lane, wave)
-                            : epilogue_body<EF_DOT, true, false>(p, tm, tn, acc, ci, cx, cc, lane, wave); break;
+            case EF_STORE: part = masked ? epilogue_body<EF_STORE, false, true>(p, at, acc, ci, cx, cc)
+                            : epilogue_body<EF_STORE, false, false>(p, at, acc, ci, cx, cc); break;
+            case EF_STORE | 256: part = masked ? epilogue_body<EF_STORE, true, true>(p, at, acc, ci, cx, cc)
+                            : epilogue_body<EF_STORE, true, false>(p, at, acc, ci, cx, cc); break;
+            case EF_STORE_T: part = masked ? epilogue_body<EF_STORE_T, false, true>(p, at, acc, ci, cx, cc)
+                            : epilogue_body<EF_STORE_T, false, false>(p, at, acc, ci, cx, cc); break;
+            case EF_DOT | 256: part = masked ? epilogue_body<EF_DOT, true, true>(p, at, acc, ci, cx, cc)
+                            : epilogue_body<EF_DOT, true, false>(p, at, acc, ci, cx, cc); break;
             case EF_STORE | EF_STORE_T | EF_NORM:
-                part = masked ? epilogue_body<EF_STORE | EF_STORE_T | EF_NORM, false, true>(p, tm, tn, acc, ci, cx, cc, lane, wave)
-                            : epilogue_body<EF_STORE | EF_STORE_T | EF_NORM, false, false>(p, tm, tn, acc, ci, cx, cc, lane, wave);
+                part = masked ? epilogue_body<EF_STORE | EF_STORE_T | EF_NORM, false, true>(p, at, acc, ci, cx, cc)
+                            : epilogue_body<EF_STORE | EF_STORE_T | EF_NORM, false, false>(p, at, acc, ci, cx, cc);
                 break;
             case EF_STORE_T | EF_READX:
-                part = masked ? epilogue_body<EF_STORE_T | EF_READX, false, true>(p, tm, tn, acc, ci, cx, cc, lane, wave)
-                            : epilogue_body<EF_STORE_T | EF_READX, false, false>(p, tm, tn, acc, ci, cx, cc, lane, wave);
+                part = masked ? epilogue_body<EF_STORE_T | EF_READX, false, true>(p, at, acc, ci, cx, cc)
+                            : epilogue_body<EF_STORE_T | EF_READX, false, false>(p, at, acc, ci, cx, cc);
                 break;
             case EF_STORE | EF_READX:
-                part = masked ? epilogue_body<EF_STORE | EF_READX, false, true>(p, tm, tn, acc, ci, cx, cc, lane, wave)
-                            : epilogue_body<EF_STORE | EF_READX, false, false>(p, tm, tn, acc, ci, cx, cc, lane, wave);
+                part = masked ? epilogue_body<EF_STORE | EF_READX, false, true>(p, at, acc, ci, cx, cc)
+                            : epilogue_body<EF_STORE | EF_READX, false, false>(p, at, acc, ci, cx, cc);
                 break;
             case EF_STORE | EF_STORE_T:
-                part = masked ? epilogue_body<EF_STORE | EF_STORE_T, false, true>(p, tm, tn, acc, ci, cx, cc, lane, wave)
-                              : epilogue_body<EF_STORE | EF_STORE_T, false, false>(p, tm, tn, acc, ci, cx, cc, lane, wave);
+                part = masked ? epilogue_body<EF_STORE | EF_STORE_T, false, true>(p, at, acc, ci, cx, cc)
+                              : epilogue_body<EF_STORE | EF_STORE_T, false, false>(p, at, acc, ci, cx, cc);
                 break;
             case EF_STORE | EF_STORE_T | EF_READX:
-                part = masked ? epilogue_body<EF_STORE | EF_STORE_T | EF_READX, false, true>(p, tm, tn, acc, ci, cx, cc, lane, wave)
-                              : epilogue_body<EF_STORE | EF_STORE_T | EF_READX, false, false>(p, tm, tn, acc, ci, cx,
-                                                                                              cc, lane, wave);
+                part = masked ? epilogue_body<EF_STORE | EF_STORE_T | EF_READX, false, true>(p, at, acc, ci, cx, cc)
+                              : epilogue_body<EF_STORE | EF_STORE_T | EF_READX, false, false>(p, at, acc, ci, cx, cc);
                 break;
             case EF_STORE | EF_READX | 256:
-                part = masked ? epilogue_body<EF_STORE | EF_READX, true, true>(p, tm, tn, acc, ci, cx, cc, lane, wave)
-                            : epilogue_body<EF_STORE | EF_READX, true, false>(p, tm, tn, acc, ci, cx, cc, lane, wave);
+                part = masked ? epilogue_body<EF_STORE | EF_READX, true, true>(p, at, acc, ci, cx, cc)
+                            : epilogue_body<EF_STORE | EF_READX, true, false>(p, at, acc, ci, cx, cc);
                 break;
             default:  // any other combination: every flag tested at run time
-                part = epilogue_generic(p, tm, tn, acc, ci, cx, cc, lane, wave);
+                part = epilogue_generic(p, at, acc, ci, cx, cc);
                 break;
         }
     }
-    if (flags & (EF_NORM | EF_DOT | EF_MOMENTUM)) {
+    return part;
+}
+
+// The same for quadrant `wave` of tile (tm, tn), whose partial sum goes to
+// sub-slot `wave` of the tile's slot.
+__device__ __forceinline__ void gemm_epilogue(const GemmProblem& p, int tm, int tn, int slot, float beta1,
+                                              const f32x4 (&acc)[16], int lane, int wave) {
+    const double part = gemm_epilogue_part(p, place_of(tm, tn, lane, wave), (tm + 1) * kTile, (tn + 1) * kTile, beta1, acc);
+    if (p.flags & (EF_NORM | EF_DOT | EF_MOMENTUM)) {
         const double total = wave_sum(part);
         if (lane == 0) p.partials[(size_t)slot * kWaveSlots + wave] = total;
     }
@@ -702,9 +712,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmProblem& p, int tm, int 
 // 521 -> 505 us per step, between updates 150 -> 139. (Also for products up to 128
 // wide, whose tiles' four waves would share their operands through LDS, it is
 // slower: 505 -> 536.)
-template <bool UPPER, int BI, int BJ>
+template <bool UPPER, int BI, int BJ, int LDB = 4>
 __device__ __forceinline__ void direct_loop(const GemmProblem& p, int row0, int col0, int kb, int ke, int lane,
-                                            f32x4 (&acc)[16]) {
+                                            f32x4 (&acc)[4 * LDB]) {
     constexpr int kA[6] = {2, 1, 0, 1, 0, 0}, kB[6] = {0, 1, 2, 0, 1, 0};
     const int r = lane & 15, c = lane >> 4;
     unsigned oa[BI], ob[BJ];
@@ -741,8 +751,8 @@ __device__ __forceinline__ void direct_loop(const GemmProblem& p, int row0, int 
 #pragma unroll
                 for (int j = 0; j < BJ; ++j)
                     if (!UPPER || i <= j)
-                        acc[i * 4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i].t[kA[u]], b[j].t[kB[u]],
-                                                                                 acc[i * 4 + j], 0, 0, 0);
+                        acc[i * LDB + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i].t[kA[u]], b[j].t[kB[u]],
+                                                                                 acc[i * LDB + j], 0, 0, 0);
     }
 }
 
@@ -809,6 +819,50 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_grouped(const GemmProble
         store_partial(ws + (size_t)td.part * kSplitBlock, acc);
     else
         gemm_epilogue(p, td.tm, td.tn, td.slot, beta1, acc, threadIdx.x & 63, threadIdx.x >> 6);
+}
+
+// Wave-split launch, for a level with too few tiles to fill the GPU: one
+// workgroup of eight waves per 32 x 32 block (blocks bm, bn of SmallUnit in units
+// of 32; slot: the block's place in the problem's partial sums). Each wave takes an
+// eighth of K straight from global memory (direct_loop); the eight partial
+// products meet in LDS, where four waves sum one 16 x 16 piece each, in K order,
+// and run the epilogue. No partial product leaves the CU and no second launch
+// gathers them. Bound by latency: first loads, a few slabs per wave, epilogue.
+constexpr int kWaveSplit = 8;
+constexpr int kWaveSplitThreads = 64 * kWaveSplit;
+__global__ __launch_bounds__(kWaveSplitThreads) void gemm_wave_split(const GemmProblem* __restrict__ probs,
+                                                                     const SmallUnit* __restrict__ blocks,
+                                                                     float beta1) {
+    __shared__ f32x4 sum[kWaveSplit][4][64];
+    __shared__ double red[4];
+    const SmallUnit u = blocks[blockIdx.x];
+    const GemmProblem p = probs[u.prob];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row0 = u.bm * 32, col0 = u.bn * 32, ns = p.K / kSlab;
+    f32x4 acc[8];  // 2 x 2 blocks, row stride 2 (the last four unused)
+#pragma unroll
+    for (int b = 0; b < 8; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int kb = wave * ns / kWaveSplit * kSlab, ke = (wave + 1) * ns / kWaveSplit * kSlab;
+    if (kb < ke) direct_loop<false, 2, 2, 2>(p, row0, col0, kb, ke, lane, acc);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) sum[wave][b][lane] = acc[b];
+    __syncthreads();
+    double part = 0.0;
+    if (wave < 4) {
+        f32x4 v[1] = {sum[0][wave][lane]};
+#pragma unroll
+        for (int w = 1; w < kWaveSplit; ++w)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[0][e] += sum[w][wave][lane][e];
+        const Place at = {row0 + (wave >> 1) * 16 + (lane >> 4) * 4, col0 + (wave & 1) * 16 + (lane & 15), u.bm == u.bn};
+        part = gemm_epilogue_part(p, at, row0 + 32, col0 + 32, beta1, v);
+    }
+    if (p.flags & (EF_NORM | EF_DOT | EF_MOMENTUM)) {
+        part = wave_sum(part);
+        if (wave < 4 && lane == 0) red[wave] = part;
+        __syncthreads();
+        if (threadIdx.x == 0) p.partials[u.slot] = (red[0] + red[1]) + (red[2] + red[3]);
+    }
 }
 
 // Split tiles of a grouped launch: sums the partial products in K order

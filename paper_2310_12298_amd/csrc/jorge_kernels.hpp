@@ -178,7 +178,7 @@ __device__ __forceinline__ FactorScalars factor_scalars(double nu, double beta2,
 __global__ void factor_finalize_kernel(const FactorDev* __restrict__ f, const int* __restrict__ list,
                                        double beta2, int mode) {
     const FactorDev F = f[list[blockIdx.x]];
-    const double nu = sqrt(fmax(0.0, wave_sum_array(F.partials, F.nparts * kWaveSlots)));
+    const double nu = sqrt(fmax(0.0, wave_sum_array(F.partials, F.nparts)));
     if (threadIdx.x == 0) *F.sc = factor_scalars(nu, beta2, mode);
 }
 
@@ -747,7 +747,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_apply128_kernel(const Lay
 __global__ void layer_finalize_kernel(const LayerDev* __restrict__ layers, double lr, double wd,
                                       int graft) {
     const LayerDev L = layers[blockIdx.x];
-    const double nm = sqrt(wave_sum_array(L.part_m, L.n_part_m * kWaveSlots));
+    const double nm = sqrt(wave_sum_array(L.part_m, L.n_part_m));
     const double ns = sqrt(wave_sum_array(L.part_sgd, L.n_part_sgd));
     if (threadIdx.x != 0) return;
     *L.ls = layer_scalars(nm, ns, lr, wd, graft, L.nonfinite);

@@ -70,7 +70,8 @@ struct GemmProblem {
     const float* X;            // EF_READX / EF_DOT operand
     const FactorScalars* sc;   // coefficients (any Coef but CO_ONE)
     float* mom;                // EF_MOMENTUM: dense valid_m x valid_n momentum
-    double* partials;          // EF_NORM, EF_DOT, EF_MOMENTUM: kWaveSlots doubles per tile slot
+    double* partials;          // EF_NORM, EF_DOT, EF_MOMENTUM: kWaveSlots doubles per tile slot, or in a
+                               // wave-split launch one per 32 x 32 block
     int M, N, K, K1;
     int lda, ldb, lda2, ldb2;
     int ldc, ldc2, ldx, ldmom;
@@ -133,14 +134,16 @@ struct FixupDesc {
 constexpr int kSplitBlock = 128 * 128;
 // Partial sums of a GEMM tile's epilogue (norms, dot products): one double
 // per 64 x 64 quadrant, each written by the wave that owns it; consumers sum
-// all kWaveSlots * (tile slots) of them in index order.
+// all of them in index order. A wave-split launch writes one per 32 x 32 block
+// instead, kBlockSlots per tile at most.
 constexpr int kWaveSlots = 4;
+constexpr int kBlockSlots = 16;
 
 // Device view of a factor (L_hat or R_hat of one layer).
 struct FactorDev {
     float* A;              // state, dp x dp, ld = dp, zero outside the d x d block
     FactorScalars* sc;
-    double* partials;      // partial sums of ||X||_F^2: kWaveSlots per tile slot
+    double* partials;      // partial sums of ||X||_F^2, nparts of them
     float* Z;              // explicit form: the unsymmetrized product s A P (dp x dp)
     const float* H;        // the statistic's factor, row-major d x k (ld kp, zero padded)
     int d, dp;
@@ -156,7 +159,7 @@ struct LayerDev {
     float* T;              // L_hat G, mp x np
     float* mom;            // m_t, dense m x n
     float* msgd;           // m_SGD, dense m x n
-    double* part_m;        // sums of m_ij^2: kWaveSlots per tile slot
+    double* part_m;        // partial sums of m_ij^2, n_part_m of them
     double* part_sgd;      // per-block sums of m_SGD,ij^2
     LayerScalars* ls;
     int* nonfinite;        // set to 1 by a step whose ||m_SGD|| is not finite; cleared by the host

@@ -3,9 +3,10 @@
 A step between updates forms L G R with two grouped products, so m after the
 first such step is (1 - beta1) L G R for any injected L and R. The gate is
 componentwise: each product of depth K may be off by gamma(K) |A| |B| with
-gamma(K) = (6 ceil(K / 32) + 4) 2^-23: six MFMAs per 32 k, each of which may move the
+gamma(K) = (6 ceil(K / 32) + 4 + 8) 2^-23: six MFMAs per 32 k, each of which may move the
 accumulated sum by 2^-23 of it (truncation included), and 2^-23 each for the
-terms left out, the stored result and the ends. A scheme that scaled whole matrices into a narrower
+terms left out, the stored result and the ends, and 8 for the partial products that a
+wave-split block sums. A scheme that scaled whole matrices into a narrower
 range would fail it on the graded gradients, whose rows and columns span 24 decades.
 """
 import numpy as np
@@ -19,7 +20,7 @@ pytestmark = pytest.mark.gpu
 
 
 def gamma(K):
-    return (6 * -(-K // 32) + 4) * 2.0 ** -23
+    return (6 * -(-K // 32) + 4 + 8) * 2.0 ** -23
 
 
 # One slab of K (32), two and three (the loop's short forms), tiles with remainders on
@@ -27,14 +28,15 @@ def gamma(K):
 @pytest.mark.parametrize("m,n", [(1, 32), (32, 33), (64, 64), (65, 96), (130, 97), (257, 129), (31, 520), (640, 1152)])
 @pytest.mark.parametrize("symmetrize", [True, False])
 @pytest.mark.parametrize("graded", [False, True])
-def test_between_updates_product_is_componentwise_fp32(m, n, symmetrize, graded):
+@pytest.mark.parametrize("split_k", [True, False])   # wave-split blocks (the larger shapes: tiles) and whole tiles
+def test_between_updates_product_is_componentwise_fp32(m, n, symmetrize, graded, split_k):
     rng = np.random.default_rng([m, n, symmetrize, graded])
     L, R, G = (rng.standard_normal(s).astype(np.float32) for s in ((m, m), (n, n), (m, n)))
     if symmetrize:
         L, R = L + L.T, R + R.T
     if graded:
         G *= (10.0 ** rng.uniform(-6, 6, (m, 1)) * 10.0 ** rng.uniform(-6, 6, (1, n))).astype(np.float32)
-    ctx = Jorge([(m, n)], precond_interval=2, symmetrize=symmetrize)
+    ctx = Jorge([(m, n)], precond_interval=2, symmetrize=symmetrize, split_k=split_k, lds_chain_max=0)
     ctx.t = 1
     dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
     ctx.set_state(0, "L", dev(L))
