@@ -181,6 +181,7 @@ struct jorge_ctx {
     std::vector<int> grouped, chain;
     int* dgrouped = nullptr;
     int* dchain = nullptr;
+    bool fused_norms = false;  // the weight update sums the layers' norms (each at most kFusedNormParts)
     int small = 0;  // 64 or 128: a small context of that size class (0: the grouped levels)
     double chain_flops = 0.0;  // algorithmic flops of a small context's update step
     float* splitws = nullptr;     // partial products of split tiles (shared by the stages, in turn)
@@ -1429,8 +1430,11 @@ void count_partials(jorge_ctx* c, std::vector<LayerDev>& ld, std::vector<FactorD
                 }
     for (FactorDev& F : fd)
         if (count.count(F.partials)) F.nparts = count[F.partials];
-    for (LayerDev& L : ld)
+    c->fused_norms = true;
+    for (LayerDev& L : ld) {
         if (count.count(L.part_m)) L.n_part_m = count[L.part_m];
+        c->fused_norms &= std::max(L.n_part_m, L.n_part_sgd) <= kFusedNormParts;
+    }
 }
 
 // Launch tables for the arena at c->arena, checked on the host.
@@ -1681,6 +1685,7 @@ jorge_status launch_step(jorge_ctx* c, float* const* params, const float* const*
     const bool update = (t - 1) % c->hp.precond_interval == 0;
     if (c->small) return launch_small(c, params, grads, update, lr, beta2, beta1, weight_decay);
     const int nbatch = (nl + kPtrBatch - 1) / kPtrBatch;
+    const StepScalars sc{lr, weight_decay, (float)beta1, (int)c->hp.graft};
     for (int b = 0; b < nbatch; ++b) {
         PtrBatch pb{};
         for (int i = b * kPtrBatch; i < std::min(nl, (b + 1) * kPtrBatch); ++i) pb.p[i - b * kPtrBatch] = grads[i];
@@ -1696,7 +1701,7 @@ jorge_status launch_step(jorge_ctx* c, float* const* params, const float* const*
     // Update steps take the preconditioning tables that reuse the update's low-rank terms.
     if ((s = launch_stage(c, update ? ST_UPRECOND_L : ST_PRECOND_L, 0.f)) != JORGE_OK) return s;
     if ((s = launch_stage(c, update ? ST_UPRECOND_R : ST_PRECOND_R, (float)beta1)) != JORGE_OK) return s;
-    {
+    if (!c->fused_norms) {
         TimedLaunch tl(c, ST_LFINAL);
         hipLaunchKernelGGL(layer_finalize_kernel, dim3(nl), dim3(64), 0, c->stream, c->dlayers, lr,
                            weight_decay, (int)c->hp.graft);
@@ -1708,8 +1713,12 @@ jorge_status launch_step(jorge_ctx* c, float* const* params, const float* const*
         for (int i = b * kPtrBatch; i < std::min(nl, (b + 1) * kPtrBatch); ++i) pb.p[i - b * kPtrBatch] = params[i];
         const int c0 = c->flat_batch_start[b], c1 = c->flat_batch_start[b + 1];
         TimedLaunch tl(c, ST_WEIGHT);
-        hipLaunchKernelGGL(weight_kernel, dim3(c1 - c0), dim3(kEwThreads), 0, c->stream, c->dlayers,
-                           c->dflat + c0, b * kPtrBatch, pb);
+        if (c->fused_norms)
+            hipLaunchKernelGGL(weight_kernel<true>, dim3(c1 - c0), dim3(kEwThreads), 0, c->stream, c->dlayers,
+                               c->dflat + c0, b * kPtrBatch, pb, sc);
+        else
+            hipLaunchKernelGGL(weight_kernel<false>, dim3(c1 - c0), dim3(kEwThreads), 0, c->stream, c->dlayers,
+                               c->dflat + c0, b * kPtrBatch, pb, sc);
         tl.finish();
         JORGE_HIP(c, hipGetLastError());
     }

@@ -712,7 +712,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmProblem& p, int tm, int 
 // 521 -> 505 us per step, between updates 150 -> 139. (Also for products up to 128
 // wide, whose tiles' four waves would share their operands through LDS, it is
 // slower: 505 -> 536.)
-template <bool UPPER, int BI, int BJ, int LDB = 4>
+template <bool UPPER, int BI, int BJ, int LDB = 4, SplitPair (*Split)(float, float) = split_pair_round>
 __device__ __forceinline__ void direct_loop(const GemmProblem& p, int row0, int col0, int kb, int ke, int lane,
                                             f32x4 (&acc)[4 * LDB]) {
     constexpr int kA[6] = {2, 1, 0, 1, 0, 0}, kB[6] = {0, 1, 2, 0, 1, 0};
@@ -736,14 +736,14 @@ __device__ __forceinline__ void direct_loop(const GemmProblem& p, int row0, int 
             for (int j = 0; j < BJ; ++j) rb[j][h] = *(global_f32x4*)(b + ob[j] + 16 * h);
         }
     };
-    load(kb);
-    for (int k = kb; k < ke; k += kSlab) {
+    // One slab: split, then `refill` (the next slab's loads), then the MFMAs.
+    auto slab = [&](auto refill) {
         SplitOct a[BI], b[BJ];
 #pragma unroll
-        for (int i = 0; i < BI; ++i) a[i] = split_oct<split_pair_round>(ra[i][0], ra[i][1]);
+        for (int i = 0; i < BI; ++i) a[i] = split_oct<Split>(ra[i][0], ra[i][1]);
 #pragma unroll
-        for (int j = 0; j < BJ; ++j) b[j] = split_oct<split_pair_round>(rb[j][0], rb[j][1]);
-        if (k + kSlab < ke) load(k + kSlab);
+        for (int j = 0; j < BJ; ++j) b[j] = split_oct<Split>(rb[j][0], rb[j][1]);
+        refill();
 #pragma unroll
         for (int i = 0; i < BI; ++i)
 #pragma unroll
@@ -752,8 +752,12 @@ __device__ __forceinline__ void direct_loop(const GemmProblem& p, int row0, int 
                 for (int j = 0; j < BJ; ++j)
                     if (!UPPER || i <= j)
                         acc[i * LDB + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i].t[kA[u]], b[j].t[kB[u]],
-                                                                                 acc[i * LDB + j], 0, 0, 0);
-    }
+                                                                                   acc[i * LDB + j], 0, 0, 0);
+    };
+    load(kb);
+    int k = kb;
+    for (; k + kSlab < ke; k += kSlab) slab([&] { load(k + kSlab); });
+    slab([] {});
 }
 
 // One small-mode block: its K loop, then the epilogue of the block's
@@ -843,7 +847,7 @@ __global__ __launch_bounds__(kWaveSplitThreads) void gemm_wave_split(const GemmP
 #pragma unroll
     for (int b = 0; b < 8; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     const int kb = wave * ns / kWaveSplit * kSlab, ke = (wave + 1) * ns / kWaveSplit * kSlab;
-    if (kb < ke) direct_loop<false, 2, 2, 2>(p, row0, col0, kb, ke, lane, acc);
+    if (kb < ke) direct_loop<false, 2, 2, 2, split_pair_trunc>(p, row0, col0, kb, ke, lane, acc);
 #pragma unroll
     for (int b = 0; b < 4; ++b) sum[wave][b][lane] = acc[b];
     __syncthreads();
