@@ -409,20 +409,6 @@ __device__ __forceinline__ void store_partial(float* __restrict__ blk, const f32
     for (int b = 0; b < 16; ++b) *reinterpret_cast<f32x4*>(blk + b * 1024 + 4 * threadIdx.x) = acc[b];
 }
 
-// The 64 values of one partial product that thread t of the computing workgroup kept.
-__device__ __forceinline__ void load_partial(const float* __restrict__ blk, int t, f32x4 (&v)[16]) {
-#pragma unroll
-    for (int b = 0; b < 16; ++b) v[b] = *(global_f32x4*)(blk + b * 1024 + 4 * t);
-}
-
-__device__ __forceinline__ void add_partial(const f32x4 (&v)[16], f32x4 (&acc)[16]) {
-#pragma unroll
-    for (int b = 0; b < 16; ++b) {
-        acc[b][0] += v[b][0]; acc[b][1] += v[b][1];
-        acc[b][2] += v[b][2]; acc[b][3] += v[b][3];
-    }
-}
-
 typedef __attribute__((address_space(1))) float gfloat;
 typedef __attribute__((address_space(1))) f32x4 gfloat4;
 typedef __attribute__((address_space(1))) char gchar;
@@ -871,37 +857,55 @@ __global__ __launch_bounds__(kWaveSplitThreads) void gemm_wave_split(const GemmP
 
 // Split tiles of a grouped launch: sums the partial products in K order
 // (a fixed order, so results are deterministic) and runs the epilogue. One
-// single-wave workgroup per 64 x 64 quadrant of each split tile (workgroup b:
-// tile b / 4, quadrant b % 4), so a tile's pieces are read by four
-// workgroups in parallel; each takes the accumulators that wave b % 4 of the
-// computing workgroups kept.
-constexpr int kFixupThreads = 64;
+// workgroup per 64 x 64 quadrant of each split tile (workgroup b: tile b / 4,
+// quadrant b % 4), whose wave w takes the w-th row of four 16 x 16 blocks of the
+// quadrant, as wave b % 4 of the computing workgroups kept them. Bound by the
+// latency of the pieces and of what the epilogue reads: four waves with four blocks
+// each in place of one with sixteen, 512 x 4608's step (seven fixups) 910 -> 901 us.
+constexpr int kFixupThreads = 256;
 __global__ __launch_bounds__(kFixupThreads) void gemm_fixup(const GemmProblem* __restrict__ probs,
                                                             const FixupDesc* __restrict__ fix, float beta1,
                                                             const float* __restrict__ ws) {
+    __shared__ double red[4];
     const FixupDesc fd = fix[blockIdx.x / kWaveSlots];
-    const int wave = blockIdx.x % kWaveSlots, lane = threadIdx.x;
-    const int t = wave * 64 + lane;  // thread of the computing workgroup
+    const int quadrant = blockIdx.x % kWaveSlots, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const GemmProblem p = probs[fd.prob];
-    f32x4 acc[16];
+    // The pieces' first block of this wave, at thread 64 quadrant + lane of the computing workgroup.
+    const float* src = ws + (size_t)fd.part0 * kSplitBlock + wave * 4 * 1024 + 4 * (quadrant * 64 + lane);
+    auto load = [&](int s, f32x4 (&v)[4]) {
 #pragma unroll
-    for (int b = 0; b < 16; ++b)
+        for (int j = 0; j < 4; ++j) v[j] = gload4(src + (size_t)s * kSplitBlock + j * 1024);
+    };
+    f32x4 acc[4], v0[4], v1[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
-    // Partials are added in K order; the loads of the next one are in flight
-    // while the current one is added (nsplit >= 2).
-    const float* blk = ws + (size_t)fd.part0 * kSplitBlock;
-    f32x4 v0[16], v1[16];
-    load_partial(blk, t, v0);
+    for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto add = [&](const f32x4 (&v)[4]) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[j][e] += v[j][e];
+    };
+    // The loads of the next piece are in flight while the current one is added (nsplit >= 2).
+    load(0, v0);
     int s = 0;
     for (; s + 2 <= fd.nsplit; s += 2) {
-        load_partial(blk + (size_t)(s + 1) * kSplitBlock, t, v1);
-        add_partial(v0, acc);
-        if (s + 2 < fd.nsplit) load_partial(blk + (size_t)(s + 2) * kSplitBlock, t, v0);
-        add_partial(v1, acc);
+        load(s + 1, v1);
+        add(v0);
+        if (s + 2 < fd.nsplit) load(s + 2, v0);
+        add(v1);
     }
-    if (s < fd.nsplit) add_partial(v0, acc);
-    gemm_epilogue(p, fd.tm, fd.tn, fd.slot, beta1, acc, lane, wave);
+    if (s < fd.nsplit) add(v0);
+    Place at = place_of(fd.tm, fd.tn, lane, quadrant);
+    at.row += 16 * wave;
+    double part = gemm_epilogue_part(p, at, (fd.tm + 1) * kTile, (fd.tn + 1) * kTile, beta1, acc);
+    if (p.flags & (EF_NORM | EF_DOT | EF_MOMENTUM)) {
+        part = wave_sum(part);
+        if (lane == 0) red[wave] = part;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            p.partials[(size_t)fd.slot * kWaveSlots + quadrant] = (red[0] + red[1]) + (red[2] + red[3]);
+    }
 }
 
 }  // namespace jorge
