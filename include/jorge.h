@@ -121,17 +121,18 @@ typedef struct jorge_hparams {
     int32_t split_k;          /* 1: a GEMM level splits some of its tiles along K where the
                                  library's cost model of the launch says it then finishes
                                  sooner: a level with too few tiles for the GPU, or one whose
-                                 last round of tiles would leave most workgroups idle
+                                 last round of tiles would leave most workgroups idle; a level
+                                 with little work splits K over the waves of a workgroup instead
                                  (partial products summed in a fixed order: deterministic,
                                  but rounded differently from an unsplit tile, and the split
                                  plan depends on every layer of the context); 0: never.
                                  Default 1. */
-    int32_t lds_chain_max;    /* when every factor's size rounded up to 32 is at most this, each
-                                 factor update runs in the explicit order in one workgroup with
-                                 its matrices in LDS (one launch for the factors up to 64, one
-                                 for those of 96 and 128, which need symmetrize = 1) instead of
-                                 the grouped levels. With any larger factor present the levels
-                                 run anyway and take the small factors too. 0 disables.
+    int32_t lds_chain_max;    /* when every factor's size rounded up to 32 is at most this, the
+                                 whole step runs with its matrices in LDS, the factor updates in
+                                 the explicit order, instead of the grouped levels: one launch
+                                 per 256 layers when all are at most 64, two when some are 96 or
+                                 128, which needs symmetrize = 1. With any larger factor present
+                                 the levels run and take the small factors too. 0 disables.
                                  In [0, 128]. Default 128. */
     int32_t precond_lowrank;  /* 1: on update steps, a factored factor A with d > 3k preconditions
                                  through A_new H = s A H - (s/2)(W H^T H + H W^T H), built from
@@ -226,7 +227,8 @@ jorge_status jorge_step(jorge_ctx* ctx, float* const* params, const float* const
  * The call returns after the stream has executed the step (the scratch is
  * reused by the next call). Calls on one GPU share its scratch: the library
  * runs them one at a time (a lock per GPU), and each starts by clearing what
- * must start at zero. Errors: JORGE_ERR_INVALID_ARGUMENT as for jorge_step;
+ * must start at zero. The launch plans of the last 16 kinds of layer (shape and
+ * options) are kept per GPU, in host memory. Errors: JORGE_ERR_INVALID_ARGUMENT as for jorge_step;
  * JORGE_ERR_UNSUPPORTED if the layer's workspace and launch tables need more
  * than JORGE_NOALLOC_SCRATCH_BYTES (a 512 x 1024 layer fits with split_k = 1,
  * a 1024 x 1024 one with split_k = 0); JORGE_ERR_HIP on a runtime error, in

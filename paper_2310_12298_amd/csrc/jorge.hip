@@ -181,6 +181,7 @@ struct jorge_ctx {
     std::vector<int> grouped, chain;
     int* dgrouped = nullptr;
     int* dchain = nullptr;
+    size_t block_slot_bytes = 0;  // arena bytes of partial sums beyond kWaveSlots per tile
     bool fused_norms = false;  // the weight update sums the layers' norms (each at most kFusedNormParts)
     int small = 0;  // 64 or 128: a small context of that size class (0: the grouped levels)
     double chain_flops = 0.0;  // algorithmic flops of a small context's update step
@@ -215,7 +216,10 @@ struct jorge_ctx {
 // the library runs on holds its own copy from module load to process end. In
 // host code this name is only a stand-in for the symbol: kernels and copies
 // take the per-device address that hipGetSymbolAddress returns.
-static __device__ __align__(256) unsigned char scratch[JORGE_NOALLOC_SCRATCH_BYTES];
+// kScratchExtra holds what wave-split levels add to a layer's needs (their block
+// lists and one partial sum per block), which the documented limit does not count.
+static constexpr size_t kScratchExtra = 1 << 20;
+static __device__ __align__(256) unsigned char scratch[JORGE_NOALLOC_SCRATCH_BYTES + kScratchExtra];
 
 namespace {
 
@@ -640,6 +644,12 @@ void split_stage(GemmStage& st) {
     st.tiles.swap(out);
 }
 
+// Work of one product in 32 x 32 x 32 products.
+int64_t wave_split_slabs(int64_t M, int64_t N, int64_t K, bool upper) {
+    const int64_t bm = M / 32, bn = N / 32;
+    return (upper ? bm * (bm + 1) / 2 : bm * bn) * (K / kSlab);
+}
+
 // Wave-split in place of tiles: a level with fewer tiles than CUs whose whole
 // work is short. Its 32 x 32 blocks, eight waves each, spread it over more CUs than
 // the tiles would and need no second launch; past kWaveSplitWork the tiles' four
@@ -650,10 +660,7 @@ void split_stage(GemmStage& st) {
 bool wave_split_pays(const GemmStage& st) {
     if (!st.kmajor_b || st.tiles.empty() || !st.small.empty() || st.tiles.size() >= (size_t)kCus) return false;
     int64_t slabs = 0;
-    for (const GemmProblem& p : st.probs) {
-        const int64_t bm = p.M / 32, bn = p.N / 32;
-        slabs += (p.upper ? bm * (bm + 1) / 2 : bm * bn) * (p.K / kSlab);
-    }
+    for (const GemmProblem& p : st.probs) slabs += wave_split_slabs(p.M, p.N, p.K, p.upper);
     return slabs <= kWaveSplitWork;
 }
 
@@ -754,6 +761,13 @@ size_t plan(jorge_ctx* c) {
         return o;
     };
     const bool sym = c->hp.symmetrize != 0;
+    // Partial sums of a product of `tiles` tiles: room for one per 32 x 32 block
+    // where its level could be wave-split.
+    auto part_bytes = [&](int tiles, int64_t M, int64_t N, int64_t K, bool upper) {
+        const bool blocks = c->hp.split_k && wave_split_slabs(M, N, K, upper) <= kWaveSplitWork;
+        if (blocks) c->block_slot_bytes += (size_t)tiles * (kBlockSlots - kWaveSlots) * sizeof(double);
+        return (size_t)tiles * (blocks ? kBlockSlots : kWaveSlots) * sizeof(double);
+    };
     // The small-context kernels take the step when every factor of the context
     // has padded size up to lds_chain_max (sizes 96 and 128 need symmetric
     // factors). With any larger factor present the levels run anyway, and the
@@ -810,7 +824,8 @@ size_t plan(jorge_ctx* c) {
                 F.off_v2t = take(kk);  // H^T W, k x k
                 F.off_xa = take(kd);   // A_new H, d x k
             }
-            F.off_part = take((size_t)F.nparts * kBlockSlots * sizeof(double));
+            // ||X||'s product: dp x dp over dp, or the upper kp x kp over dp.
+            F.off_part = take(part_bytes(F.nparts, F.expl ? F.dp : F.kp, F.expl ? F.dp : F.kp, F.dp, !F.expl));
             F.off_sc = take(sizeof(FactorScalars));
             (side == 0 ? L.fL : L.fR) = (int)c->factors.size();
             c->factors.push_back(F);
@@ -827,7 +842,7 @@ size_t plan(jorge_ctx* c) {
         L.off_mom = take(dense);
         L.off_msgd = take(dense);
         L.n_part_m = tile_count(L.mp, L.np);
-        L.off_part_m = take((size_t)L.n_part_m * kBlockSlots * sizeof(double));
+        L.off_part_m = take(part_bytes(L.n_part_m, L.mp, L.np, std::min(L.mp, L.np), false));
         L.n_part_sgd = ((L.m + 63) / 64) * ((L.n + 63) / 64);
         L.off_part_sgd = take((size_t)L.n_part_sgd * sizeof(double));
         L.off_ls = take(sizeof(LayerScalars));
@@ -1035,14 +1050,11 @@ void build_tables(jorge_ctx* c, std::vector<LayerDev>& ld, std::vector<FactorDev
         d.sc = at<FactorScalars>(c, F.off_sc);
         d.partials = at<double>(c, F.off_part);
         d.Z = (F.expl && !F.chain) ? at<float>(c, F.off_w[1]) : nullptr;
-        const auto& L = c->layers[F.layer];
-        d.H = c->small ? nullptr : at<float>(c, F.side == 0 ? L.off_Gp : L.off_Gpt);
         d.d = F.d;
         d.dp = F.dp;
         d.k = F.k;
         d.kp = F.kp;
         d.nparts = F.nparts;
-        d.explicit_form = F.expl ? 1 : 0;
         fd.push_back(d);
     }
     for (int li = 0; li < nl; ++li) {
@@ -1640,9 +1652,6 @@ jorge_status launch_small(jorge_ctx* c, float* const* params, const float* const
                           double beta2, double beta1, double weight_decay) {
     const int nl = (int)c->layers.size();
     const StepScalars sc{lr, weight_decay, (float)beta1, (int)c->hp.graft};
-    for (int i = 0; i < nl; ++i)
-        if ((reinterpret_cast<uint64_t>(params[i]) | reinterpret_cast<uint64_t>(grads[i])) >> 48)
-            return fail(c, JORGE_ERR_UNSUPPORTED, "a tensor's address has more than 48 bits");
     for (int l0 = 0; l0 < nl; l0 += kPtrBatch) {
         const int n = std::min(kPtrBatch, nl - l0);
         PtrPack pp{};
@@ -1767,10 +1776,13 @@ jorge_status build_noalloc(const jorge_shape& shape, const jorge_hparams& h, cha
     const size_t arena = (size_t)round_up((int64_t)c->arena_bytes, kAlign);
     const size_t split = (size_t)round_up(c->splitws_blocks * kSplitBlock * (int64_t)sizeof(float), kAlign);
     const size_t need = arena + split + tables_bytes(c, ld, fd);
-    if (need > (size_t)JORGE_NOALLOC_SCRATCH_BYTES) return JORGE_ERR_UNSUPPORTED;
+    size_t extra = c->block_slot_bytes;
+    for (int i = 0; i < ST_COUNT; ++i) extra += table_bytes(c->nt[i].blocks);
+    const size_t limit = (size_t)JORGE_NOALLOC_SCRATCH_BYTES;
+    if (need > limit + std::min(extra, kScratchExtra)) return JORGE_ERR_UNSUPPORTED;
     c->splitws = c->splitws_blocks > 0 ? reinterpret_cast<float*>(base + arena) : nullptr;
     c->pool = base + arena + split;
-    c->pool_bytes = JORGE_NOALLOC_SCRATCH_BYTES - arena - split;
+    c->pool_bytes = limit + kScratchExtra - arena - split;
     return upload_tables(c, ld, fd);
 }
 
@@ -1896,6 +1908,10 @@ jorge_status jorge_step(jorge_ctx* c, float* const* params, const float* const* 
     const int nl = (int)c->layers.size();
     for (int i = 0; i < nl; ++i)
         if (!params[i] || !grads[i]) return fail(c, JORGE_ERR_INVALID_ARGUMENT, "jorge_step: null tensor");
+    // A small context's launches carry 48-bit addresses (PtrPack); user addresses have 47.
+    for (int i = 0; c->small && i < nl; ++i)
+        if ((reinterpret_cast<uint64_t>(params[i]) | reinterpret_cast<uint64_t>(grads[i])) >> 48)
+            return fail(c, JORGE_ERR_UNSUPPORTED, "jorge_step: a tensor's address has more than 48 bits");
     if (c->poisoned)
         return fail(c, JORGE_ERR_HIP,
                     "jorge_step: an earlier step failed part-way; restore the state (jorge_set_state) and "
@@ -1917,6 +1933,7 @@ jorge_status jorge_step_noalloc(const jorge_shape* shape, const jorge_hparams* h
     jorge_status st = validate_args(shape, 1, hp, &h);
     if (st != JORGE_OK) return st;
     if (t < 1 || !theta || !grad || !L || !R || !mom || !mom_sgd) return JORGE_ERR_INVALID_ARGUMENT;
+    if ((reinterpret_cast<uint64_t>(theta) | reinterpret_cast<uint64_t>(grad)) >> 48) return JORGE_ERR_UNSUPPORTED;
     if (!(std::isfinite(lr) && lr >= 0.0) || !(beta2 > 0.0 && beta2 < 1.0) || !(beta1 >= 0.0 && beta1 < 1.0) ||
         !(std::isfinite(weight_decay) && weight_decay >= 0.0))
         return JORGE_ERR_INVALID_ARGUMENT;

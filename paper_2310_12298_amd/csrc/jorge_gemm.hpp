@@ -8,12 +8,11 @@
 // four waves each own a 64 x 64 sub-tile held as 4 x 4 blocks of 16 x 16
 // accumulators. Operands and results are fp32.
 //
-// NT products (both operands K-contiguous: every product of the symmetric
-// mode) run on the bf16 matrix pipe without giving up fp32: each operand
-// element is split into three bf16 terms that sum to it exactly (24 bits),
-// and the six term products down to 2^-16 of the whole are accumulated in
-// fp32 (see split_pair below). NN products (the literal mode's powers) use the
-// fp32 MFMA with a K-contiguous A and an MN-contiguous B.
+// Products run on the bf16 matrix pipe without giving up fp32: each operand
+// element is split into three bf16 terms that sum to it exactly (24 bits), and
+// the six term products down to 2^-16 of the whole are accumulated in fp32 (see
+// split_pair below). A is K-contiguous; B is K-contiguous (NT: every product of
+// the symmetric mode) or MN-contiguous (NN: the literal mode's powers).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -23,11 +22,10 @@
 namespace jorge {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // Accumulator layout. A wave's 64 x 64 quadrant (wy, wx) of its tile is a
 // 4 x 4 grid of 16 x 16 blocks; block b = 4 i + j (rows 16 i, columns 16 j of
-// the quadrant) is one v_mfma_f32_16x16x4_f32 accumulator, in which lane l
+// the quadrant) is one v_mfma_f32_16x16x32_bf16 accumulator, in which lane l
 // holds column l % 16, rows 4 (l / 16) .. 4 (l / 16) + 3. Each lane thus
 // holds, for each of its 16 blocks, four consecutive rows of one column.
 // Where a lane's accumulators lie in the result: the first of block b's four
@@ -58,21 +56,20 @@ constexpr int kSlabBytes = 3 * kPlaneBytes;
 // to global_load rather than flat_load, which would also count against the
 // LDS wait counter and make every LDS wait drain the in-flight prefetch.
 typedef __attribute__((address_space(1))) const f32x4 global_f32x4;
-typedef __attribute__((address_space(1))) const float global_f32;
 
 __device__ __forceinline__ f32x4 gload4(const float* p) {
     return *(global_f32x4*)p;
 }
 
 // ---------------------------------------------------------------- three-term split
-// x = x0 + x1 + x2 with x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1):
-// both differences are exact in fp32 and 3 x 8 significant bits hold all 24 of
-// x, over the whole fp32 exponent range (down to 2^-110, below which x2 and then
-// x1 underflow). A product a b is summed as a2 b0 + a1 b1 + a0 b2 + a1 b0 + a0 b1
+// x = x0 + x1 + x2 by truncation: x0 is the upper half of x, x1 that of x - x0, x2
+// what is left. Both differences are exact in fp32 and 3 x 8 significant bits hold
+// all 24 of x, over the whole fp32 exponent range (down to 2^-110, below which x2
+// and then x1 underflow). A product a b is summed as a2 b0 + a1 b1 + a0 b2 + a1 b0 + a0 b1
 // + a0 b0, every term exact and accumulated in fp32; the three left out are below
 // 2^-23 |a b| together, and a K-long sum takes 6 K / 32 roundings of the
 // accumulator where the fp32 MFMA takes K / 4. Measured against fp64 on Gaussian
-// operands (relative 2-norm): 3.4e-7 at K = 512 and 1.0e-6 at K = 4096, where the
+// operands (relative 2-norm): 3.4e-7 at K = 512 and 1.04e-6 at K = 4096, where the
 // fp32 MFMA has 4.0e-7 and 1.1e-6.
 // The bf16 MFMA does 16 times the fp32 one's flops per cycle, so six of them are
 // 2.7 times as fast at the same clock; under the power limit 4096^3 runs at
@@ -86,37 +83,12 @@ struct SplitPair {
     bf16x2 t[kTerms];
 };
 
-// Seven instructions for two elements: a difference x - x0 is one bf16 dot
-// product, x + (x0 of the pair) . (-1, 0), with no unpacking of x0. (The
-// other element of the pair enters times zero: an infinity there makes this
-// element's x1 NaN, in a row whose every output is non-finite anyway.)
+// Eleven instructions of the plain VALU for two elements. Rounding conversions
+// and dot products (v_cvt_pk_bf16_f32, v_dot2c_f32_bf16) make it in seven, but
+// those run at half rate and hold up the MFMAs, while these take two waves'
+// instructions at once and run beside the MFMAs: cycles for 24 pairs and 48 MFMAs
+// of each of two waves per SIMD, 2528 this way and 4012 that way (MFMAs alone 1564).
 __device__ __forceinline__ SplitPair split_pair(float a, float b) {
-    // In registers, not inline constants: the packed encoding of an inline -1.0 is not (-1, 0).
-    unsigned c10, c01;
-    asm("s_mov_b32 %0, 0xbf80" : "=s"(c10));
-    asm("s_mov_b32 %0, 0xbf800000" : "=s"(c01));
-    const bf16x2 first = __builtin_bit_cast(bf16x2, c10), second = __builtin_bit_cast(bf16x2, c01);
-    SplitPair o;
-    o.t[0] = __builtin_convertvector((f32x2{a, b}), bf16x2);
-    const float ra = __builtin_amdgcn_fdot2_f32_bf16(o.t[0], first, a, false);
-    const float rb = __builtin_amdgcn_fdot2_f32_bf16(o.t[0], second, b, false);
-    o.t[1] = __builtin_convertvector((f32x2{ra, rb}), bf16x2);
-    const float qa = __builtin_amdgcn_fdot2_f32_bf16(o.t[1], first, ra, false);
-    const float qb = __builtin_amdgcn_fdot2_f32_bf16(o.t[1], second, rb, false);
-    o.t[2] = __builtin_convertvector((f32x2{qa, qb}), bf16x2);
-    return o;
-}
-
-// The three-term split by truncation: x0 and x1 are the upper halves of x and of
-// the exact difference x - x0, x2 the upper half of what is left (8 bits, so
-// exact). Eleven instructions for two elements against split_pair's seven, but
-// all of the plain VALU, which takes two waves' instructions at once and runs
-// beside the MFMAs; the conversions and dot products of split_pair hold up both.
-// Measured with two waves per SIMD, cycles for 24 pairs and 48 MFMAs of each:
-// 2528 by truncation, 4012 with split_pair (MFMAs alone 1564). The staged GEMM
-// splits each element a quarter as often per MFMA, in a clump before them, and is
-// slower with it (ResNet-50's step 5.5 -> 7.2 ms).
-__device__ __forceinline__ SplitPair split_pair_trunc(float a, float b) {
     SplitPair o;
     unsigned ua, ub;
 #pragma unroll
@@ -130,27 +102,12 @@ __device__ __forceinline__ SplitPair split_pair_trunc(float a, float b) {
     return o;
 }
 
-// The terms of split_pair, bit for bit, with the upper halves taken back by a shift
-// and a mask instead of dot products: for products whose tiles are computed now by
-// the staged path, now by direct_loop, with the same result.
-__device__ __forceinline__ SplitPair split_pair_round(float a, float b) {
-    SplitPair o;
-#pragma unroll
-    for (int t = 0; t < kTerms; ++t) {
-        o.t[t] = __builtin_convertvector((f32x2{a, b}), bf16x2);
-        const unsigned u = __builtin_bit_cast(unsigned, o.t[t]);
-        a -= __builtin_bit_cast(float, u << 16);
-        b -= __builtin_bit_cast(float, u & 0xffff0000u);
-    }
-    return o;
-}
-
 struct SplitOct {
     bf16x8 t[kTerms];
 };
-template <SplitPair (*Split)(float, float)>
 __device__ __forceinline__ SplitOct split_oct(f32x4 u, f32x4 v) {
-    const SplitPair a = Split(u[0], u[1]), b = Split(u[2], u[3]), c = Split(v[0], v[1]), d = Split(v[2], v[3]);
+    const SplitPair a = split_pair(u[0], u[1]), b = split_pair(u[2], u[3]);
+    const SplitPair c = split_pair(v[0], v[1]), d = split_pair(v[2], v[3]);
     SplitOct o;
 #pragma unroll
     for (int t = 0; t < kTerms; ++t)
@@ -317,6 +274,32 @@ __device__ __forceinline__ void mma_slab(const char* lds, const SlabLds& o, int 
     }
 }
 
+// Spreads the split's VALU instructions evenly among a slab's MFMAs, the LDS
+// reads of a block row ahead of its MFMAs and the next loads last. Left to itself
+// the compiler puts the whole split before the first MFMA (and spills): ResNet-50's
+// step 7.2 ms, against 5.2 with the seven-instruction split, which it interleaved,
+// and 4.9 with this order.
+template <int N, int VALU>
+__device__ __forceinline__ void interleave_row() {
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);     // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x2, VALU, 0);  // VALU
+        if (q == N / 3) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);  // LDS reads of the next row
+    }
+}
+template <int BS, bool LOADS>
+__device__ __forceinline__ void interleave_slab() {
+    if constexpr (BS == BS_NONE) return;
+    __builtin_amdgcn_sched_group_barrier(0x100, 15, 0);  // LDS reads
+    constexpr int V = BS == BS_ALL ? 2 : 4;
+    interleave_row<24, V>();
+    interleave_row<BS == BS_ALL ? 24 : 18, V>();
+    interleave_row<BS == BS_ALL ? 24 : 12, V>();
+    interleave_row<BS == BS_ALL ? 24 : 6, V>();
+    if constexpr (LOADS) __builtin_amdgcn_sched_group_barrier(0x20, 8, 0);  // global loads
+}
+
 // Workgroup barrier that waits for this wave's LDS accesses but leaves its
 // global loads in flight.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -338,6 +321,7 @@ __device__ __forceinline__ void slab_loop(const GemmProblem& p, const SlabOffset
         split_slab<BK>(r, s);
         load_slab<BK>(p, o, k0 + (kt + 2) * kSlab, r);
         mma_slab<BS>(lds, l, wy, wx, acc);
+        interleave_slab<BS, true>();
         __builtin_amdgcn_s_setprio(0);
         lds_barrier();
         store_slab<BK>(lds, l, s);
@@ -347,6 +331,7 @@ __device__ __forceinline__ void slab_loop(const GemmProblem& p, const SlabOffset
     if (kt + 1 < nk) {
         split_slab<BK>(r, s);
         mma_slab<BS>(lds, l, wy, wx, acc);
+        interleave_slab<BS, false>();
         __builtin_amdgcn_s_setprio(0);
         lds_barrier();
         store_slab<BK>(lds, l, s);
@@ -698,7 +683,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmProblem& p, int tm, int 
 // 521 -> 505 us per step, between updates 150 -> 139. (Also for products up to 128
 // wide, whose tiles' four waves would share their operands through LDS, it is
 // slower: 505 -> 536.)
-template <bool UPPER, int BI, int BJ, int LDB = 4, SplitPair (*Split)(float, float) = split_pair_round>
+template <bool UPPER, int BI, int BJ, int LDB = 4>
 __device__ __forceinline__ void direct_loop(const GemmProblem& p, int row0, int col0, int kb, int ke, int lane,
                                             f32x4 (&acc)[4 * LDB]) {
     constexpr int kA[6] = {2, 1, 0, 1, 0, 0}, kB[6] = {0, 1, 2, 0, 1, 0};
@@ -726,9 +711,9 @@ __device__ __forceinline__ void direct_loop(const GemmProblem& p, int row0, int 
     auto slab = [&](auto refill) {
         SplitOct a[BI], b[BJ];
 #pragma unroll
-        for (int i = 0; i < BI; ++i) a[i] = split_oct<Split>(ra[i][0], ra[i][1]);
+        for (int i = 0; i < BI; ++i) a[i] = split_oct(ra[i][0], ra[i][1]);
 #pragma unroll
-        for (int j = 0; j < BJ; ++j) b[j] = split_oct<Split>(rb[j][0], rb[j][1]);
+        for (int j = 0; j < BJ; ++j) b[j] = split_oct(rb[j][0], rb[j][1]);
         refill();
 #pragma unroll
         for (int i = 0; i < BI; ++i)
@@ -833,7 +818,7 @@ __global__ __launch_bounds__(kWaveSplitThreads) void gemm_wave_split(const GemmP
 #pragma unroll
     for (int b = 0; b < 8; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     const int kb = wave * ns / kWaveSplit * kSlab, ke = (wave + 1) * ns / kWaveSplit * kSlab;
-    if (kb < ke) direct_loop<false, 2, 2, 2, split_pair_trunc>(p, row0, col0, kb, ke, lane, acc);
+    if (kb < ke) direct_loop<false, 2, 2, 2>(p, row0, col0, kb, ke, lane, acc);
 #pragma unroll
     for (int b = 0; b < 4; ++b) sum[wave][b][lane] = acc[b];
     __syncthreads();

@@ -255,7 +255,7 @@ __global__ __launch_bounds__(kEwThreads) void symmetrize_kernel(const FactorDev*
 //
 // Every product is C = A B with both operands held in LDS as fp32 rows that
 // are contiguous in k: A's rows and B's columns (the rows of B^T). They are
-// split into bf16 terms as they are read (split_pair_trunc): a piece of 16 BI x
+// split into bf16 terms as they are read (split_pair): a piece of 16 BI x
 // 16 BJ costs BI + BJ splits per 6 BI BJ MFMAs. What bounds a team is the chain
 // of six dependent products with barriers between them.
 
@@ -315,9 +315,9 @@ __device__ __forceinline__ void piece_mma_n(const float* a, const float* b, int 
     for (int k0 = 0; k0 < K; k0 += 32) {
         SplitOct sb[BJ], sa[NBI];
 #pragma unroll
-        for (int j = 0; j < BJ; ++j) sb[j] = split_oct<split_pair_trunc>(fb[j][0], fb[j][1]);
+        for (int j = 0; j < BJ; ++j) sb[j] = split_oct(fb[j][0], fb[j][1]);
 #pragma unroll
-        for (int i = 0; i < NBI; ++i) sa[i] = split_oct<split_pair_trunc>(fa[i][0], fa[i][1]);
+        for (int i = 0; i < NBI; ++i) sa[i] = split_oct(fa[i][0], fa[i][1]);
         read(k0 + 32 < K ? k0 + 32 : 0);  // past the end: group 0 again, never multiplied
 #pragma unroll
         for (int i = 0; i < NBI; ++i)
