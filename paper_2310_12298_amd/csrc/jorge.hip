@@ -421,7 +421,9 @@ void order_for_xcds(std::vector<TileDesc>& tiles) {
 }
 
 // Cost model of a grouped launch for the split planner, in units of one k
-// step of a 128 x 128 tile on a whole compute unit (0.058 us). Workgroup b
+// step of a 128 x 128 tile on a whole compute unit (0.058 us when the constants were
+// fitted, on the fp32 MFMA; 0.04 us now, with which fixup starts of 150-300 and unit
+// costs of 48-96 plan within 0.5% of these or worse). Workgroup b
 // runs on XCD b mod kXcds, on one of that XCD's CUs. A CU holds two work
 // units at a time; two resident units share its throughput, a unit alone on
 // a CU runs at kLoneRate of it. A work unit costs its K plus its own

@@ -62,10 +62,13 @@ __device__ __forceinline__ f32x4 gload4(const float* p) {
 }
 
 // ---------------------------------------------------------------- three-term split
-// x = x0 + x1 + x2 by truncation: x0 is the upper half of x, x1 that of x - x0, x2
-// what is left. Both differences are exact in fp32 and 3 x 8 significant bits hold
-// all 24 of x, over the whole fp32 exponent range (down to 2^-110, below which x2
-// and then x1 underflow). A product a b is summed as a2 b0 + a1 b1 + a0 b2 + a1 b0 + a0 b1
+// x = x0 + x1 + x2: x0 is x rounded to its upper half, x1 the upper half of x - x0,
+// x2 what is left. Both differences are exact in fp32 and 3 x 8 significant bits
+// hold all 24 of x, over the whole fp32 exponent range (down to 2^-110, below
+// which x2 and then x1 underflow). x0 is rounded, not cut off: x1 and x2 then have
+// either sign, and the terms left out of a sum cancel where cut-off ones would all
+// have the product's sign (a bias of 2^-24 per product, which ResNet-50's and the
+// 4096-wide layers' powers added up to 2.1e-6 and 1.4e-6 of a factor). A product a b is summed as a2 b0 + a1 b1 + a0 b2 + a1 b0 + a0 b1
 // + a0 b0, every term exact and accumulated in fp32; the three left out are below
 // 2^-23 |a b| together, and a K-long sum takes 6 K / 32 roundings of the
 // accumulator where the fp32 MFMA takes K / 4. Measured against fp64 on Gaussian
@@ -83,18 +86,19 @@ struct SplitPair {
     bf16x2 t[kTerms];
 };
 
-// Eleven instructions of the plain VALU for two elements. Rounding conversions
+// Thirteen instructions of the plain VALU for two elements. Rounding conversions
 // and dot products (v_cvt_pk_bf16_f32, v_dot2c_f32_bf16) make it in seven, but
 // those run at half rate and hold up the MFMAs, while these take two waves'
 // instructions at once and run beside the MFMAs: cycles for 24 pairs and 48 MFMAs
-// of each of two waves per SIMD, 2528 this way and 4012 that way (MFMAs alone 1564).
+// of each of two waves per SIMD, 2528 this way (without the rounding) and 4012 that
+// way (MFMAs alone 1564).
 __device__ __forceinline__ SplitPair split_pair(float a, float b) {
     SplitPair o;
     unsigned ua, ub;
 #pragma unroll
     for (int t = 0; t < kTerms; ++t) {
-        ua = __builtin_bit_cast(unsigned, a);
-        ub = __builtin_bit_cast(unsigned, b);
+        ua = __builtin_bit_cast(unsigned, a) + (t == 0 ? 0x8000u : 0u);
+        ub = __builtin_bit_cast(unsigned, b) + (t == 0 ? 0x8000u : 0u);
         o.t[t] = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(ub, ua, 0x07060302));
         a -= __builtin_bit_cast(float, ua & 0xffff0000u);
         b -= __builtin_bit_cast(float, ub & 0xffff0000u);
@@ -292,11 +296,12 @@ template <int BS, bool LOADS>
 __device__ __forceinline__ void interleave_slab() {
     if constexpr (BS == BS_NONE) return;
     __builtin_amdgcn_sched_group_barrier(0x100, 15, 0);  // LDS reads
+    // 208 of the split and the addresses' few over 96 (60) MFMAs.
     constexpr int V = BS == BS_ALL ? 2 : 4;
     interleave_row<24, V>();
     interleave_row<BS == BS_ALL ? 24 : 18, V>();
-    interleave_row<BS == BS_ALL ? 24 : 12, V>();
-    interleave_row<BS == BS_ALL ? 24 : 6, V>();
+    interleave_row<BS == BS_ALL ? 24 : 12, BS == BS_ALL ? 3 : 4>();
+    interleave_row<BS == BS_ALL ? 24 : 6, BS == BS_ALL ? 3 : 4>();
     if constexpr (LOADS) __builtin_amdgcn_sched_group_barrier(0x20, 8, 0);  // global loads
 }
 
