@@ -65,11 +65,13 @@ __device__ __forceinline__ f32x4 gload4(const float* p) {
 // x = x0 + x1 + x2: x0 is x rounded to its upper half, x1 the upper half of x - x0,
 // x2 what is left. Both differences are exact in fp32 and 3 x 8 significant bits
 // hold all 24 of x, over the whole fp32 exponent range (down to 2^-110, below
-// which x2 and then x1 underflow). x0 is rounded, not cut off: x1 and x2 then have
-// either sign, and the terms left out of a sum cancel where cut-off ones would all
-// have the product's sign (a bias of 2^-24 per product, which ResNet-50's and the
-// 4096-wide layers' powers added up to 2.1e-6 and 1.4e-6 of a factor). A product a b is summed as a2 b0 + a1 b1 + a0 b2 + a1 b0 + a0 b1
-// + a0 b0, every term exact and accumulated in fp32; the three left out are below
+// which x2 and then x1 underflow). NaN stays NaN; an infinity, or a magnitude that
+// rounds to 2^128 (above 3.39e38), leaves no finite x - x0 and makes its products
+// NaN. x0 is rounded, not cut off: x1 and x2 then have either sign, and the terms
+// left out of a sum cancel where cut-off ones would all have the product's sign
+// (a bias of 2^-24 per product, which ResNet-50's and the 4096-wide layers' powers
+// added up to 2.1e-6 and 1.4e-6 of a factor).
+// A product a b is summed as a2 b0 + a1 b1 + a0 b2 + a1 b0 + a0 b1 + a0 b0, every term exact and accumulated in fp32; the three left out are below
 // 2^-23 |a b| together, and a K-long sum takes 6 K / 32 roundings of the
 // accumulator where the fp32 MFMA takes K / 4. Measured against fp64 on Gaussian
 // operands (relative 2-norm): 3.4e-7 at K = 512 and 1.04e-6 at K = 4096, where the
