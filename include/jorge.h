@@ -30,6 +30,14 @@
  * the scalar arithmetic they enter runs in fp64 on the device. The options
  * fixed at creation (jorge_hparams) therefore carry none of them.
  *
+ * Matrix products are products of fp32 matrices accumulated in fp32. Each is
+ * formed from bf16 terms that hold the operands exactly (three per element, six
+ * of the nine term products; what is left out is below 2^-22 of a product), or
+ * by the fp32 matrix instructions where the terms do not hold an operand: a
+ * non-zero magnitude below 2^-110 or above 3.39e38, an infinity, a NaN. Such
+ * values take their fp32 course (subnormals and infinities included); the tiles
+ * they enter take up to 2.3 times as long.
+ *
  * A context is not re-entrant: calls on one context must not overlap.
  * Distinct contexts are independent.
  */

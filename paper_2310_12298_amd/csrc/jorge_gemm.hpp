@@ -64,10 +64,10 @@ __device__ __forceinline__ f32x4 gload4(const float* p) {
 // ---------------------------------------------------------------- three-term split
 // x = x0 + x1 + x2: x0 is x rounded to its upper half, x1 the upper half of x - x0,
 // x2 what is left. Both differences are exact in fp32 and 3 x 8 significant bits
-// hold all 24 of x, over the whole fp32 exponent range (down to 2^-110, below
-// which x2 and then x1 underflow). NaN stays NaN; an infinity, or a magnitude that
-// rounds to 2^128 (above 3.39e38), leaves no finite x - x0 and makes its products
-// NaN. x0 is rounded, not cut off: x1 and x2 then have either sign, and the terms
+// hold all 24 of x from 2^-110 to 3.39e38 (split_lost tells of the rest). The
+// scheme is that of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations" (arXiv 1904.06376).
+// x0 is rounded, not cut off: x1 and x2 then have either sign, and the terms
 // left out of a sum cancel where cut-off ones would all have the product's sign
 // (a bias of 2^-24 per product, which ResNet-50's and the 4096-wide layers' powers
 // added up to 2.1e-6 and 1.4e-6 of a factor).
@@ -87,14 +87,30 @@ constexpr int kTerms = 3;
 struct SplitPair {
     bf16x2 t[kTerms];
 };
+// Elements the three terms do not hold: magnitudes below 2^-110 (x2 runs out of bf16's
+// exponents and drops bits), infinities and magnitudes that round to 2^128. A product
+// with one among its operands is formed by the fp32 MFMA instead (fp32_blocks): the
+// split collects the bits it drops (lost, in its lower half), and the other two kinds
+// leave no finite sum, as does a term product that overflows where the fp32 one does not.
+__device__ __forceinline__ bool split_lost(unsigned lost) { return (lost & 0xffffu) != 0; }
 
-// Thirteen instructions of the plain VALU for two elements. Rounding conversions
+template <int N>
+__device__ __forceinline__ bool any_non_finite(const f32x4 (&acc)[N]) {
+    float z = 0.0f;
+#pragma unroll
+    for (int b = 0; b < N; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z += 0.0f * acc[b][e];
+    return !(z == 0.0f);
+}
+
+// Fourteen instructions of the plain VALU for two elements, one of them for lost. Rounding conversions
 // and dot products (v_cvt_pk_bf16_f32, v_dot2c_f32_bf16) make it in seven, but
 // those run at half rate and hold up the MFMAs, while these take two waves'
 // instructions at once and run beside the MFMAs: cycles for 24 pairs and 48 MFMAs
 // of each of two waves per SIMD, 2528 this way (without the rounding) and 4012 that
 // way (MFMAs alone 1564).
-__device__ __forceinline__ SplitPair split_pair(float a, float b) {
+__device__ __forceinline__ SplitPair split_pair(float a, float b, unsigned& lost) {
     SplitPair o;
     unsigned ua, ub;
 #pragma unroll
@@ -105,15 +121,18 @@ __device__ __forceinline__ SplitPair split_pair(float a, float b) {
         a -= __builtin_bit_cast(float, ua & 0xffff0000u);
         b -= __builtin_bit_cast(float, ub & 0xffff0000u);
     }
+    lost |= ua | ub;
+    asm("" : "+v"(lost));  // in this order: gathered at the end of a slab, 32 residuals would stay in registers (32 spilled)
     return o;
 }
 
 struct SplitOct {
     bf16x8 t[kTerms];
 };
-__device__ __forceinline__ SplitOct split_oct(f32x4 u, f32x4 v) {
-    const SplitPair a = split_pair(u[0], u[1]), b = split_pair(u[2], u[3]);
-    const SplitPair c = split_pair(v[0], v[1]), d = split_pair(v[2], v[3]);
+__device__ __forceinline__ SplitOct split_oct(f32x4 u, f32x4 v, unsigned& lost) {
+    const SplitPair a = split_pair(u[0], u[1], lost), b = split_pair(u[2], u[3], lost);
+    const SplitPair c = split_pair(v[0], v[1], lost), d = split_pair(v[2], v[3], lost);
+    asm volatile("" : "+v"(lost));  // (106 registers in gemm_wave_split, 130 without: one workgroup per CU fewer)
     SplitOct o;
 #pragma unroll
     for (int t = 0; t < kTerms; ++t)
@@ -196,12 +215,12 @@ struct SlabTerms {
 };
 
 template <bool BK>
-__device__ __forceinline__ void split_slab(const SlabRegs& r, SlabTerms& s) {
+__device__ __forceinline__ void split_slab(const SlabRegs& r, SlabTerms& s, unsigned& lost) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        const SplitPair x = split_pair(r.a[v][0], r.a[v][1]), y = split_pair(r.a[v][2], r.a[v][3]);
-        const SplitPair z = BK ? split_pair(r.b[v][0], r.b[v][1]) : split_pair(r.b[0][v], r.b[1][v]);
-        const SplitPair w = BK ? split_pair(r.b[v][2], r.b[v][3]) : split_pair(r.b[2][v], r.b[3][v]);
+        const SplitPair x = split_pair(r.a[v][0], r.a[v][1], lost), y = split_pair(r.a[v][2], r.a[v][3], lost);
+        const SplitPair z = BK ? split_pair(r.b[v][0], r.b[v][1], lost) : split_pair(r.b[0][v], r.b[1][v], lost);
+        const SplitPair w = BK ? split_pair(r.b[v][2], r.b[v][3], lost) : split_pair(r.b[2][v], r.b[3][v], lost);
 #pragma unroll
         for (int t = 0; t < kTerms; ++t) {
             s.a[v][t] = bf16x4{x.t[t][0], x.t[t][1], y.t[t][0], y.t[t][1]};
@@ -316,7 +335,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // slab 1's loads are in flight.
 template <bool BK, int BS>
 __device__ __forceinline__ void slab_loop(const GemmProblem& p, const SlabOffsets& o, const SlabLds& l, int k0, int nk,
-                                          char* lds, SlabRegs& r, int wy, int wx, f32x4 (&acc)[16]) {
+                                          char* lds, SlabRegs& r, int wy, int wx, f32x4 (&acc)[16], unsigned& lost) {
     // One LDS buffer: the next slab is split under this slab's MFMAs (its raw
     // values, loaded a slab earlier, make room for the loads of the slab after
     // it) and written between two barriers; the other workgroup of the CU
@@ -325,7 +344,7 @@ __device__ __forceinline__ void slab_loop(const GemmProblem& p, const SlabOffset
     int kt = 0;
     __builtin_amdgcn_s_setprio(1);
     for (; kt + 2 < nk; ++kt) {
-        split_slab<BK>(r, s);
+        split_slab<BK>(r, s, lost);
         load_slab<BK>(p, o, k0 + (kt + 2) * kSlab, r);
         mma_slab<BS>(lds, l, wy, wx, acc);
         interleave_slab<BS, true>();
@@ -336,7 +355,7 @@ __device__ __forceinline__ void slab_loop(const GemmProblem& p, const SlabOffset
         __builtin_amdgcn_s_setprio(1);
     }
     if (kt + 1 < nk) {
-        split_slab<BK>(r, s);
+        split_slab<BK>(r, s, lost);
         mma_slab<BS>(lds, l, wy, wx, acc);
         interleave_slab<BS, false>();
         __builtin_amdgcn_s_setprio(0);
@@ -349,14 +368,52 @@ __device__ __forceinline__ void slab_loop(const GemmProblem& p, const SlabOffset
     __builtin_amdgcn_s_setprio(0);
 }
 
+// The product of BI x BJ blocks of 16 x 16 at (row0, col0) over [kb, ke), by the
+// calling wave alone and with the fp32 MFMA, straight from global memory: for operands
+// that the split does not hold, so it is short rather than fast. Lane l loads k = 4 (l /
+// 16) .. + 3 of each 16; rows and columns past the extent are clamped as in a slab.
+template <bool BK, int BI, int BJ, int LDB, int NB>
+__device__ __forceinline__ void fp32_blocks(const GemmProblem& p, int row0, int col0, int kb, int ke, int lane,
+                                            f32x4 (&acc)[NB]) {
+    const int r = lane & 15, c = 4 * (lane >> 4);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int k = kb; k < ke; k += 16) {
+        const bool two = k >= p.K1;
+        const int kl = (two ? k - p.K1 : k) + c;
+        const float* A = (two ? p.A2 : p.A) + kl;
+        const float* B = two ? p.B2 : p.B;
+        f32x4 a[BI], b[BJ];
+#pragma unroll
+        for (int i = 0; i < BI; ++i) a[i] = gload4(A + (size_t)min(row0 + 16 * i + r, p.M - 1) * p.lda);
+#pragma unroll
+        for (int j = 0; j < BJ; ++j) {
+            const int col = min(col0 + 16 * j + r, p.N - 1);
+            if constexpr (BK) {
+                b[j] = gload4(B + (size_t)col * p.ldb + kl);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) b[j][e] = B[(size_t)(kl + e) * p.ldb + col];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < BI; ++i)
+#pragma unroll
+                for (int j = 0; j < BJ; ++j)
+                    acc[i * LDB + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc[i * LDB + j], 0, 0, 0);
+    }
+}
+
 // The product of one 128 x 128 tile (tm, tn) of problem p over K range
 // [k0, k1), accumulated by the whole workgroup into acc. Every thread of the
-// workgroup must call it. Waves return without waiting for each other, so
-// LDS may be written after it only behind a barrier (the grouped kernel
-// writes none).
+// workgroup must call it. inexact: an int of LDS, for the workgroup's verdict on
+// the split.
 template <bool BK>
 __device__ __forceinline__ void gemm_mainloop(const GemmProblem& p, int tm, int tn, int k0, int k1, char* lds,
-                                              f32x4 (&acc)[16]) {
+                                              int* inexact, f32x4 (&acc)[16]) {
     const int row0 = tm * kTile, col0 = tn * kTile;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wy = wave >> 1, wx = wave & 1;
@@ -370,9 +427,11 @@ __device__ __forceinline__ void gemm_mainloop(const GemmProblem& p, int tm, int 
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
     const SlabLds l = slab_lds<BK>();
+    unsigned lost = 0;
+    if (threadIdx.x == 0) *inexact = 0;
     {
         SlabTerms s;
-        split_slab<BK>(r, s);
+        split_slab<BK>(r, s, lost);
         if (nk > 1) load_slab<BK>(p, o, k0 + kSlab, r);
         store_slab<BK>(lds, l, s);
     }
@@ -382,15 +441,21 @@ __device__ __forceinline__ void gemm_mainloop(const GemmProblem& p, int tm, int 
     // outputs are discarded. On a diagonal tile of a symmetric result the
     // quadrant below the diagonal is not needed and the diagonal quadrants
     // only on and above it.
-    if (row0 + wy * 64 >= p.M || col0 + wx * 64 >= p.N) {
-        slab_loop<BK, BS_NONE>(p, o, l, k0, nk, lds, r, wy, wx, acc);
+    const bool outside = row0 + wy * 64 >= p.M || col0 + wx * 64 >= p.N;
+    if (outside) {
+        slab_loop<BK, BS_NONE>(p, o, l, k0, nk, lds, r, wy, wx, acc, lost);
     } else if (p.upper && tm == tn) {
-        if (wy > wx) slab_loop<BK, BS_NONE>(p, o, l, k0, nk, lds, r, wy, wx, acc);
-        else if (wy == wx) slab_loop<BK, BS_UPPER>(p, o, l, k0, nk, lds, r, wy, wx, acc);
-        else slab_loop<BK, BS_ALL>(p, o, l, k0, nk, lds, r, wy, wx, acc);
+        if (wy > wx) slab_loop<BK, BS_NONE>(p, o, l, k0, nk, lds, r, wy, wx, acc, lost);
+        else if (wy == wx) slab_loop<BK, BS_UPPER>(p, o, l, k0, nk, lds, r, wy, wx, acc, lost);
+        else slab_loop<BK, BS_ALL>(p, o, l, k0, nk, lds, r, wy, wx, acc, lost);
     } else {
-        slab_loop<BK, BS_ALL>(p, o, l, k0, nk, lds, r, wy, wx, acc);
+        slab_loop<BK, BS_ALL>(p, o, l, k0, nk, lds, r, wy, wx, acc, lost);
     }
+    // Each thread split its share of the whole tile's operands, so one verdict for all waves.
+    if (split_lost(lost) || any_non_finite(acc)) *inexact = 1;
+    lds_barrier();
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(*inexact), 0) && !outside)
+        fp32_blocks<BK, 4, 4, 4>(p, row0 + wy * 64, col0 + wx * 64, k0, k1, threadIdx.x & 63, acc);
 }
 
 // Partial products of split tiles: thread t (= 64 wave + lane) keeps its 64
@@ -693,6 +758,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmProblem& p, int tm, int 
 template <bool UPPER, int BI, int BJ, int LDB = 4>
 __device__ __forceinline__ void direct_loop(const GemmProblem& p, int row0, int col0, int kb, int ke, int lane,
                                             f32x4 (&acc)[4 * LDB]) {
+    unsigned lost = 0;
     constexpr int kA[6] = {2, 1, 0, 1, 0, 0}, kB[6] = {0, 1, 2, 0, 1, 0};
     const int r = lane & 15, c = lane >> 4;
     unsigned oa[BI], ob[BJ];
@@ -718,9 +784,9 @@ __device__ __forceinline__ void direct_loop(const GemmProblem& p, int row0, int 
     auto slab = [&](auto refill) {
         SplitOct a[BI], b[BJ];
 #pragma unroll
-        for (int i = 0; i < BI; ++i) a[i] = split_oct(ra[i][0], ra[i][1]);
+        for (int i = 0; i < BI; ++i) a[i] = split_oct(ra[i][0], ra[i][1], lost);
 #pragma unroll
-        for (int j = 0; j < BJ; ++j) b[j] = split_oct(rb[j][0], rb[j][1]);
+        for (int j = 0; j < BJ; ++j) b[j] = split_oct(rb[j][0], rb[j][1], lost);
         refill();
 #pragma unroll
         for (int i = 0; i < BI; ++i)
@@ -736,6 +802,8 @@ __device__ __forceinline__ void direct_loop(const GemmProblem& p, int row0, int 
     int k = kb;
     for (; k + kSlab < ke; k += kSlab) slab([&] { load(k + kSlab); });
     slab([] {});
+    if (__builtin_expect(__any(split_lost(lost) || any_non_finite(acc)), 0))
+        fp32_blocks<true, BI, BJ, LDB>(p, row0, col0, kb, ke, lane, acc);
 }
 
 // One small-mode block: its K loop, then the epilogue of the block's
@@ -783,6 +851,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_grouped(const GemmProble
                                                                 const SmallUnit* __restrict__ small,
                                                                 float beta1, float* __restrict__ ws) {
     __shared__ __attribute__((aligned(16))) char lds[kSlabBytes];
+    __shared__ int inexact;
     const TileDesc td = tiles[blockIdx.x];
     if (td.part == kSmallGroup) {
         if constexpr (BK) {
@@ -796,7 +865,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_grouped(const GemmProble
     }
     const GemmProblem p = probs[td.prob];
     f32x4 acc[16];
-    gemm_mainloop<BK>(p, td.tm, td.tn, td.k0, td.k1, lds, acc);
+    gemm_mainloop<BK>(p, td.tm, td.tn, td.k0, td.k1, lds, &inexact, acc);
     if (td.part >= 0)
         store_partial(ws + (size_t)td.part * kSplitBlock, acc);
     else

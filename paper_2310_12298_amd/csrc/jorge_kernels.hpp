@@ -311,13 +311,14 @@ __device__ __forceinline__ void piece_mma_n(const float* a, const float* b, int 
             for (int i = 0; i < NBI; ++i) fa[i][h] = *reinterpret_cast<const f32x4*>(pa + 16 * i * LD + k0 + 16 * h);
         }
     };
+    unsigned lost = 0;
     read(0);
     for (int k0 = 0; k0 < K; k0 += 32) {
         SplitOct sb[BJ], sa[NBI];
 #pragma unroll
-        for (int j = 0; j < BJ; ++j) sb[j] = split_oct(fb[j][0], fb[j][1]);
+        for (int j = 0; j < BJ; ++j) sb[j] = split_oct(fb[j][0], fb[j][1], lost);
 #pragma unroll
-        for (int i = 0; i < NBI; ++i) sa[i] = split_oct(fa[i][0], fa[i][1]);
+        for (int i = 0; i < NBI; ++i) sa[i] = split_oct(fa[i][0], fa[i][1], lost);
         read(k0 + 32 < K ? k0 + 32 : 0);  // past the end: group 0 again, never multiplied
 #pragma unroll
         for (int i = 0; i < NBI; ++i)
@@ -327,6 +328,25 @@ __device__ __forceinline__ void piece_mma_n(const float* a, const float* b, int 
                 for (int j = 0; j < BJ; ++j)
                     acc[i * BJ + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sa[i].t[kA[u]], sb[j].t[kB[u]],
                                                                              acc[i * BJ + j], 0, 0, 0);
+    }
+    if (__builtin_expect(__any(split_lost(lost) || any_non_finite(acc)), 0)) {  // see fp32_blocks
+#pragma unroll
+        for (int q = 0; q < NBI * BJ; ++q) acc[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+        for (int k0 = 0; k0 < K; k0 += 16) {
+            f32x4 ga[NBI], gb[BJ];
+#pragma unroll
+            for (int j = 0; j < BJ; ++j) gb[j] = *reinterpret_cast<const f32x4*>(pb + 16 * j * LD + k0);
+#pragma unroll
+            for (int i = 0; i < NBI; ++i) ga[i] = *reinterpret_cast<const f32x4*>(pa + 16 * i * LD + k0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < NBI; ++i)
+#pragma unroll
+                    for (int j = 0; j < BJ; ++j)
+                        acc[i * BJ + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[i][e], gb[j][e], acc[i * BJ + j], 0, 0, 0);
+        }
     }
 }
 

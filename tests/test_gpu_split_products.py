@@ -74,3 +74,58 @@ def test_small_mode_blocks_equal_tiles_bitwise(shape, interval):
         assert torch.equal(pm[l], po[0]), l
         for k in ("L", "R", "mom", "mom_sgd"):
             assert torch.equal(many.get_state(l, k), one.get_state(0, k)), (l, k)
+
+
+def mom_after(shapes, L, R, G, **kw):
+    """m of the last layer after a step between updates without decay or grafting: (1 - beta1) L G R."""
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    ctx = Jorge(shapes, precond_interval=2, graft=False, **kw)
+    ctx.t, last = 1, len(shapes) - 1
+    ctx.set_state(last, "L", dev(L))
+    ctx.set_state(last, "R", dev(R))
+    ctx.step([torch.zeros(s, device="cuda") for s in shapes], [dev(G)] * len(shapes), 0.1, 0.9, 0.9, 0.0)
+    return ctx.get_state(last, "mom").cpu().numpy()
+
+
+# Every kernel that multiplies: the small contexts of both size classes, wave-split blocks,
+# tiles (whole and split, each operand layout) and small-mode blocks.
+PATHS = [((48, 64), 1, {}), ((100, 128), 1, {}), ((130, 260), 1, {}), ((640, 1152), 1, {}),
+         ((640, 1152), 1, dict(split_k=False)), ((300, 100), 1, dict(symmetrize=False)), ((64, 200), 300, {})]
+
+
+@pytest.mark.parametrize("shape,layers,kw", PATHS)
+def test_magnitudes_the_terms_do_not_hold(shape, layers, kw):
+    """Below 2^-110 three bf16 terms drop bits, above 3.39e38 the first overflows: the product is
+    still the fp32 one. L = 2^60 I, R = 2^60 I or random, so each product has one live term or few."""
+    (m, n), rng = shape, np.random.default_rng(11)
+    b = 1.0 - np.float64(np.float32(0.9))
+    eye = lambda d, e: np.ldexp(np.eye(d, dtype=np.float32), e)  # noqa: E731
+    # Every exponent from 2^-149's subnormals to above the limit, among zeros.
+    G = np.ldexp(rng.uniform(0.5, 1.0, (m, n)), rng.integers(-140, -100, (m, n))).astype(np.float32)
+    G[rng.random((m, n)) < 0.2] = 0.0
+    got = mom_after([shape] * layers, eye(m, 60), eye(n, 60), G, **kw)
+    want = b * np.ldexp(G.astype(np.float64), 120)
+    assert np.all(np.abs(got - want) <= 2.0 ** -22 * np.abs(want))     # one rounding each for both products, m and b
+    # A finite value above the terms' range, at full precision.
+    G = rng.standard_normal((m, n)).astype(np.float32)
+    G[m // 2, 5] = 3.4e38
+    R = rng.standard_normal((n, n)).astype(np.float32)
+    R = R + R.T
+    L = eye(m, -20)
+    got = mom_after([shape] * layers, L, R, G, **kw)
+    L, G, R = (x.astype(np.float64) for x in (L, G, R))
+    bound = b * (gamma(m) + gamma(n)) * (np.abs(L) @ np.abs(G) @ np.abs(R))
+    assert np.all(np.abs(got - b * (L @ G @ R)) <= bound)
+
+
+@pytest.mark.parametrize("shape,layers,kw", PATHS)
+def test_an_infinity_stays_one(shape, layers, kw):
+    """Its row comes out as infinities of R's signs; where it meets L's zeros, NaN."""
+    (m, n), rng = shape, np.random.default_rng(12)
+    G = rng.standard_normal((m, n)).astype(np.float32)
+    G[m // 2, 5] = np.inf
+    R = rng.standard_normal((n, n)).astype(np.float32)
+    R = R + R.T
+    got = mom_after([shape] * layers, np.eye(m, dtype=np.float32), R, G, **kw)
+    assert np.array_equal(got[m // 2], np.copysign(np.inf, R[5]).astype(np.float32))
+    assert np.all(np.isnan(np.delete(got, m // 2, 0)))
