@@ -1673,10 +1673,12 @@ jorge_status launch_small(jorge_ctx* c, float* const* params, const float* const
         if (update) {
             PtrBatch pb{};
             for (int i = 0; i < n; ++i) pb.p[i] = grads[l0 + i];
+            const int* const fi = c->chain.data() + 2 * l0;  // largest first
+            const int large = (int)std::count_if(fi, fi + 2 * n, [&](int i) { return c->factors[i].dp > Team64::D; });
             TimedLaunch tl(c, ST_LDS_CHAIN);
-            hipLaunchKernelGGL(small_chain128_kernel, dim3(2 * n), dim3(kSmallThreads), 0, c->stream, c->dfactors,
-                               c->dchain + 2 * l0, c->dlayers, l0, pb, beta2, (int)c->hp.beta_mode,
-                               (int)c->hp.series_order);
+            hipLaunchKernelGGL(small_chain128_kernel, dim3(large + (2 * n - large + 1) / 2), dim3(kSmallThreads), 0,
+                               c->stream, c->dfactors, c->dchain + 2 * l0, 2 * n, large, c->dlayers, l0, pb, beta2,
+                               (int)c->hp.beta_mode, (int)c->hp.series_order);
             tl.finish();
             JORGE_HIP(c, hipGetLastError());
         }

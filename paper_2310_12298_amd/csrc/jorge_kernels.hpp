@@ -271,7 +271,7 @@ struct Team {
     static constexpr int GV = D_ * D_ / THREADS;      // gradient elements per thread
     static_assert(WAVES_ / GRID_X * 16 * BI_ == D_, "the pieces cover the product");
 };
-typedef Team<64, 4, 2, 2> Team64;     // a factor of a layer with m, n <= 64
+typedef Team<64, 4, 2, 2> Team64;     // a factor up to 64
 typedef Team<128, 8, 4, 2> Team128;   // a factor up to 128; the rest of a layer's step
 typedef Team<64, 8, 2, 1> Apply64;    // the rest of the step of a layer with m, n <= 64
 constexpr int kSmallThreads = 512;
@@ -427,17 +427,17 @@ __device__ __forceinline__ void factor_store(int t, const f32x4 (&r)[T::AV], flo
     }
 }
 
-// The gradient (dense m x n, any alignment) through registers: thread t holds
+// The gradient (m x n, row stride ld, any alignment) through registers: thread t holds
 // column t % D of rows t / D + i (THREADS / D), zero outside the layer. The loads are
 // unconditional (positions outside read the nearest one inside), so all are in
 // flight at once.
 template <class T>
-__device__ __forceinline__ void grad_load(int t, const float* __restrict__ G, int m, int n, float (&r)[T::GV]) {
+__device__ __forceinline__ void grad_load(int t, const float* __restrict__ G, int m, int n, int ld, float (&r)[T::GV]) {
     const int c = t % T::D, cc = min(c, n - 1);
 #pragma unroll
     for (int i = 0; i < T::GV; ++i) {
         const int row = t / T::D + i * (T::THREADS / T::D);
-        r[i] = ld_at(G, 4u * (unsigned)(min(row, m - 1) * n + cc));
+        r[i] = ld_at(G, 4u * (unsigned)(min(row, m - 1) * ld + cc));
     }
 #pragma unroll
     for (int i = 0; i < T::GV; ++i) {
@@ -467,13 +467,15 @@ __device__ __forceinline__ double sum_waves(const double* red) {
 
 // One factor's update by a team (threads t = 0 .. T::THREADS - 1, wave = t / 64).
 // m0, m1: two LDS matrices of T::MAT floats; red: T::WAVES doubles. g: the layer's
-// gradient in the team's registers. Every thread of the
+// gradient in the team's registers, with WIDE its first D columns (rows for R_hat):
+// the others, if kp > D, are loaded under the product of the first (deep: some team of
+// the workgroup has such a factor). live: the team stores its results. Every thread of the
 // workgroup calls it (all its teams meet the same barriers). On return the new
 // factor is in global memory and, for side R of a non-symmetric factor
 // transposed, in m1 (behind a barrier).
-template <class T>
-__device__ __forceinline__ void chain_update(const FactorDev& F, int side, int t, int wave, const float (&g)[T::GV],
-                                             double beta2, int mode, int symmetrize, int order, float* m0, float* m1,
+template <class T, bool WIDE = false>
+__device__ __forceinline__ void chain_update(const FactorDev& F, int side, int t, int wave, float (&g)[T::GV],
+                                             const LayerDev& L, const float* __restrict__ G, bool deep, bool live, double beta2, int mode, int symmetrize, int order, float* m0, float* m1,
                                              double* red) {
     constexpr int NB = T::BI * T::BJ;
     const int dp = F.dp, kp = F.kp, d = F.d;
@@ -496,8 +498,22 @@ __device__ __forceinline__ void chain_update(const FactorDev& F, int side, int t
     grad_store<T>(t, g, m1, side != 0);
     __syncthreads();
     // M = H H^T
-    piece_mma<T>(p, m1, m1, kp, acc);
+    const bool more = WIDE && kp > T::D;
+    if (more) {
+        if (side == 0) grad_load<T>(t, G + T::D, L.m, L.n - T::D, L.n, g);
+        else grad_load<T>(t, G + T::D * L.n, L.m - T::D, L.n, L.n, g);
+    }
+    piece_mma<T>(p, m1, m1, more ? T::D : kp, acc);
     __syncthreads();
+    if (WIDE && deep) {
+        if (more) grad_store<T>(t, g, m1, side != 0);
+        __syncthreads();
+        f32x4 rest[NB];
+        piece_mma<T>(p, m1, m1, more ? kp - T::D : 0, rest);
+#pragma unroll
+        for (int q = 0; q < NB; ++q) acc[q] += rest[q];
+        __syncthreads();
+    }
     piece_store<T, false>(p, m1, acc);
     __syncthreads();
     // X = A^4 M (M symmetric: its rows are its columns) with ||X||_F^2; the wave
@@ -518,7 +534,7 @@ __device__ __forceinline__ void chain_update(const FactorDev& F, int side, int t
     f32x4 av2[T::AV];
     factor_load<T>(t, F.A, dp, av2);
     const FactorScalars fs = factor_scalars(sqrt(sum_waves<T::WAVES>(red)), beta2, mode);
-    if (t == 0) *F.sc = fs;
+    if (t == 0 && live) *F.sc = fs;
     const float a = fs.a, b = fs.b, sf = fs.sf, ce = fs.e;
     __syncthreads();
     // X X (B = X: its rows in k are the rows of X^T in m1)
@@ -567,7 +583,7 @@ __device__ __forceinline__ void chain_update(const FactorDev& F, int side, int t
                 const f32x4 zt = *reinterpret_cast<const f32x4*>(m0 + col * T::LD + row);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) z[e] = 0.5f * (z[e] + zt[e]);
-                st4_at(F.A, 4u * (unsigned)(col * dp + row), z);
+                if (live) st4_at(F.A, 4u * (unsigned)(col * dp + row), z);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) st_at(F.A, 4u * (unsigned)((row + e) * dp + col), z[e]);
@@ -709,13 +725,13 @@ __global__ __launch_bounds__(kSmallThreads) void small_step64_kernel(const Layer
     const int tid = threadIdx.x, team = __builtin_amdgcn_readfirstlane(tid >> 8), t = tid & 255;
     const FactorDev F = f[2 * li + team];
     float ga[Apply64::GV];
-    grad_load<Apply64>(tid, G, L.m, L.n, ga);
+    grad_load<Apply64>(tid, G, L.m, L.n, L.n, ga);
     const double ps = msgd_update<Apply64>(L, ga, sc.beta1);
     if (update) {
         float gt[Team64::GV];
-        grad_load<Team64>(t, G, L.m, L.n, gt);
-        chain_update<Team64>(F, team, t, __builtin_amdgcn_readfirstlane(t >> 6), gt, beta2, mode, symmetrize, order,
-                             mat[2 * team], mat[2 * team + 1], red + 4 * team);
+        grad_load<Team64>(t, G, L.m, L.n, L.n, gt);
+        chain_update<Team64>(F, team, t, __builtin_amdgcn_readfirstlane(t >> 6), gt, L, G, false, true, beta2, mode,
+                             symmetrize, order, mat[2 * team], mat[2 * team + 1], red + 4 * team);
     } else {
         f32x4 av[Team64::AV];
         factor_load<Team64>(t, F.A, F.dp, av);
@@ -726,21 +742,47 @@ __global__ __launch_bounds__(kSmallThreads) void small_step64_kernel(const Layer
     layer_apply<Apply64, false>(L, F, ptrs.param(blockIdx.x), ps, sc, mat[1], mat[0], mat[2], mat[3], red, coef);
 }
 
-// Layers up to 128 (symmetric factors): each factor's update in a workgroup of
-// its own (blockIdx.x: one of the batch's factors, largest first) ...
+// Layers up to 128 (symmetric factors): the factors' updates, first those above
+// 64 in a workgroup each (the list's first `large`), then the others two to a workgroup,
+// one per team of four waves. LDS and registers let one workgroup run per CU whatever
+// its factors' sizes; alone in one, a factor up to 64 would use two of its eight waves.
+// 512 layers of 32-64 with one of 96 x 96 take 131 us per step, with one factor to each
+// workgroup 171; 256 of them 91 against 111; 512 of 48 x 96 the same 150 ...
 __global__ __launch_bounds__(kSmallThreads) void small_chain128_kernel(const FactorDev* __restrict__ f,
-                                                                       const int* __restrict__ list,
+                                                                       const int* __restrict__ list, int count,
+                                                                       int large,
                                                                        const LayerDev* __restrict__ layers,
                                                                        int layer_base, PtrBatch grads, double beta2,
                                                                        int mode, int order) {
     __shared__ __attribute__((aligned(16))) float mat[2][Team128::MAT];
     __shared__ double red[Team128::WAVES];
-    const int fi = list[blockIdx.x], li = fi >> 1;
+    static_assert(4 * Team64::MAT <= 2 * Team128::MAT && 2 * Team64::WAVES == Team128::WAVES, "two teams fit");
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x < large) {
+        const int fi = list[blockIdx.x];
+        const FactorDev F = f[fi];
+        const LayerDev& L = layers[fi >> 1];
+        const float* G = grads.p[(fi >> 1) - layer_base];
+        float g[Team128::GV];
+        grad_load<Team128>(tid, G, L.m, L.n, L.n, g);
+        chain_update<Team128, false>(F, fi & 1, tid, __builtin_amdgcn_readfirstlane(tid >> 6), g, L, G, false, true,
+                                     beta2, mode, 1, order, mat[0], mat[1], red);
+        return;
+    }
+    const int team = __builtin_amdgcn_readfirstlane(tid >> 8), t = tid & 255;
+    const int first = large + 2 * ((int)blockIdx.x - large), mine = first + team;
+    // The last workgroup's second team may be one too many: it follows the first and stores nothing.
+    const bool live = mine < count;
+    const int fi = list[live ? mine : first], other = list[live && first + 1 < count ? first + 1 - team : first];
     const FactorDev F = f[fi];
-    float g[Team128::GV];
-    grad_load<Team128>(threadIdx.x, grads.p[li - layer_base], layers[li].m, layers[li].n, g);
-    chain_update<Team128>(F, fi & 1, threadIdx.x, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g, beta2, mode, 1,
-                          order, mat[0], mat[1], red);
+    const LayerDev& L = layers[fi >> 1];
+    const float* G = grads.p[(fi >> 1) - layer_base];
+    const bool deep = max(F.kp, f[other].kp) > Team64::D;  // for both teams alike: they share their barriers
+    float g[Team64::GV];
+    grad_load<Team64>(t, G, L.m, L.n, L.n, g);
+    float* const m0 = mat[0] + 2 * team * Team64::MAT;
+    chain_update<Team64, true>(F, fi & 1, t, __builtin_amdgcn_readfirstlane(t >> 6), g, L, G, deep, live, beta2, mode, 1,
+                               order, m0, m0 + Team64::MAT, red + team * Team64::WAVES);
 }
 
 // ... and the rest of each layer's step in one.
@@ -754,7 +796,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_apply128_kernel(const Lay
     const LayerDev L = layers[li];
     const FactorDev FL = f[2 * li], FR = f[2 * li + 1];
     float g[Team128::GV];
-    grad_load<Team128>(t, ptrs.grad(blockIdx.x), L.m, L.n, g);
+    grad_load<Team128>(t, ptrs.grad(blockIdx.x), L.m, L.n, L.n, g);
     f32x4 av[Team128::AV];
     factor_load<Team128>(t, FL.A, FL.dp, av);
     const double ps = msgd_update<Team128>(L, g, sc.beta1);

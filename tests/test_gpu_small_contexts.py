@@ -20,6 +20,8 @@ HP = dict(lr=0.1, beta2=0.9, beta1=0.9, weight_decay=5e-4)
 # Edges of the 16- and 32-wide blocks and of both size classes, single rows and columns.
 UP_TO_64 = [(1, 1), (1, 64), (64, 1), (31, 33), (32, 32), (33, 64), (64, 64), (17, 48)]
 UP_TO_128 = [(65, 1), (1, 128), (97, 96), (128, 128), (127, 65), (96, 33), (32, 128), (64, 64)]
+# Factors up to 64 share a workgroup: k up to and above 64 side by side, and an odd number of them.
+PAIRED_128 = UP_TO_128 + [(64, 127), (90, 64), (31, 97), (128, 17), (64, 50), (65, 20), (20, 20)]
 
 
 def off_by_one_float(x):
@@ -39,11 +41,11 @@ def state(rng, m, n, sigma):
                   rng.standard_normal((m, n)).astype(np.float32) * np.float32(sigma)]
 
 
-@pytest.mark.parametrize("shapes", [UP_TO_64, UP_TO_128], ids=["64", "128"])
+@pytest.mark.parametrize("shapes", [UP_TO_64, UP_TO_128, PAIRED_128], ids=["64", "128", "paired"])
 @pytest.mark.parametrize("update", [True, False])
 @pytest.mark.parametrize("symmetrize,order", [(True, 2), (True, 3), (False, 2), (False, 3)])
 def test_one_step_from_an_injected_state(shapes, update, symmetrize, order):
-    if shapes is UP_TO_128 and not symmetrize:
+    if shapes is not UP_TO_64 and not symmetrize:
         pytest.skip("contexts above 64 need symmetric factors to run in LDS")
     rng = np.random.default_rng([len(shapes), update, symmetrize, order, shapes[0][0]])
     sigma = 1e-2
@@ -63,7 +65,8 @@ def test_one_step_from_an_injected_state(shapes, update, symmetrize, order):
     opt.set_timing(True)
     opt.step(pg, [off_by_one_float(x) for x in grads], **HP)
     launches = {k: v[1] for k, v in opt.read_timing().items() if v[1]}
-    assert set(launches) == {"lds_chain"}, launches         # the whole step
+    # the whole step: one kernel up to 64; else one for the factors and one for the rest
+    assert launches == {"lds_chain": 1 if shapes is UP_TO_64 or not update else 2}
     prev = [x.astype(np.float64) for x in theta]
     po = orc.step(prev, grads, HP["lr"], HP["beta2"], HP["beta1"], HP["weight_decay"])
     for l in range(len(shapes)):
@@ -73,6 +76,31 @@ def test_one_step_from_an_injected_state(shapes, update, symmetrize, order):
                     HP["lr"], HP["weight_decay"], STEP, f"layer {l} {shapes[l]}")
         if symmetrize:
             assert np.array_equal(got["L"], got["L"].T) and np.array_equal(got["R"], got["R"].T), l
+
+
+def test_paired_sizes():
+    small = [(k, d) for m, n in PAIRED_128 for d, k in ((m, n), (n, m)) if d <= 64]
+    assert len(small) % 2 and any(k > 64 for k, _ in small) and any(k <= 64 for k, _ in small)
+
+
+@pytest.mark.parametrize("layers", [1, 2, 7])
+def test_a_factor_does_not_depend_on_its_neighbour(layers):
+    """A layer's factors up to 64 give the same bits beside deep and shallow factors, alone and in pairs."""
+    rng = np.random.default_rng(9)
+    shape = (48, 40)
+    st, g = state(rng, *shape, 1e-2), (rng.standard_normal(shape) * 1e-2).astype(np.float32)
+    out = []
+    for shapes in ([(96, 96), shape], [shape] * layers + [(128, 40)], [(60, 120)] * layers + [shape, (70, 9)]):
+        opt, l = Jorge(shapes), shapes.index(shape)
+        for kind, v in zip(("L", "R", "mom", "mom_sgd"), st):
+            opt.set_state(l, kind, torch.from_numpy(v))
+        params = [torch.zeros(s, device="cuda") for s in shapes]
+        grads = [torch.ones(s, device="cuda") for s in shapes]
+        grads[l] = torch.from_numpy(g).cuda()
+        opt.step(params, grads, **HP)
+        out.append([opt.get_state(l, k) for k in ("L", "R", "mom")] + [params[l]])
+    for other in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out[0], other))
 
 
 def test_layers_of_several_batches_step_alike():
