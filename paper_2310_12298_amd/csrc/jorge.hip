@@ -1656,21 +1656,7 @@ jorge_status launch_small(jorge_ctx* c, float* const* params, const float* const
     const StepScalars sc{lr, weight_decay, (float)beta1, (int)c->hp.graft};
     for (int l0 = 0; l0 < nl; l0 += kPtrBatch) {
         const int n = std::min(kPtrBatch, nl - l0);
-        PtrPack pp{};
-        for (int i = 0; i < n; ++i) {
-            pp.set(2 * i, reinterpret_cast<uint64_t>(grads[l0 + i]));
-            pp.set(2 * i + 1, reinterpret_cast<uint64_t>(params[l0 + i]));
-        }
-        if (c->small == Team64::D) {
-            TimedLaunch tl(c, ST_LDS_CHAIN);
-            hipLaunchKernelGGL(small_step64_kernel, dim3(n), dim3(kSmallThreads), 0, c->stream, c->dlayers, c->dfactors,
-                               l0, pp, sc, (int)update, beta2, (int)c->hp.beta_mode, (int)c->hp.symmetrize,
-                               (int)c->hp.series_order);
-            tl.finish();
-            JORGE_HIP(c, hipGetLastError());
-            continue;
-        }
-        if (update) {
+        if (update && c->small != Team64::D) {
             PtrBatch pb{};
             for (int i = 0; i < n; ++i) pb.p[i] = grads[l0 + i];
             const int* const fi = c->chain.data() + 2 * l0;  // largest first
@@ -1682,11 +1668,21 @@ jorge_status launch_small(jorge_ctx* c, float* const* params, const float* const
             tl.finish();
             JORGE_HIP(c, hipGetLastError());
         }
-        TimedLaunch tl(c, ST_LDS_CHAIN);
-        hipLaunchKernelGGL(small_apply128_kernel, dim3(n), dim3(kSmallThreads), 0, c->stream, c->dlayers, c->dfactors,
-                           l0, pp, sc);
-        tl.finish();
-        JORGE_HIP(c, hipGetLastError());
+        // One launch for all of the batch, unless its addresses differ in their upper 16 bits.
+        for (int i0 = 0, i1; i0 < n; i0 = i1) {
+            PtrPack pp{};
+            for (i1 = i0; i1 < n && pp.set(i1 - i0, grads[l0 + i1], params[l0 + i1]);) ++i1;
+            TimedLaunch tl(c, ST_LDS_CHAIN);
+            if (c->small == Team64::D)
+                hipLaunchKernelGGL(small_step64_kernel, dim3(i1 - i0), dim3(kSmallThreads), 0, c->stream, c->dlayers,
+                                   c->dfactors, l0 + i0, pp, sc, (int)update, beta2, (int)c->hp.beta_mode,
+                                   (int)c->hp.symmetrize, (int)c->hp.series_order);
+            else
+                hipLaunchKernelGGL(small_apply128_kernel, dim3(i1 - i0), dim3(kSmallThreads), 0, c->stream, c->dlayers,
+                                   c->dfactors, l0 + i0, pp, sc);
+            tl.finish();
+            JORGE_HIP(c, hipGetLastError());
+        }
     }
     return JORGE_OK;
 }
@@ -1912,10 +1908,6 @@ jorge_status jorge_step(jorge_ctx* c, float* const* params, const float* const* 
     const int nl = (int)c->layers.size();
     for (int i = 0; i < nl; ++i)
         if (!params[i] || !grads[i]) return fail(c, JORGE_ERR_INVALID_ARGUMENT, "jorge_step: null tensor");
-    // A small context's launches carry 48-bit addresses (PtrPack); user addresses have 47.
-    for (int i = 0; c->small && i < nl; ++i)
-        if ((reinterpret_cast<uint64_t>(params[i]) | reinterpret_cast<uint64_t>(grads[i])) >> 48)
-            return fail(c, JORGE_ERR_UNSUPPORTED, "jorge_step: a tensor's address has more than 48 bits");
     if (c->poisoned)
         return fail(c, JORGE_ERR_HIP,
                     "jorge_step: an earlier step failed part-way; restore the state (jorge_set_state) and "
@@ -1937,7 +1929,6 @@ jorge_status jorge_step_noalloc(const jorge_shape* shape, const jorge_hparams* h
     jorge_status st = validate_args(shape, 1, hp, &h);
     if (st != JORGE_OK) return st;
     if (t < 1 || !theta || !grad || !L || !R || !mom || !mom_sgd) return JORGE_ERR_INVALID_ARGUMENT;
-    if ((reinterpret_cast<uint64_t>(theta) | reinterpret_cast<uint64_t>(grad)) >> 48) return JORGE_ERR_UNSUPPORTED;
     if (!(std::isfinite(lr) && lr >= 0.0) || !(beta2 > 0.0 && beta2 < 1.0) || !(beta1 >= 0.0 && beta1 < 1.0) ||
         !(std::isfinite(weight_decay) && weight_decay >= 0.0))
         return JORGE_ERR_INVALID_ARGUMENT;

@@ -199,16 +199,29 @@ struct MutPtrBatch {
     float* p[kPtrBatch];
 };
 // Gradient and parameter pointers of up to kPtrBatch layers in 3 KB (both as
-// full pointers would take the whole 4 KB): 48 bits each, which is what a user
-// address has. Gradient of layer i at 2 i, parameter at 2 i + 1.
+// full pointers would take the whole 4 KB): 48 bits each, and the upper 16 once for
+// all gradients and once for all parameters of the launch. Gradient of layer i at
+// 2 i, parameter at 2 i + 1.
 struct PtrPack {
     uint32_t lo[2 * kPtrBatch];
     uint16_t hi[2 * kPtrBatch];
-    __host__ void set(int i, uint64_t v) {
-        lo[i] = (uint32_t)v;
-        hi[i] = (uint16_t)(v >> 32);
+    uint16_t top[2];
+    // False, and nothing set, if either address is of another upper part than layer 0's.
+    __host__ bool set(int i, const float* grad, const float* param) {
+        const uint64_t v[2] = {reinterpret_cast<uint64_t>(grad), reinterpret_cast<uint64_t>(param)};
+        for (int w = 0; w < 2; ++w) {
+            if (i == 0) top[w] = (uint16_t)(v[w] >> 48);
+            else if (top[w] != (uint16_t)(v[w] >> 48)) return false;
+        }
+        for (int w = 0; w < 2; ++w) {
+            lo[2 * i + w] = (uint32_t)v[w];
+            hi[2 * i + w] = (uint16_t)(v[w] >> 32);
+        }
+        return true;
     }
-    __device__ uint64_t get(int i) const { return (uint64_t)lo[i] | (uint64_t)hi[i] << 32; }
+    __host__ __device__ uint64_t get(int i) const {
+        return (uint64_t)lo[i] | (uint64_t)hi[i] << 32 | (uint64_t)top[i & 1] << 48;
+    }
     __device__ const float* grad(int i) const { return reinterpret_cast<const float*>(get(2 * i)); }
     __device__ float* param(int i) const { return reinterpret_cast<float*>(get(2 * i + 1)); }
 };
