@@ -104,8 +104,20 @@ GEMM_STAGES = ("gram", "pow4", "xform", "chain4", "chain5", "poly", "poly2", "up
 NON_UPDATE_STAGES = ("precond_L", "precond_R")
 # Launches of the grouped GEMM's split-tile fixup: their time is part of the GEMM stages' time.
 FIXUP_STAGE = "split_fixup"
-# The LDS chain kernels (whole factor updates of small factors in one workgroup each).
+# The small-context kernels: every launch of a context whose factors are all small, its factor
+# updates (this stage's own flops) and its preconditioning (the flops of the precond stages).
 CHAIN_STAGE = "lds_chain"
+
+
+def executed_flops(flops, launches, steps, updates):
+    """Flops of each stage over `steps` steps, `updates` of them updating the factors, from its flops
+    in one step; the preconditioning of a small context counts where it runs, in CHAIN_STAGE."""
+    out = {k: flops[k] * (steps - updates if k in NON_UPDATE_STAGES else updates) for k in GEMM_STAGES}
+    out[CHAIN_STAGE] = flops[CHAIN_STAGE] * updates
+    if launches[CHAIN_STAGE]:
+        out[CHAIN_STAGE] += sum(out[k] for k in GEMM_STAGES)
+        out.update({k: 0.0 for k in GEMM_STAGES})
+    return out
 
 
 def copy_reference_gbs(mib=1024, reps=10):
@@ -275,16 +287,15 @@ def measure(config, steps, warmup, interval=1, form="auto", split_k=1, series_or
         raise SystemExit("no factor update in the timed steps; use more steps or a smaller interval")
     # Algorithmic flops of each stage in one factor-updating step, from the library's launch tables.
     flops = opt.stage_flops()
-    ran = {k: (steps - updates if k in NON_UPDATE_STAGES else updates) for k in GEMM_STAGES}
-    ran[CHAIN_STAGE] = updates
+    ran = executed_flops(flops, {k: n for k, (_, n) in timing.items()}, steps, updates)
     per_stage = {}
     for k, (ms, n) in timing.items():
         e = {"ms_per_launch": ms / n if n else 0.0, "launches": n}
         if k in ran and ms > 0:
-            e["tflops"] = flops[k] * ran[k] / (ms * 1e-3) / 1e12
+            e["tflops"] = ran[k] / (ms * 1e-3) / 1e12
         per_stage[k] = e
     # Dominant kernel: the grouped NT GEMM; every GEMM stage of the step is a launch of it.
-    g_flops = sum(flops[k] * ran[k] for k in GEMM_STAGES)
+    g_flops = sum(ran[k] for k in GEMM_STAGES)
     g_ms = sum(timing[k][0] for k in GEMM_STAGES) + timing[FIXUP_STAGE][0]
     g_launches = sum(timing[k][1] for k in GEMM_STAGES)
     achieved = g_flops / (g_ms * 1e-3) / 1e12 if g_ms > 0 else 0.0
@@ -295,9 +306,8 @@ def measure(config, steps, warmup, interval=1, form="auto", split_k=1, series_or
         k_ms = timing[k][0] / max(1, timing[k][1])
         gbs = nbytes / (k_ms * 1e-3) / 1e9 if k_ms else 0.0
         hbm[k] = {"achieved": gbs, "frac": gbs / PEAK_HBM_GBS, "bytes_per_launch": nbytes}
-    # the step's flops: the grouped levels' and the LDS chains' (in a context of small factors only, the
-    # chains take every factor update in place of the levels)
-    step_f = (g_flops + flops[CHAIN_STAGE] * updates) / steps
+    # the step's flops: the grouped levels' or the small-context kernels'
+    step_f = (g_flops + ran[CHAIN_STAGE]) / steps
     step_b = (step_bytes(shapes, True) * updates + step_bytes(shapes, False) * (steps - updates)) / steps
     t_mfma, t_hbm = step_f / (PEAK_SPLIT_TFLOPS * 1e12), step_b / (PEAK_HBM_GBS * 1e9)
     step_roof = {"flops": step_f, "bytes": step_b, "t_mfma_ms": t_mfma * 1e3, "t_hbm_ms": t_hbm * 1e3,

@@ -317,7 +317,11 @@ jorge_status jorge_reset_timing(jorge_ctx* ctx);
 int32_t      jorge_num_stages(void);
 /* Algorithmic flops of each stage in one step that updates the factors
  * (symmetric products counted once per stored pair), for
- * min(n, jorge_num_stages()) stages; flops: host array. */
+ * min(n, jorge_num_stages()) stages; flops: host array. The stages precond_L and
+ * precond_R hold L G and (L G) R of a step that does not update, uprecond_L and
+ * uprecond_R those of one that does; where the LDS kernels take the whole step,
+ * lds_chain holds the factor updates only, and the products of the other four run
+ * in its launches. */
 jorge_status jorge_stage_flops(const jorge_ctx* ctx, double* flops, int32_t n);
 const char*  jorge_stage_name(int32_t stage);  /* NULL if out of range */
 

@@ -184,7 +184,8 @@ struct jorge_ctx {
     size_t block_slot_bytes = 0;  // arena bytes of partial sums beyond kWaveSlots per tile
     bool fused_norms = false;  // the weight update sums the layers' norms (each at most kFusedNormParts)
     int small = 0;  // 64 or 128: a small context of that size class (0: the grouped levels)
-    double chain_flops = 0.0;  // algorithmic flops of a small context's update step
+    double chain_flops = 0.0;            // algorithmic flops of a small context's factor updates
+    double apply_flops[2] = {0.0, 0.0};  // and of its L G and (L G) R, on every step
     float* splitws = nullptr;     // partial products of split tiles (shared by the stages, in turn)
     int64_t splitws_blocks = 0;
     // Per stage: products with both operands K-major, and (literal mode only)
@@ -839,7 +840,8 @@ size_t plan(jorge_ctx* c) {
             L.off_Gpt = take(padded);
             L.off_T = take(padded);
         } else {
-            c->chain_flops += 2.0 * L.m * L.n * ((double)L.m + L.n);  // L G R
+            c->apply_flops[0] += 2.0 * L.m * L.n * (double)L.m;
+            c->apply_flops[1] += 2.0 * L.m * L.n * (double)L.n;
         }
         L.off_mom = take(dense);
         L.off_msgd = take(dense);
@@ -2181,8 +2183,11 @@ int32_t jorge_num_stages(void) { return ST_COUNT; }
 
 jorge_status jorge_stage_flops(const jorge_ctx* c, double* flops, int32_t n) {
     if (!c || !flops || n < 0) return JORGE_ERR_INVALID_ARGUMENT;
-    for (int i = 0; i < std::min<int>(n, ST_COUNT); ++i)
+    for (int i = 0; i < std::min<int>(n, ST_COUNT); ++i) {
         flops[i] = c->nt[i].flops + c->nn[i].flops + (i == ST_LDS_CHAIN ? c->chain_flops : 0.0);
+        if (i == ST_PRECOND_L || i == ST_UPRECOND_L) flops[i] += c->apply_flops[0];
+        if (i == ST_PRECOND_R || i == ST_UPRECOND_R) flops[i] += c->apply_flops[1];
+    }
     return JORGE_OK;
 }
 

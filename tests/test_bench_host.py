@@ -71,6 +71,17 @@ def test_workload_sub_record_fields():
     json.dumps(rec)
 
 
+def test_executed_flops_count_preconditioning_on_every_step():
+    stages = {k: 0.0 for k in bench.GEMM_STAGES}
+    levels = dict(stages, gram=7.0, precond_L=3.0, precond_R=4.0, uprecond_L=2.0, uprecond_R=1.0, lds_chain=0.0)
+    ran = bench.executed_flops(levels, {"lds_chain": 0}, 50, 2)
+    assert ran["gram"] == 14 and ran["precond_L"] == 3 * 48 and ran["uprecond_R"] == 2 and ran["lds_chain"] == 0
+    # A small context: everything in its own launches, L G R on all 50 steps.
+    small = dict(stages, precond_L=3.0, precond_R=4.0, uprecond_L=3.0, uprecond_R=4.0, lds_chain=100.0)
+    ran = bench.executed_flops(small, {"lds_chain": 52}, 50, 2)
+    assert ran["lds_chain"] == 2 * 100 + 50 * 7 and all(ran[k] == 0 for k in bench.GEMM_STAGES)
+
+
 def test_layers_option_parses_shape_lists():
     assert bench.parse_layers("128x128*3,64x576") == [(128, 128)] * 3 + [(64, 576)]
     assert bench.parse_layers(" 1x1 ") == [(1, 1)]

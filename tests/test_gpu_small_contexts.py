@@ -116,3 +116,13 @@ def test_layers_of_several_batches_step_alike():
     for i in range(3, 300):
         assert torch.equal(params[i], params[i % 3]), i
     assert not torch.equal(params[0], params[1])
+
+
+def test_stage_flops_keep_updates_and_preconditioning_apart():
+    m, n = 40, 96
+    fl = Jorge([(m, n)] * 3).stage_flops()
+    for stage in ("precond", "uprecond"):       # on steps between updates, and on updating ones
+        assert fl[stage + "_L"] == 3 * 2 * m * m * n and fl[stage + "_R"] == 3 * 2 * m * n * n
+    # Algorithm 2's products, symmetric ones once: H H^T, A^2, A^4, then X, X X and A P
+    factor = lambda d, k: d * d * k + 2 * d ** 3 + 6 * d ** 3  # noqa: E731
+    assert fl["lds_chain"] == 3 * (factor(m, n) + factor(n, m))
