@@ -324,7 +324,8 @@ def measure(config, steps, warmup, interval=1, form="auto", split_k=1, series_or
         "gemm": {"achieved": achieved, "ms_per_launch": ms_launch, "launches": g_launches,
                  "gflop_per_launch": g_flops / max(1, g_launches) / 1e9},
         "step_roofline": step_roof,
-        "mfma_util_pct": 100.0 * step_f / (inst_ms / steps * 1e-3) / (PEAK_FP32_MFMA_TFLOPS * 1e12),
+        "mfma_util_pct": 100.0 * step_f / (inst_ms / steps * 1e-3) / (PEAK_SPLIT_TFLOPS * 1e12),
+        "fp32_mfma_equivalent_pct": 100.0 * step_f / (inst_ms / steps * 1e-3) / (PEAK_FP32_MFMA_TFLOPS * 1e12),
         "paper_order": {"flops_per_step": f_paper, "effective_tflops": f_paper / (total_ms / steps * 1e-3) / 1e12,
                         "note": PAPER_ORDER_NOTE},
         "hbm": hbm, "stages": per_stage,
@@ -338,8 +339,8 @@ def measure(config, steps, warmup, interval=1, form="auto", split_k=1, series_or
 def summary(res):
     """The sub-record of a workload measured beside the headline one."""
     return {"workload": WORKLOAD_NAMES[res["config"]], "steps": res["steps"], "value": res["value"], "unit": "steps/s",
-            "ms_per_step": res["ms_per_step"], "gemm_frac": res["gemm"]["achieved"] / PEAK_FP32_MFMA_TFLOPS,
-            "gemm_split_frac": res["gemm"]["achieved"] / PEAK_SPLIT_TFLOPS,
+            "ms_per_step": res["ms_per_step"], "gemm_frac": res["gemm"]["achieved"] / PEAK_SPLIT_TFLOPS,
+            "fp32_mfma_frac": res["gemm"]["achieved"] / PEAK_FP32_MFMA_TFLOPS,
             "gemm_tflops": res["gemm"]["achieved"], "step_roofline_frac": res["step_roofline"]["frac"],
             "step_roofline_bound": res["step_roofline"]["bound"], "factors": res["forms"],
             "hbm_frac": {k: v["frac"] for k, v in res["hbm"].items()},
@@ -418,7 +419,8 @@ def main():
                    "factor_updates": res["updates"], "factor_form": args.form, "factors": res["forms"],
                    "split_k": args.split_k, "series_order": args.series_order, "lds_chain_max": args.chain_max,
                    "seed": args.seed},
-        "roofline": {"bound": "mfma", "kernel": "gemm_grouped<true> (every GEMM stage of the step)",
+        "roofline": {"bound": "mfma", "kernel": "gemm_grouped<true>, and gemm_wave_split in levels with little work (every GEMM "
+                                                "stage of the step, with gemm_fixup)",
                      "achieved": achieved, "peak": PEAK_SPLIT_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_SPLIT_TFLOPS,
                      "peak_basis": "fp32 products as six bf16 MFMA products: a sixth of the dense bf16 peak",
@@ -434,9 +436,12 @@ def main():
         # split GEMM's peak and the algorithmic bytes at the HBM peak, the larger of the two
         # over the measured step time.
         "step_roofline": res["step_roofline"],
-        # executed algorithmic flops of the whole step / (instrumented step time x fp32 MFMA peak);
-        # above 100 where the bf16 pipe does an fp32 product faster than the fp32 MFMA could
+        # executed algorithmic flops of the whole step / (instrumented step time x the split GEMM's
+        # peak): the matrix pipe's utilisation by the products as they run
         "mfma_util_pct": res["mfma_util_pct"],
+        # the same over the fp32 MFMA's peak, for comparison with a step whose products use that
+        # instruction: above 100 where the bf16 pipe does an fp32 product faster than it could
+        "fp32_mfma_equivalent_pct": res["fp32_mfma_equivalent_pct"],
         "paper_order": res["paper_order"],
         "hbm": dict(hbm, peak=PEAK_HBM_GBS, unit="GB/s"),
         "stages": res["stages"],

@@ -65,7 +65,9 @@ def test_workload_sub_record_fields():
            "forms": {"explicit": 811, "factored": 132, "squared": 81},
            "hbm": {"weight": {"frac": 0.8}, "stage_in": {"frac": 0.85}}}
     rec = bench.summary(res)
-    assert rec["gemm_frac"] == pytest.approx(60.0 / 157.3)
+    # the roof of the headline record's roofline.frac, and beside it the fp32 MFMA's
+    assert rec["gemm_frac"] == pytest.approx(60.0 / (2516.6 / 6))
+    assert rec["fp32_mfma_frac"] == pytest.approx(60.0 / 157.3)
     assert rec["workload"] == bench.WORKLOAD_NAMES["many_small"] and rec["unit"] == "steps/s"
     assert set(rec["hbm_frac"]) == {"weight", "stage_in"}
     json.dumps(rec)
