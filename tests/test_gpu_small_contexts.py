@@ -3,8 +3,9 @@ against the fp64 oracle, from injected states that do not commute with the
 gradient's statistics.
 
 The gates are those of one step (tests/parity_metrics.py: 1e-5 on every tensor,
-1e-3 on the factors' informative part, 1e-4 on the applied step); products of
-depth up to 128 in fp32 are off by about 1e-7.
+1e-3 on the factors' informative part, 1e-4 on the applied step), and 2e-6 on the
+state: products of depth up to 128 in fp32 are off by about 1e-7, and an update chains
+eight of them.
 """
 import numpy as np
 import pytest
@@ -74,6 +75,9 @@ def test_one_step_from_an_injected_state(shapes, update, symmetrize, order):
         got = {k: opt.get_state(l, k).cpu().numpy() for k in ("L", "R", "mom", "mom_sgd")}
         check_layer(got, {"L": o.L, "R": o.R, "mom": o.m, "mom_sgd": o.m_sgd}, pg[l].cpu().numpy(), po[l], prev[l],
                     HP["lr"], HP["weight_decay"], STEP, f"layer {l} {shapes[l]}")
+        for k, want in (("L", o.L), ("R", o.R), ("mom", o.m), ("mom_sgd", o.m_sgd)):
+            err = np.linalg.norm(got[k] - want) / np.linalg.norm(want)
+            assert err <= 2e-6, (l, shapes[l], k, err)
         if symmetrize:
             assert np.array_equal(got["L"], got["L"].T) and np.array_equal(got["R"], got["R"].T), l
 

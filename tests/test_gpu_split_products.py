@@ -23,6 +23,13 @@ def gamma(K):
     return (6 * -(-K // 32) + 4 + 8) * 2.0 ** -23
 
 
+def typical(m, n):
+    """2-norm of the relative error of L G R for random operands: every MFMA rounds the running sum, by up to 2^-24
+    of it and 2^-24 / sqrt(3) in the mean square, and the running sum grows like the square root of K (a half in the
+    mean square); the ends and the terms left out as two roundings more for each product."""
+    return sum(2.0 ** -24 * np.sqrt((6 * -(-K // 32) / 2 + 2) / 3) for K in (m, n)) + 2.0 ** -24
+
+
 # One slab of K (32), two and three (the loop's short forms), tiles with remainders on
 # either side, quadrants outside the product, several tiles and split tiles.
 @pytest.mark.parametrize("m,n", [(1, 32), (32, 33), (64, 64), (65, 96), (130, 97), (257, 129), (31, 520), (640, 1152)])
@@ -48,8 +55,29 @@ def test_between_updates_product_is_componentwise_fp32(m, n, symmetrize, graded,
     want = b * (L @ G @ R)
     bound = b * (gamma(m) + gamma(n)) * (np.abs(L) @ np.abs(G) @ np.abs(R))
     off = np.max(np.abs(got - want) / bound)
-    print(f"{m} x {n}: largest error {off:.3f} of the bound", flush=True)
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print(f"{m} x {n}: largest error {off:.3f} of the bound, 2-norm {err:.2e} of {typical(m, n):.2e}", flush=True)
     assert off <= 1.0
+    if not graded:      # the bound is the worst case and grows with K; typical errors are far below it
+        assert err <= typical(m, n)
+
+
+# The same through the LDS kernels of small contexts, of both size classes.
+@pytest.mark.parametrize("m,n", [(1, 32), (33, 64), (64, 64), (17, 48), (65, 96), (128, 128), (100, 33), (64, 128)])
+@pytest.mark.parametrize("graded", [False, True])
+def test_small_context_product_is_componentwise_fp32(m, n, graded):
+    rng = np.random.default_rng([m, n, graded, 7])
+    L, R, G = (rng.standard_normal(s).astype(np.float32) for s in ((m, m), (n, n), (m, n)))
+    L, R = L + L.T, R + R.T
+    if graded:
+        G *= (10.0 ** rng.uniform(-6, 6, (m, 1)) * 10.0 ** rng.uniform(-6, 6, (1, n))).astype(np.float32)
+    got = mom_after([(m, n)], L, R, G)
+    b = 1.0 - np.float64(np.float32(0.9))
+    L, R, G = (x.astype(np.float64) for x in (L, R, G))
+    want = b * (L @ G @ R)
+    assert np.all(np.abs(got - want) <= b * (gamma(m) + gamma(n)) * (np.abs(L) @ np.abs(G) @ np.abs(R)))
+    if not graded:
+        assert np.linalg.norm(got - want) <= typical(m, n) * np.linalg.norm(want)
 
 
 @pytest.mark.parametrize("shape", [(64, 200), (33, 130), (160, 32)])
@@ -129,3 +157,48 @@ def test_an_infinity_stays_one(shape, layers, kw):
     got = mom_after([shape] * layers, np.eye(m, dtype=np.float32), R, G, **kw)
     assert np.array_equal(got[m // 2], np.copysign(np.inf, R[5]).astype(np.float32))
     assert np.all(np.isnan(np.delete(got, m // 2, 0)))
+
+
+def terms(x):
+    """The three bf16 terms of fp32 x: the first rounded (half away from zero), the others cut off."""
+    out = []
+    for t in range(3):
+        u = x.view(np.uint32) + np.uint32(0x8000 if t == 0 else 0)
+        out.append((u & np.uint32(0xFFFF0000)).view(np.float32))
+        x = x - out[-1]
+    assert not x.any()
+    return [t.astype(np.float64) for t in out]
+
+
+def six(a, b):
+    """The fp32 product as the kernels form it: six of the nine term products, rounded to fp32."""
+    a, b = terms(a), terms(b)
+    return sum(a[i] * b[j] for i in range(3) for j in range(3 - i)).astype(np.float32)
+
+
+@pytest.mark.parametrize("shape,layers,kw", PATHS)
+def test_one_live_term_is_unbiased_to_the_last_bit(shape, layers, kw):
+    """Diagonal L and R: every product has one term, so nothing averages out. Largest error: 2^-23 for the
+    terms left out and 2^-24 for the sum's rounding, for each product, and 2^-24 each for 1 - beta1's
+    product and m. Mean square: as in the split's emulation on the same numbers. Mean: zero; a split that
+    cut its first term off would be 2^-24 off in the mean, all errors towards zero, and one without the
+    a1 b1 term or the third terms 2^-18 off in the mean square."""
+    (m, n), rng = shape, np.random.default_rng(13)
+    sign = lambda *s: rng.choice((-1.0, 1.0), s)  # noqa: E731
+    L, R = ((rng.uniform(1, 2, d) * sign(d)).astype(np.float32) for d in shape)
+    G = (rng.uniform(1, 2, (m, n)) * sign(m, n)).astype(np.float32)
+    got = mom_after([shape] * layers, np.diag(L), np.diag(R), G, **kw).astype(np.float64)
+    b = np.float32(1.0) - np.float32(0.9)
+    want = np.float64(b) * L[:, None].astype(np.float64) * G * R.astype(np.float64)
+    e = got / want - 1.0
+    emulated = (b * six(six(np.repeat(L[:, None], n, 1), G), np.repeat(R[None], m, 0))) / want - 1.0
+    rms = lambda x: np.sqrt((x * x).mean())  # noqa: E731
+    print(f"{shape}: mean {e.mean():.1e}, rms {rms(e):.2e} (emulated {rms(emulated):.2e}), max {np.abs(e).max():.2e}",
+          flush=True)
+    assert np.abs(e).max() <= 2 * (2.0 ** -23 + 2.0 ** -24) + 2 * 2.0 ** -24
+    # The emulation rounds each sum once. The matrix unit also aligns the smaller terms' sum to the last
+    # product before it adds, which may drop up to 2^-24 of the result with either sign: 2^-24 / sqrt(3)
+    # in the mean square for each of the two products.
+    assert rms(e) <= np.sqrt(rms(emulated) ** 2 + 2 * (2.0 ** -24) ** 2 / 3)
+    # 2^-29 for what rounding to nearest leaves, and four standard deviations of the mean
+    assert abs(e.mean()) <= 2.0 ** -29 + 4 * 2.0 ** -24 / np.sqrt(e.size)

@@ -16,6 +16,7 @@ from paper_2310_12298_amd.workloads import gradient, initial_params  # noqa: E40
 pytestmark = pytest.mark.gpu
 HP = dict(lr=0.1, beta2=0.9, beta1=0.9, weight_decay=5e-5)
 KINDS = ("L", "R", "mom", "mom_sgd")
+SPLIT = (512, 1024)     # its levels have split tiles, so the scratch holds a split workspace
 
 
 def to_dev(x):
@@ -56,7 +57,8 @@ class Pair:
 
 
 def test_alternating_layers_and_options():
-    pairs = [Pair((130, 260)), Pair((130, 260), symmetrize=False), Pair((130, 260), precond_interval=2),
+    assert any(v[1] for v in Jorge.plan_stages([SPLIT]).values())
+    pairs = [Pair(SPLIT), Pair((130, 260)), Pair((130, 260), symmetrize=False), Pair((130, 260), precond_interval=2),
              Pair((48, 40)), Pair((100, 70)), Pair((33, 577)), Pair((256, 300), series_order=3)]
     for _ in range(3):
         for p in pairs:
@@ -76,7 +78,7 @@ def test_a_dropped_plan_is_built_again():
     first.check()
 
 
-@pytest.mark.parametrize("shape", [(70, 301), (33, 47), (100, 65)])
+@pytest.mark.parametrize("shape", [(70, 301), (33, 47), (100, 65), SPLIT])
 @pytest.mark.parametrize("value", [math.nan, math.inf])
 def test_a_non_finite_step_leaves_nothing_behind(shape, value):
     p = Pair(shape)
