@@ -32,11 +32,14 @@
  *
  * Matrix products are products of fp32 matrices accumulated in fp32. Each is
  * formed from bf16 terms that hold the operands exactly (three per element, six
- * of the nine term products; what is left out is below 2^-22 of a product), or
+ * of the nine term products; what is left out is below 2^-23 of a product), or
  * by the fp32 matrix instructions where the terms do not hold an operand: a
  * non-zero magnitude below 2^-110 or above 3.39e38, an infinity, a NaN. Such
  * values take their fp32 course (subnormals and infinities included); the tiles
- * they enter take up to 2.3 times as long.
+ * they enter take up to 2.3 times as long. Against products on the fp32 matrix
+ * instructions throughout, long sums err less and sums of one or two non-zero
+ * terms (diagonal factors, layers one row or column wide) up to 1.3 times as much
+ * in the mean square.
  *
  * A context is not re-entrant: calls on one context must not overlap.
  * Distinct contexts are independent.

@@ -46,13 +46,14 @@
 //   precond   T = L_hat G, then G~ = T R_hat fused with m <- beta1 m + (1-beta1) G~;
 //             on update steps a factored factor with d > 3k supplies A_new H from the
 //             update's own terms instead (low-rank preconditioning)
-//   lfinal    ||m||, ||m_SGD||, grafted step g
+//   lfinal    ||m||, ||m_SGD||, grafted step g (in the weight launch where the norms
+//             have few partial sums)
 //   weight    theta <- theta (1 - lr wd) - g m
 // When every factor has padded size up to hp.lds_chain_max (at most 128), none of
 // these launches runs: the small-context kernels take the whole step with their
 // matrices in LDS (up to 64: small_step64_kernel, one workgroup per layer; up to
-// 128: small_chain128_kernel, one per factor, then small_apply128_kernel, one
-// per layer).
+// 128: small_chain128_kernel, one per factor above 64 or pair of others, then
+// small_apply128_kernel, one per layer).
 // Non-update steps run stage-in, precond, lfinal and weight only.
 #include <hip/hip_runtime.h>
 
@@ -423,8 +424,10 @@ void order_for_xcds(std::vector<TileDesc>& tiles) {
 
 // Cost model of a grouped launch for the split planner, in units of one k
 // step of a 128 x 128 tile on a whole compute unit (0.058 us when the constants were
-// fitted, on the fp32 MFMA; 0.04 us now, with which fixup starts of 150-300 and unit
-// costs of 48-96 plan within 0.5% of these or worse). Workgroup b
+// fitted, on the fp32 MFMA; 0.04 us now). With fixup starts of 150 and 300 and unit
+// costs of 48 and 96 the steps of ResNet-50, 512 layers of 32-256, 8192 x 512 and 768 x
+// 3000 stay within 0.5%; a start of 300 with 96 gains 1.5% on four layers of 1024 x
+// 1024 (643 -> 634 us) and loses 1.6% on 512 x 4608 (913 -> 927). Workgroup b
 // runs on XCD b mod kXcds, on one of that XCD's CUs. A CU holds two work
 // units at a time; two resident units share its throughput, a unit alone on
 // a CU runs at kLoneRate of it. A work unit costs its K plus its own
@@ -1623,7 +1626,8 @@ jorge_status run_update(jorge_ctx* c, double beta2) {
 // the last few kinds of layer (shape and options), newest first. Building a plan
 // (layout, launch tables, split model) and uploading its tables took 1.7 of the
 // 2.0 ms of a 256 x 1024 call; a caller that steps the layers of one model in turn
-// finds them here. Host memory only, some 100 KB each, bounded by kNoallocPlans
+// finds them here (256 x 1024 and 512 x 512 in turn 366 us for both; 175 and 134 each
+// again and again, whose tables also stay in the scratch). Host memory only, some 100 KB each, bounded by kNoallocPlans
 // per device and freed at process end.
 constexpr int kMaxDevices = 64;
 constexpr size_t kNoallocPlans = 16;

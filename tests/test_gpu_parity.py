@@ -365,7 +365,7 @@ def test_split_k_parity_and_determinism(form):
 
 
 SMALL_SHAPES = [(64, 64), (32, 48), (5, 3), (40, 1), (33, 60), (64, 32), (1, 64), (50, 17)]
-# Padded sizes 96 and 128 (and smaller ones beside them), for lds_chain128_kernel.
+# Padded sizes 96 and 128 (and smaller ones beside them), for the small-context kernels up to 128.
 SMALL128_SHAPES = [(128, 128), (96, 128), (100, 70), (128, 40), (65, 97), (3, 128), (128, 90)]
 
 
@@ -407,7 +407,7 @@ def test_lds_chain_small_factors(symmetrize):
 @pytest.mark.parametrize("series_order", [2, 3])
 def test_lds_chain128_small_factors(series_order):
     """In a context whose factors all have padded size <= 128, those of 96 and 128 run
-    their whole update in lds_chain128_kernel (and the smaller ones in lds_chain_kernel):
+    their whole update in a workgroup each and the smaller ones two to a workgroup:
     against the oracle, against the grouped levels, bitwise symmetric."""
     shapes = SMALL128_SHAPES
     say("LDS chain 128, series order", series_order)
