@@ -488,17 +488,16 @@ __device__ __forceinline__ void st4_at(float* base, unsigned byte_off, f32x4 v) 
 }
 
 // The epilogue body for one combination of flags F and symmetry UP, known
-// at compile time. value = ci [row == col < valid_m] + cx X + cc acc.
+// at compile time. value = cx X + cc acc.
 // Offsets are 32-bit (every matrix has fewer than 2^32 elements) from
 // uniform base pointers; per-element masks are only evaluated on edge tiles
 // and on diagonal tiles of symmetric results.
 template <int F, bool UP, bool MASKED, int NB>
 __device__ __forceinline__ double epilogue_body(const GemmProblem& p, const Place& at, const f32x4 (&acc)[NB],
-                                                float ci, float cx, float cc) {
+                                                float cx, float cc) {
     constexpr bool kReadX = (F & EF_READX) != 0;
     constexpr bool kRead = (F & (EF_READX | EF_DOT)) != 0;
     const bool diag = MASKED && UP && at.diag;
-    const bool ident = kReadX && ci != 0.f && at.diag;
     constexpr double w_off = UP ? 2.0 : 1.0;   // off-diagonal tiles of a symmetric result
     float* C = p.C;
     float* C2 = p.C2;
@@ -542,10 +541,7 @@ __device__ __forceinline__ double epilogue_body(const GemmProblem& p, const Plac
             const float v = acc[b][e];
             float o = cc * v;
             if constexpr (kRead) x[e] = xv[b][e];
-            if constexpr (kReadX) {
-                const float id = (ident && rowb + e == col && col < p.valid_m) ? ci : 0.0f;
-                o = (id + cx * x[e]) + o;
-            }
+            if constexpr (kReadX) o = cx * x[e] + o;
             out[e] = o;
         }
         if (!diag) {
@@ -585,7 +581,7 @@ __device__ __forceinline__ double epilogue_body(const GemmProblem& p, const Plac
 // the launch tables the library builds; kept so every combination works).
 template <int NB>
 __device__ __forceinline__ double epilogue_generic(const GemmProblem& p, const Place& at, const f32x4 (&acc)[NB],
-                                                   float ci, float cx, float cc) {
+                                                   float cx, float cc) {
     double part = 0.0;
     const int F = p.flags;
     const bool up = p.upper != 0;
@@ -603,7 +599,7 @@ __device__ __forceinline__ double epilogue_generic(const GemmProblem& p, const P
             const float v = acc[b][e];
             const float xe = (F & (EF_READX | EF_DOT)) ? ld_at(X, (unsigned)row * sx + 4u * (unsigned)col) : 0.f;
             float o = cc * v;
-            if (F & EF_READX) o = (((row == col && row < p.valid_m) ? ci : 0.0f) + cx * xe) + o;
+            if (F & EF_READX) o = cx * xe + o;
             const double w = (up && row != col) ? 2.0 : 1.0;
             if (F & EF_NORM) part += w * (double)o * (double)o;
             if (F & EF_DOT) part += w * (double)v * (double)xe;
@@ -679,17 +675,17 @@ __device__ __forceinline__ double gemm_epilogue_part(const GemmProblem& p, const
         else
             part = epilogue_momentum<true>(p, at, acc, beta1);
     } else {
-        float ci = 0.f, cx = 0.f, cc = 1.f;
+        float cx = 0.f, cc = 1.f;
         if (p.coef != CO_ONE) {
             const FactorScalars* sc = p.sc;
             switch (p.coef) {
-                case CO_POLY: ci = 1.f; cx = -sc->a; cc = sc->b; break;
-                case CO_SCALE: cc = sc->sf; break;
+                case CO_POLY: cx = -sc->a; cc = sc->b; break;
+                case CO_SCALE: cx = sc->sf; cc = sc->sf; break;
                 case CO_WMIX: cx = sc->a; cc = -sc->b; break;
                 case CO_SYR2K: cx = sc->sf; cc = -0.5f * sc->sf; break;
                 case CO_LITUPD: cx = sc->sf; cc = -sc->sf; break;
                 case CO_VSER: cx = sc->b; cc = -sc->e; break;
-                case CO_POLY3: ci = 1.f; cx = -sc->a; break;
+                case CO_POLY3: cx = -sc->a; break;
                 case CO_WMIX3: cx = sc->a; cc = -1.f; break;
                 default: break;
             }
@@ -697,40 +693,40 @@ __device__ __forceinline__ double gemm_epilogue_part(const GemmProblem& p, const
         const int key = flags | (p.upper ? 256 : 0);
         const bool masked = row_end > p.M || col_end > p.N || (p.upper && at.diag);
         switch (key) {
-            case EF_STORE: part = masked ? epilogue_body<EF_STORE, false, true>(p, at, acc, ci, cx, cc)
-                            : epilogue_body<EF_STORE, false, false>(p, at, acc, ci, cx, cc); break;
-            case EF_STORE | 256: part = masked ? epilogue_body<EF_STORE, true, true>(p, at, acc, ci, cx, cc)
-                            : epilogue_body<EF_STORE, true, false>(p, at, acc, ci, cx, cc); break;
-            case EF_STORE_T: part = masked ? epilogue_body<EF_STORE_T, false, true>(p, at, acc, ci, cx, cc)
-                            : epilogue_body<EF_STORE_T, false, false>(p, at, acc, ci, cx, cc); break;
-            case EF_DOT | 256: part = masked ? epilogue_body<EF_DOT, true, true>(p, at, acc, ci, cx, cc)
-                            : epilogue_body<EF_DOT, true, false>(p, at, acc, ci, cx, cc); break;
+            case EF_STORE: part = masked ? epilogue_body<EF_STORE, false, true>(p, at, acc, cx, cc)
+                            : epilogue_body<EF_STORE, false, false>(p, at, acc, cx, cc); break;
+            case EF_STORE | 256: part = masked ? epilogue_body<EF_STORE, true, true>(p, at, acc, cx, cc)
+                            : epilogue_body<EF_STORE, true, false>(p, at, acc, cx, cc); break;
+            case EF_STORE_T: part = masked ? epilogue_body<EF_STORE_T, false, true>(p, at, acc, cx, cc)
+                            : epilogue_body<EF_STORE_T, false, false>(p, at, acc, cx, cc); break;
+            case EF_DOT | 256: part = masked ? epilogue_body<EF_DOT, true, true>(p, at, acc, cx, cc)
+                            : epilogue_body<EF_DOT, true, false>(p, at, acc, cx, cc); break;
             case EF_STORE | EF_STORE_T | EF_NORM:
-                part = masked ? epilogue_body<EF_STORE | EF_STORE_T | EF_NORM, false, true>(p, at, acc, ci, cx, cc)
-                            : epilogue_body<EF_STORE | EF_STORE_T | EF_NORM, false, false>(p, at, acc, ci, cx, cc);
+                part = masked ? epilogue_body<EF_STORE | EF_STORE_T | EF_NORM, false, true>(p, at, acc, cx, cc)
+                            : epilogue_body<EF_STORE | EF_STORE_T | EF_NORM, false, false>(p, at, acc, cx, cc);
                 break;
             case EF_STORE_T | EF_READX:
-                part = masked ? epilogue_body<EF_STORE_T | EF_READX, false, true>(p, at, acc, ci, cx, cc)
-                            : epilogue_body<EF_STORE_T | EF_READX, false, false>(p, at, acc, ci, cx, cc);
+                part = masked ? epilogue_body<EF_STORE_T | EF_READX, false, true>(p, at, acc, cx, cc)
+                            : epilogue_body<EF_STORE_T | EF_READX, false, false>(p, at, acc, cx, cc);
                 break;
             case EF_STORE | EF_READX:
-                part = masked ? epilogue_body<EF_STORE | EF_READX, false, true>(p, at, acc, ci, cx, cc)
-                            : epilogue_body<EF_STORE | EF_READX, false, false>(p, at, acc, ci, cx, cc);
+                part = masked ? epilogue_body<EF_STORE | EF_READX, false, true>(p, at, acc, cx, cc)
+                            : epilogue_body<EF_STORE | EF_READX, false, false>(p, at, acc, cx, cc);
                 break;
             case EF_STORE | EF_STORE_T:
-                part = masked ? epilogue_body<EF_STORE | EF_STORE_T, false, true>(p, at, acc, ci, cx, cc)
-                              : epilogue_body<EF_STORE | EF_STORE_T, false, false>(p, at, acc, ci, cx, cc);
+                part = masked ? epilogue_body<EF_STORE | EF_STORE_T, false, true>(p, at, acc, cx, cc)
+                              : epilogue_body<EF_STORE | EF_STORE_T, false, false>(p, at, acc, cx, cc);
                 break;
             case EF_STORE | EF_STORE_T | EF_READX:
-                part = masked ? epilogue_body<EF_STORE | EF_STORE_T | EF_READX, false, true>(p, at, acc, ci, cx, cc)
-                              : epilogue_body<EF_STORE | EF_STORE_T | EF_READX, false, false>(p, at, acc, ci, cx, cc);
+                part = masked ? epilogue_body<EF_STORE | EF_STORE_T | EF_READX, false, true>(p, at, acc, cx, cc)
+                              : epilogue_body<EF_STORE | EF_STORE_T | EF_READX, false, false>(p, at, acc, cx, cc);
                 break;
             case EF_STORE | EF_READX | 256:
-                part = masked ? epilogue_body<EF_STORE | EF_READX, true, true>(p, at, acc, ci, cx, cc)
-                            : epilogue_body<EF_STORE | EF_READX, true, false>(p, at, acc, ci, cx, cc);
+                part = masked ? epilogue_body<EF_STORE | EF_READX, true, true>(p, at, acc, cx, cc)
+                            : epilogue_body<EF_STORE | EF_READX, true, false>(p, at, acc, cx, cc);
                 break;
             default:  // any other combination: every flag tested at run time
-                part = epilogue_generic(p, at, acc, ci, cx, cc);
+                part = epilogue_generic(p, at, acc, cx, cc);
                 break;
         }
     }

@@ -247,8 +247,8 @@ __global__ __launch_bounds__(kEwThreads) void symmetrize_kernel(const FactorDev*
 // Contexts whose factors all have padded size <= 128. A factor's whole update
 // runs in one team of waves, in the explicit order of Algorithm 2 with its
 // matrices in LDS: A^2, A^4, M = H H^T, X = A^4 M with ||X||_F, (beta, c, s)
-// (Appendix A.1, Eq. 8-9), P = I - (c/4) X + (5c^2/32) X X (Eq. 6; with series
-// order 3, P = I - a X + X V, V = b X - e X X), Z = s A P and A <- (Z + Z^T)/2 (or
+// (Appendix A.1, Eq. 8-9), P - I = -(c/4) X + (5c^2/32) X X (Eq. 6; with series
+// order 3, -a X + X V, V = b X - e X X), Z = s A + s A (P - I) and A <- (Z + Z^T)/2 (or
 // Z). The rest of the step (m_SGD, L G R, momentum, norms, grafted weight update)
 // runs in one workgroup per layer, which holds the gradient in LDS and sums the
 // norms itself, so nothing of the step but its state passes through memory.
@@ -478,7 +478,7 @@ __device__ __forceinline__ void chain_update(const FactorDev& F, int side, int t
                                              const LayerDev& L, const float* __restrict__ G, bool deep, bool live, double beta2, int mode, int symmetrize, int order, float* m0, float* m1,
                                              double* red) {
     constexpr int NB = T::BI * T::BJ;
-    const int dp = F.dp, kp = F.kp, d = F.d;
+    const int dp = F.dp, kp = F.kp;
     const Piece p = piece_of<T>(wave, dp, dp);
     f32x4 av[T::AV], acc[NB];
     factor_load<T>(t, F.A, dp, av);
@@ -553,19 +553,19 @@ __device__ __forceinline__ void chain_update(const FactorDev& F, int side, int t
         bb = 1.0f;
     }
     __syncthreads();
-    // P = I - a X + b X X (or I - a X + X V), stored transposed; A takes X's place
-    piece_each<T>(p, [&](int row, int col, int q, int e) {
-        const float id = (row == col && row < d) ? 1.0f : 0.0f;
-        acc[q][e] = (id - a * x[q][e]) + bb * acc[q][e];
-    });
+    // P - I = -a X + b X X (or -a X + X V), stored transposed; A takes X's place
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[q][e] = bb * acc[q][e] - a * x[q][e];
     piece_store<T, true>(p, m1, acc);
     factor_store<T>(t, av2, m0, false);
     __syncthreads();
-    // Z = s A P (B = P: its rows in k are the rows of P^T in m1)
+    // Z = s A + s A (P - I) (B = P - I: its rows in k are the rows of its transpose in m1;
+    // the identity stays out of the product as in the levels, see add_explicit)
     piece_mma<T>(p, m0, m1, dp, acc);
+    piece_each<T>(p, [&](int row, int col, int q, int e) { acc[q][e] = sf * m0[row * T::LD + col] + sf * acc[q][e]; });
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < NB; ++q) acc[q] = acc[q] * sf;
     piece_store<T, false>(p, m0, acc);
     __syncthreads();
     // A <- (Z + Z^T)/2 or Z, in the accumulators' layout: four consecutive rows of a

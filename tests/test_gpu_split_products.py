@@ -202,3 +202,32 @@ def test_one_live_term_is_unbiased_to_the_last_bit(shape, layers, kw):
     assert rms(e) <= np.sqrt(rms(emulated) ** 2 + 2 * (2.0 ** -24) ** 2 / 3)
     # 2^-29 for what rounding to nearest leaves, and four standard deviations of the mean
     assert abs(e.mean()) <= 2.0 ** -29 + 4 * 2.0 ** -24 / np.sqrt(e.size)
+
+
+@pytest.mark.parametrize("d,kw", [(64, {}), (128, {}), (64, dict(lds_chain_max=0)), (96, dict(lds_chain_max=0, split_k=False)),
+                                  (256, {}), (96, dict(lds_chain_max=0, symmetrize=False)), (64, dict(symmetrize=False)),
+                                  (128, dict(series_order=3)), (256, dict(series_order=3))])
+def test_a_small_update_does_not_pull_the_factor_down(d, kw):
+    """An update with P close to I multiplies every element of A by s and adds little: rounded to nearest, its
+    errors have no mean (2^-29, and four standard deviations of the mean of 2^-24). A product A P with
+    the identity in P would pass through the matrix unit's alignment, which does not round to nearest: 6e-8 to
+    8e-8 in the mean at every update."""
+    rng = np.random.default_rng([d, 17])
+    A = rng.uniform(0.5, 1.5, (d, d)).astype(np.float32)
+    A = (A + A.T) / 2
+    G = (rng.standard_normal((d, d)) * 0.2 / d ** 2.5).astype(np.float32)      # P - I of 1e-5 to 1e-4
+    ctx = Jorge([(d, d)], factor_form="explicit", beta_mode="fixed", **kw)
+    for k in ("L", "R"):
+        ctx.set_state(0, k, torch.from_numpy(A).cuda())
+    ctx.step([torch.zeros((d, d), device="cuda")], [torch.from_numpy(G).cuda()], 0.1, 0.9, 0.9, 0.0)
+    A, G = A.astype(np.float64), G.astype(np.float64)
+    for k, M in (("L", G @ G.T), ("R", G.T @ G)):
+        X, c = np.linalg.matrix_power(A, 4) @ M, (1.0 - 0.9) / 0.9
+        S = -c / 4 * X + 5 * c * c / 32 * X @ X - (15 * c ** 3 / 128 * X @ X @ X if kw.get("series_order") == 3 else 0)
+        Z = np.float64(np.float32(0.9 ** -0.25)) * (A + A @ S)      # s as the kernels hold it
+        assert 1e-6 < np.abs(S).max() < 1e-2
+        want = Z if kw.get("symmetrize") is False else (Z + Z.T) / 2
+        e = ctx.get_state(0, k).double().cpu().numpy() / want - 1.0
+        print(f"{d} {kw} {k}: mean {e.mean():.1e}, max {np.abs(e).max():.1e}, largest of P - I {np.abs(S).max():.1e}", flush=True)
+        assert abs(e.mean()) <= 2.0 ** -29 + 4 * 2.0 ** -24 / d
+        assert np.abs(e).max() <= 4 * 2.0 ** -24        # s, s A, its sum with s A (P - I), and the mean with Z^T
