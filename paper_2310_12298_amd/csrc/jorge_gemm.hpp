@@ -75,8 +75,8 @@ __device__ __forceinline__ f32x4 gload4(const float* p) {
 // 2^-23 |a b| together, and a K-long sum takes 6 K / 32 roundings of the
 // accumulator where the fp32 MFMA takes K / 4. Measured against fp64 on Gaussian
 // operands (relative 2-norm): 3.4e-7 at K = 512 and 1.04e-6 at K = 4096, where the
-// fp32 MFMA has 4.0e-7 and 1.1e-6; over the steps of 38 shapes 0.82 of its error in the
-// geometric mean. A sum with one live term has only its own roundings and is behind:
+// fp32 MFMA has 4.0e-7 and 1.1e-6; over the steps of 38 shapes 0.66 of its error in the
+// geometric mean (0.82 by the products alone). A sum with one live term has only its own roundings and is behind:
 // 5.7e-8 against 4.4e-8 for L G R with diagonal L and R (from the largest term product to
 // the smallest 8.1e-8, with the second-order terms before the leading one 7.1e-8).
 // The bf16 MFMA does 16 times the fp32 one's flops per cycle, so six of them are
