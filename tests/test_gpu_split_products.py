@@ -121,6 +121,19 @@ PATHS = [((48, 64), 1, {}), ((100, 128), 1, {}), ((130, 260), 1, {}), ((640, 115
          ((640, 1152), 1, dict(split_k=False)), ((300, 100), 1, dict(symmetrize=False)), ((64, 200), 300, {})]
 
 
+def test_paths_are_what_they_are_for():
+    """(units, split tiles, small-mode blocks) of the level (L G) R on each path."""
+    blocks = lambda m, n: -(-m // 32) * -(-n // 32)  # noqa: E731
+    tiles = lambda m, n: -(-m // 128) * -(-n // 128)  # noqa: E731
+    got = [Jorge.plan_stages([s] * n, precond_interval=2, graft=False, **kw)["precond_R"] for s, n, kw in PATHS]
+    assert got[0] == got[1] == (0, 0, 0)                            # small contexts
+    assert got[2] == (blocks(130, 260), 0, 0)                       # wave-split
+    assert got[3][1] > 0 and got[3][0] > tiles(640, 1152)           # split tiles
+    assert got[4] == (tiles(640, 1152), 0, 0)                       # whole tiles
+    assert got[5] == (tiles(300, 100), 0, 0)                        # whole tiles, R_hat read across its rows
+    assert got[6][2] == 300 * 4                                     # small-mode blocks: 64 x 200 in 64 x 64
+
+
 @pytest.mark.parametrize("shape,layers,kw", PATHS)
 def test_magnitudes_the_terms_do_not_hold(shape, layers, kw):
     """Below 2^-110 three bf16 terms drop bits, above 3.39e38 the first overflows: the product is

@@ -53,7 +53,9 @@ def test_noalloc_matches_the_context_step_on_shrinking_layers():
     # Levels with split tiles, wave-split levels, then the small-context kernels.
     split = lambda shape: any(v[1] for v in Jorge.plan_stages([shape]).values())  # noqa: E731
     units = lambda shape: any(v[0] for v in Jorge.plan_stages([shape]).values())  # noqa: E731
-    assert split((512, 1024)) and not split((256, 1152)) and units((256, 1152)) and not units((64, 100))
+    assert split((512, 1024)) and not split((256, 1152)) and not units((64, 100))
+    # (256, 1152): a unit per 32 x 32 block of L G
+    assert Jorge.plan_stages([(256, 1152)])["uprecond_L"][0] == (256 // 32) * (1152 // 32)
     for shape in [(512, 1024), (256, 1152), (200, 300), (64, 100), (48, 40)]:
         say("noalloc vs context", shape)
         _compare_steps(shape, 3)
