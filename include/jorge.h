@@ -36,7 +36,7 @@
  * by the fp32 matrix instructions where the terms do not hold an operand: a
  * non-zero magnitude below 2^-110 or above 3.39e38, an infinity, a NaN. Such
  * values take their fp32 course (subnormals and infinities included); the tiles
- * they enter take up to 2.3 times as long. Against products on the fp32 matrix
+ * they enter are formed twice (up to 2.3 times the time). Against products on the fp32 matrix
  * instructions throughout, long sums err less and sums of one or two non-zero
  * terms (diagonal factors, layers one row or column wide) up to 1.3 times as much
  * in the mean square.
