@@ -475,7 +475,8 @@ __device__ __forceinline__ double sum_waves(const double* red) {
 // transposed, in m1 (behind a barrier).
 template <class T, bool WIDE = false>
 __device__ __forceinline__ void chain_update(const FactorDev& F, int side, int t, int wave, float (&g)[T::GV],
-                                             const LayerDev& L, const float* __restrict__ G, bool deep, bool live, double beta2, int mode, int symmetrize, int order, float* m0, float* m1,
+                                             const LayerDev& L, const float* __restrict__ G, bool deep, bool live,
+                                             double beta2, int mode, int symmetrize, int order, float* m0, float* m1,
                                              double* red) {
     constexpr int NB = T::BI * T::BJ;
     const int dp = F.dp, kp = F.kp;

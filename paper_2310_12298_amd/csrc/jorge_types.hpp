@@ -17,8 +17,9 @@ enum EpiFlags : int {
     EF_READX = 32,     // the value reads X[row][col] (coefficient cx below)
 };
 
-// Coefficient sets: value = cx X[row][col] + cc acc, with (a, b, e, s) = (c/4, 5c^2/32, 15c^3/128, beta^(-1/4)) of the factor
-// being updated (e: the cubic term of Eq. 5, kept only with series order 3).
+// Coefficient sets: value = cx X[row][col] + cc acc, with (a, b, e, s) = (c/4,
+// 5c^2/32, 15c^3/128, beta^(-1/4)) of the factor being updated (e: the cubic term of
+// Eq. 5, kept only with series order 3).
 enum Coef : int {
     CO_ONE = 0,     // (0, 1)       plain product
     CO_POLY = 1,    // (-a, b)      P - I = -(c/4) X + (5c^2/32) X X      (Eq. 6)
